@@ -26,7 +26,7 @@ from paper_1804_09741_amd import inputs as I
 from paper_1804_09741_amd import motifs as M
 
 SWITCHES_PER_ARC = 10
-K7_ROWS = 1 << 14  # more than the classes of any k = 7 case's graph (about 7,000)
+K7_ROWS = 1 << 16  # the most classes of one graph that count7 returns by default
 
 
 def listed():
@@ -193,6 +193,8 @@ def prepare(case, seed):
         made, _ = ctx.randomise(s.graphs[0], case["randoms"], s.seed, SWITCHES_PER_ARC)
         s.graphs.extend(made)
     if op == "count7":
+        # the classes of all graphs as one table (graph, place, code and count)
+        s.classes = np.zeros((len(s.graphs), K7_ROWS, 2), dtype=np.uint64)
         return s
     s.table = ctx.table(case["k"])
     if op in ("run", "static", "ensemble"):
@@ -220,11 +222,9 @@ def run(s):
         return s.d_hist
     if op == "count7":
         out, totals, _ = _ctx().count7(s.graphs)
-        # the classes of all graphs as one table (graph, place, code and count)
-        classes = np.zeros((len(out), K7_ROWS, 2), dtype=np.uint64)
-        for row, (codes, counts) in zip(classes, out):
+        for row, (codes, counts) in zip(s.classes, out):
             row[:len(codes), 0], row[:len(codes), 1] = codes, counts
-        return {"classes": classes, "totals": totals}
+        return {"classes": s.classes, "totals": totals}
     if op == "ensemble":
         ctx, stream = _ctx(), torch.cuda.current_stream()
         made, accepted = ctx.randomise(s.graphs[0], s.case["randoms"], s.seed, SWITCHES_PER_ARC)
