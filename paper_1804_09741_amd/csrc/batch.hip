@@ -43,6 +43,9 @@ struct mk_batch {
     uint32_t *d_counters = nullptr;
     uint32_t *d_unit_begin = nullptr;    // first unit of every graph, plus the total
     unsigned long long *d_hist_own = nullptr;
+    unsigned long long *d_hist_copies = nullptr;  // copies > 1: what the waves add to
+                                                  // (behind the units, one allocation)
+    uint32_t copies = 1;
     uint32_t *d_wave_scratch = nullptr;  // core method: per-workgroup arc lists
     void *d_marks = nullptr;             // MK_MARKS_GLOBAL: per-workgroup marks
     size_t mark_stride = 0;              //   marks per workgroup
@@ -195,6 +198,8 @@ static EnumConfig enum_config(const mk_batch *b)
                 (b->k <= 6 && (b->debug_flags & (kDebugNoHash | kDebugFlushAlways)) ? kVarDebug : 0);
     c.marks = b->d_marks;
     c.mark_stride = b->mark_stride;
+    c.hist_copies = b->copies;
+    c.copy_stride = b->table ? hist_copy_stride(b->ng, b->table->num_classes) : 0;
     return c;
 }
 
@@ -219,7 +224,10 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
     int rc = fill_u32(b->d_counters, 0, kNumCounters, stream);
     if (rc) return rc;
     if (hist) {
-        rc = fill_u32(hist, 0, (size_t)b->ng * b->table->num_classes * 2, stream);
+        const uint32_t nc = b->table->num_classes;
+        rc = b->copies > 1 ? fill_u32(b->d_hist_copies, 0, 2 * b->copies * hist_copy_stride(b->ng, nc),
+                                      stream)
+                           : fill_u32(hist, 0, (size_t)b->ng * nc * 2, stream);
         if (rc) return rc;
     }
     rc = batch_enqueue_typed(b, stream);
@@ -235,6 +243,7 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
 static int batch_launch_count(mk_batch *b, unsigned long long *hist, uint32_t unit_end, int grid,
                               hipStream_t stream)
 {
+    if (b->copies > 1) hist = b->d_hist_copies;
     if (b->method == MK_METHOD_CORES)
         return launch_core(b->k, b->d_graphs, b->d_units, b->unit_cap, unit_end, b->d_counters,
                            b->table->d_table, b->table->num_classes, hist, enum_config(b), grid,
@@ -244,12 +253,20 @@ static int batch_launch_count(mk_batch *b, unsigned long long *hist, uint32_t un
                        b->lds_bytes, stream);
 }
 
-// after the last unit: the cores method divides its raw sums
-static int batch_launch_finish(mk_batch *b, unsigned long long *hist, hipStream_t stream)
+// after the last unit of graphs first..first+rows-1 (hist: their rows): the
+// copies of the histograms are summed, and the cores method divides its raw
+// sums
+static int batch_launch_finish(mk_batch *b, unsigned long long *hist, int first, int rows,
+                               hipStream_t stream)
 {
-    if (b->method != MK_METHOD_CORES) return MK_OK;
-    return launch_core_divide(hist, b->ng, b->table->num_classes, b->table->d_core_mult,
-                              b->d_counters, stream);
+    const uint32_t nc = b->table->num_classes;
+    const uint8_t *mult = b->method == MK_METHOD_CORES ? b->table->d_core_mult : nullptr;
+    if (b->copies > 1)
+        return launch_hist_finish(b->d_hist_copies + (size_t)first * nc, b->copies,
+                                  hist_copy_stride(b->ng, nc), hist, rows, nc, mult, b->d_counters,
+                                  stream);
+    if (!mult) return MK_OK;
+    return launch_core_divide(hist, rows, nc, mult, b->d_counters, stream);
 }
 
 // the counting kernel and the finish, no events (a whole-pass graph)
@@ -257,7 +274,7 @@ static int batch_enqueue_count_finish(mk_batch *b, unsigned long long *hist, hip
 {
     int rc = batch_launch_count(b, hist, kAllUnits, b->grid, stream);
     if (rc) return rc;
-    return batch_launch_finish(b, hist, stream);
+    return batch_launch_finish(b, hist, 0, b->ng, stream);
 }
 
 // the counting kernel between two timing events, then the finish
@@ -267,7 +284,7 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
     int rc = batch_launch_count(b, hist, kAllUnits, b->grid, stream);
     if (rc) return rc;
     MK_HIP(hipEventRecord(b->ev[2], stream));
-    rc = batch_launch_finish(b, hist, stream);
+    rc = batch_launch_finish(b, hist, 0, b->ng, stream);
     if (rc) return rc;
     MK_HIP(hipEventRecord(b->ev[3], stream));
     return MK_OK;
@@ -474,9 +491,15 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     // the same graphs plan to the same threshold at every pass
     std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
     b->unit_cap = std::max<uint32_t>(cnt[kNumUnits], 1);
-    BAIL_HIP(hipMalloc(&b->d_units, sizeof(int4) * b->unit_cap));
-
     b->grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, std::max<uint64_t>(b->units, 1));
+    if (t) b->copies = hist_copies(ng, t->num_classes, b->grid);
+    const size_t unit_bytes = (sizeof(int4) * (size_t)b->unit_cap + 255) & ~(size_t)255;
+    const size_t copy_bytes = b->copies > 1 ? 8 * b->copies * hist_copy_stride(ng, t->num_classes) : 0;
+    BAIL_HIP(hipMalloc(&b->d_units, unit_bytes + copy_bytes));
+    if (b->copies > 1)
+        b->d_hist_copies = reinterpret_cast<unsigned long long *>(
+            reinterpret_cast<char *>(b->d_units) + unit_bytes);
+
     if (b->method == MK_METHOD_CORES)
         BAIL_HIP(hipMalloc(&b->d_wave_scratch, sizeof(uint32_t) * kParentArcCap * (size_t)b->grid));
     if (b->marks == MK_MARKS_GLOBAL) {
@@ -636,6 +659,7 @@ uint64_t batch_device_bytes(const mk_batch *b)
     for (const mk_graph *g : b->graphs) words += (uint64_t)g->n + 1 + (uint64_t)g->nnz_u;
     return 4 * words + 20ull * b->total_slots + 4 * scan_tmp_words(b->total_slots) +
            16ull * b->unit_cap + 8ull * b->ng * b->table->num_classes + 4ull * (b->ng + 1) +
+           (b->d_hist_copies ? 8ull * b->copies * hist_copy_stride(b->ng, b->table->num_classes) : 0) +
            sizeof(DevGraph) * b->graphs.size() + 4 * kNumCounters +
            (b->d_wave_scratch ? 4ull * kParentArcCap * (uint64_t)b->grid : 0) + b->mark_bytes;
 }
@@ -698,11 +722,8 @@ int batch_collect_graph(mk_batch *b, int gi, uint64_t *hist, hipStream_t copy_st
     if (gi < 0 || gi >= b->ng) return fail(MK_EINVAL, "batch_collect_graph: graph %d of %d", gi, b->ng);
     const size_t nc = b->table->num_classes;
     unsigned long long *row = b->d_hist_own + (size_t)gi * nc;
-    if (b->method == MK_METHOD_CORES) {
-        int rc = launch_core_divide(row, 1, (uint32_t)nc, b->table->d_core_mult, b->d_counters,
-                                    copy_stream);
-        if (rc) return rc;
-    }
+    int rc = batch_launch_finish(b, row, gi, 1, copy_stream);
+    if (rc) return rc;
     uint32_t cnt[kNumCounters];
     MK_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost, copy_stream));
     MK_HIP(hipMemcpyAsync(hist, row, sizeof(uint64_t) * nc, hipMemcpyDeviceToHost, copy_stream));
@@ -720,7 +741,7 @@ int batch_collect(mk_batch *b, uint64_t *hist, hipStream_t copy_stream)
 {
     MK_HIP(hipSetDevice(b->ctx->device));
     if (b->ng == 0) return MK_OK;
-    int rc = batch_launch_finish(b, b->d_hist_own, copy_stream);
+    int rc = batch_launch_finish(b, b->d_hist_own, 0, b->ng, copy_stream);
     if (rc) return rc;
     uint32_t cnt[kNumCounters];
     MK_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost, copy_stream));

@@ -556,11 +556,15 @@ __device__ __forceinline__ void for_each_unit(EnumState<K, V> &s, const DevGraph
                                               unsigned long long *hist_base, const EnumConfig &cfg,
                                               Run run)
 {
+    // this wave's copy of the histograms
+    unsigned long long *hist =
+        cfg.hist_copies > 1u ? hist_base + (blockIdx.x & (cfg.hist_copies - 1u)) * cfg.copy_stride
+                             : hist_base;
     unit_loop<HeavyFirst>(
         s, graphs, units, unit_cap, unit_end, counters, cfg, run,
         [&](int gi) {
             if (s.hused) flush_hash<K>(s);
-            s.hist = hist_base + (size_t)gi * s.num_classes;
+            s.hist = hist + (size_t)gi * s.num_classes;
         },
         [&] {
             if (s.hused > s.hunit) flush_hash<K>(s);

@@ -243,7 +243,15 @@ struct EnumConfig {
     int variant;             // kVar* bits of the enumeration kernel (esu.h)
     void *marks;             // kVarGlobal: grid x mark_stride marks, all zero
     size_t mark_stride;      //   marks per workgroup (>= max_n)
+    uint32_t hist_copies;    // copies of the histograms the waves add to (0 or 1: one)
+    size_t copy_stride;      //   u64 words from one copy to the next
 };
+
+// Copies of the histograms for a launch of `grid` waves over ng graphs of
+// num_classes bins (a power of two; 1: the waves add to the histogram
+// itself), and the words between two copies.  See launch_hist_finish.
+uint32_t hist_copies(int ng, uint32_t num_classes, int grid);
+size_t hist_copy_stride(int ng, uint32_t num_classes);
 int enum_hash_bits(int k);
 int core_hash_bits(int k);
 constexpr uint32_t kDebugNoHash = 1u;      // every code straight to the histogram
@@ -271,6 +279,11 @@ int launch_core(int k, const DevGraph *d_graphs, const int4 *units, uint32_t uni
                 unsigned long long *hist_base, const EnumConfig &cfg, int grid, int lds_bytes,
                 hipStream_t stream);
 int launch_core_divide(unsigned long long *hist, int ng, uint32_t num_classes,
+                       const uint8_t *mult, uint32_t *counters, hipStream_t stream);
+// The copies of `rows` histograms (copies of `stride` words) summed into
+// hist; with mult the sums are divided by the cores per class too.
+int launch_hist_finish(const unsigned long long *copies_base, uint32_t copies, size_t stride,
+                       unsigned long long *hist, int rows, uint32_t num_classes,
                        const uint8_t *mult, uint32_t *counters, hipStream_t stream);
 
 void free_table(Table *t);

@@ -91,14 +91,18 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     const int k = t->k;
     const uint32_t nc = t->num_classes;
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(d_hist);
-    int rc = fill_u32(hist, 0, (size_t)nc * 2, s);
-    if (rc) return rc;
-    if (g->n < k || g->nnz_u == 0) return hipStreamSynchronize(s) == hipSuccess
-                                              ? MK_OK
-                                              : fail(MK_EDEVICE, "mk_count_static: sync failed");
+    int rc = MK_OK;
+    if (g->n < k || g->nnz_u == 0) {
+        rc = fill_u32(hist, 0, (size_t)nc * 2, s);
+        if (rc) return rc;
+        return hipStreamSynchronize(s) == hipSuccess
+                   ? MK_OK
+                   : fail(MK_EDEVICE, "mk_count_static: sync failed");
+    }
 
     // layout of the scratch: counters | descriptor | bit matrices | urow |
-    // uadj | 5 planner slot arrays | scan workspace | work units
+    // uadj | 5 planner slot arrays | scan workspace | work units | copies of
+    // the histogram (when there is room)
     const uint64_t n = (uint64_t)g->n, w = (n + 31) / 32, nnz = (uint64_t)g->nnz_u;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -114,7 +118,7 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     const size_t o_slot = take(4ull * 5 * nnz);
     const size_t o_scan = take(4ull * scan_tmp_words(nnz));
     const size_t o_units = off;
-    const uint64_t unit_cap =
+    uint64_t unit_cap =
         o_units < kStaticScratchBytes ? (kStaticScratchBytes - o_units) / sizeof(int4) : 0;
     if (unit_cap < kMinStaticUnits)
         return fail(MK_ERANGE,
@@ -150,9 +154,28 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     if (rc) return rc;
     const int grid = std::max(per_cu, 1) * ctx->num_cus;
 
+    // The copies of the histogram go behind the most units this plan can
+    // make: consecutive ranges of a node exceed the split threshold together
+    // and the threshold is at least the estimated total over 32 units a
+    // wave, so there are at most two ranges per unit of that target and one
+    // more per node.
+    uint32_t copies = hist_copies(1, nc, grid);
+    const size_t copy_bytes = 8 * (size_t)copies * hist_copy_stride(1, nc);
+    const uint64_t most_units = 2 * (32ull * (uint64_t)grid + 1) + nnz + kMinStaticUnits;
+    const size_t o_copies = round_up(o_units + most_units * sizeof(int4), 256);
+    if (copies > 1 && o_copies + copy_bytes <= kStaticScratchBytes)
+        unit_cap = (o_copies - o_units) / sizeof(int4);
+    else
+        copies = 1;
+    unsigned long long *count_to =
+        copies > 1 ? reinterpret_cast<unsigned long long *>(base + o_copies) : hist;
+
     hipLaunchKernelGGL(put_devgraph, dim3(1), dim3(1), 0, s, dg, d);
     MK_HIP(hipGetLastError());
     rc = fill_u32(counters, 0, kNumCounters, s);
+    if (!rc)
+        rc = copies > 1 ? fill_u32(count_to, 0, copy_bytes / 4, s)
+                        : fill_u32(hist, 0, (size_t)nc * 2, s);
     if (!rc) rc = launch_typed_csr(dg, 1, g->n, g->m, 2 * n * w, d.bits_out, counters, s);
     if (!rc)
         rc = launch_plan(k, dg, 1, (int64_t)nnz, (uint32_t)nnz, slots, slots + nnz, slots + 2 * nnz,
@@ -163,9 +186,13 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     cfg.max_n = g->n;
     cfg.seg_cap = seg_cap;
     cfg.hash_bits = enum_hash_bits(k);
+    cfg.hist_copies = copies;
+    cfg.copy_stride = hist_copy_stride(1, nc);
     if (!rc)
         rc = launch_enum(k, dg, units, (uint32_t)std::min<uint64_t>(unit_cap, 0xFFFFFFFFull),
-                         kAllUnits, counters, t->d_table, nc, hist, cfg, grid, lds, s);
+                         kAllUnits, counters, t->d_table, nc, count_to, cfg, grid, lds, s);
+    if (!rc && copies > 1)
+        rc = launch_hist_finish(count_to, copies, cfg.copy_stride, hist, 1, nc, nullptr, counters, s);
     if (rc) return rc;
     uint32_t cnt[kNumCounters];
     MK_HIP(hipMemcpyAsync(cnt, counters, sizeof(cnt), hipMemcpyDeviceToHost, s));

@@ -1,0 +1,61 @@
+"""Histograms counted in copies and summed (few bins, one or a few graphs)
+and counted in place (many): every bin of the caller's buffer is written,
+and equals the oracle's, on both sides of the rule and through every call
+that finishes a histogram."""
+
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_hist_equals_oracle
+from paper_1804_09741_amd import inputs as I
+from paper_1804_09741_amd import motifs as M
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(i, n=60, m=150):
+    return I.chung_lu_digraph(n, m, 2.2, 25, 0.2, np.random.default_rng([77, i]))
+
+
+# (k, graphs): 2^18 words of copies hold 16 copies of one graph at k = 3..5,
+# two of 14 graphs and one of 15 at k = 5; 7 vertices make fewer than 16 waves
+@pytest.mark.parametrize("k,ng", [(3, 1), (4, 1), (5, 1), (5, 13), (5, 14), (5, 15), (4, 90)])
+@pytest.mark.parametrize("method", [M.METHOD_ESU, M.METHOD_CORES])
+def test_batch_bins_all_written(ctx, k, ng, method):
+    import torch
+    t = ctx.table(k)
+    cc = t.class_codes()
+    specs = [_graph(i) for i in range(ng - 1)] + [_graph(99, 7, 12)]
+    gs = [ctx.load_graph(*s) for s in specs]
+    b = ctx.batch(gs, t, method=method)
+    try:
+        for _ in range(2):
+            d = torch.full((ng, t.num_classes), 11, dtype=torch.int64, device="cuda:0")
+            b.run(d, torch.cuda.current_stream())
+            hist, totals = b.read()
+            assert np.array_equal(hist, d.cpu().numpy().astype(np.uint64))
+            assert np.array_equal(hist.sum(axis=1), totals)
+        for i in (0, ng // 2, ng - 1):
+            assert_hist_equals_oracle(hist[i], cc, *specs[i], k)
+    finally:
+        b.free()
+        for g in gs:
+            g.free()
+
+
+@pytest.mark.parametrize("k", [3, 4, 5])
+def test_served_rows(ctx, k):
+    """The server finishes one graph's row of a group at a time."""
+    t = ctx.table(k)
+    cc = t.class_codes()
+    specs = [_graph(200 + i, 40 + 9 * i, 90 + 20 * i) for i in range(6)]
+    gs = [ctx.load_graph(*s) for s in specs]
+    srv = ctx.server()
+    try:
+        tickets = [srv.submit(g, k) for g in gs]
+        for tk, s in zip(tickets, specs):
+            assert_hist_equals_oracle(srv.wait(tk, k)[0], cc, *s, k)
+    finally:
+        srv.stop()
+        for g in gs:
+            g.free()
