@@ -23,14 +23,14 @@
 //      first member it is adjacent to (no lower member bits in its mark), its
 //      cell counted in LDS, new cells appended to a list;
 //   2. arcs inside adj(X): the taken vertices' own lists are scanned flat
-//      (a lane-prefix sum of degrees); a neighbour v > u with a mark and not
-//      a member closes an arc pair.  With few cells the pair is counted in
+//      (a lane-prefix sum of degrees); a neighbour v > u with a mark (the
+//      members' read zero) closes an arc pair.  With few cells the pair is counted in
 //      an LDS table per (cell pair, arc type); otherwise it goes straight to
 //      the per-wave hash, +1 for the code with the arcs and -1 without;
 //   3. cell pairs: lanes take pairs (Y, Z) of the list, form the code of X
-//      + one vertex of each (marks expanded back from the cell index) and
-//      add the weight, less the table's arc pairs, to the hash; the table's
-//      entries go to the codes with their arcs.
+//      + one vertex of each (a cell is its vertices' mark) and add the weight,
+//      less the table's arc pairs, to the hash; the table's entries go to the
+//      codes with their arcs.
 // Hash counts are 32-bit two's complement (the -1s); a flush sign-extends
 // them into the 64-bit histogram, so partial sums may wrap and the totals
 // are exact modulo 2^64 -- which they are, being the final non-negative
@@ -41,98 +41,64 @@ namespace mk {
 
 template <int K>
 constexpr int kCoreR = K - 2;                     // members of a core
+// A vertex's byte mark is its relation vector, so it is also its cell.
+// While a core is processed (and while a parent's arc pairs are listed) the
+// marks of the members read zero, so that only adj(X) has marks.  A byte a
+// vertex, where 16-bit (k = 6: 32-bit) marks held the bits at the code's
+// stride, a member flag and the cell's list position, is what lets a CU hold
+// more waves: the kernel waits on dependent L2 and LDS reads, and its speed
+// follows the waves in flight.  101 graphs of n = 1000 at k = 5: 22 -> 26
+// waves a CU, 17.4 -> 16.0 ms; n = 5000, m = 30000: k = 5 10 -> 15 waves,
+// 41.7 -> 30.8 ms, k = 6 6 -> 14 waves, 192 -> 92 ms (95 with arc-pair tables
+// of 12 cells as before).
 template <int K>
-constexpr int kCells = 1 << (2 * (K - 2));        // 4^(k-2) relation vectors
-// The top four bits of a mark (above every relation bit) are all set on
-// the members of the core being processed (and of a parent while its arc
-// pairs are listed).  Otherwise, on the vertices of adj(X), they hold the
-// list position of the vertex's cell (0..14) from the core's cell phase on,
-// the arc-pair table's index; they are left as they are until the next
-// core overwrites them, or cleared with the vertex's last relation bit.
-template <int K>
-constexpr int kPosShift = 8 * (int)sizeof(MarkT<K>) - 4;
-template <int K>
-constexpr uint32_t kMemberFlag = 0xFu << kPosShift<K>;
-
-template <int K>
-__device__ __forceinline__ bool is_member(uint32_t m)
-{
-    return (m & kMemberFlag<K>) == kMemberFlag<K>;
-}
+constexpr int kCells = 1 << (2 * kSegments<K>);   // relation vectors
 
 // Cores with at most kAggCells cells count their arc pairs in a small LDS
 // table per (cell pair, arc type) first; the pair phase then takes them off
 // the pair weights and adds them to the true classes, one insert per
-// non-empty entry.  Cores with more cells insert +1/-1 per arc pair.
+// non-empty entry.  Cores with more cells insert +1/-1 per arc pair, two
+// class lookups and two inserts each.  The sizes balance those cores against
+// the waves that the table's LDS costs.  k = 5 (101 graphs of n = 1000) with
+// 13 / 15 / 18 cells: 16.8 / 16.0 / 16.6 ms; k = 6 with 8 / 12 / 16 / 20 / 24 /
+// 32 cells: n = 5000, m = 30000 121 / 95 / 92 / 92 / 96 / 110 ms, n = 1000,
+// m = 4000 13.3 / 12.3 / 11.2 / 11.0 / 11.1 / 11.1 ms.
+#ifndef MK_AGG_CELLS_K6
+#define MK_AGG_CELLS_K6 16
+#endif
+#ifndef MK_AGG_CELLS_K5
+#define MK_AGG_CELLS_K5 15
+#endif
+__host__ __device__ constexpr int agg_cells(int k) { return k == 6 ? MK_AGG_CELLS_K6 : MK_AGG_CELLS_K5; }
 template <int K>
-constexpr int kAggCells = K == 6 ? 12 : 15;
+constexpr int kAggCells = agg_cells(K);
 template <int K>
 constexpr int kAggWords = 3 * kAggCells<K> * (kAggCells<K> + 1) / 2;
 
-// Extension segments the core walk fills: those of members 0..k-4 (a
-// core's last member only marks).
-template <int K>
-constexpr int kCoreSegs = K - 3;
-// The arc scan keeps each of its 64 vertices' id beside its mark: in one
-// word while marks are 16-bit (k <= 5; LDS marks mean ids below 8,192, in
-// the high half), else in 64 words of their own.
-template <int K>
-constexpr bool kPackedUid = sizeof(MarkT<K>) == 2;
-
-// LDS of the core kernel beyond the enumeration layout: cell counts (u32),
-// the list of non-empty cells and each cell's list position (u8), the arc
-// scan's vertex ids (k = 6), and the arc-pair table.  A wave's LDS sets how
-// many waves a CU holds, and the kernel's speed follows that count.
+// LDS of the core kernel beyond the shared layout: cell counts (u32), the
+// list of non-empty cells and each cell's list position (u8), and the
+// arc-pair table.  A wave's LDS sets how many waves a CU holds, and the
+// kernel's speed follows that count.
 struct CoreLds {
     uint32_t *cnt;
     uint8_t *list;
     uint8_t *pos;
-    uint32_t *uid;  // null when packed with the marks
     uint32_t *agg;
     uint32_t *ap;  // global: this workgroup's arc list of the current parent
 };
 
 __host__ __device__ inline int core_extra_bytes(int k)
 {
-    const int cells = 1 << (2 * (k - 2));
-    const int agg_cells = k == 6 ? 12 : 15;
-    return 4 * cells + 2 * ((cells + 3) & ~3) + (k >= 6 ? 4 * kWave : 0) +
-           4 * 3 * agg_cells * (agg_cells + 1) / 2;
-}
-
-// relation vector of a mark: bits 0..R-1 = arcs u -> s_0..s_{R-1} (the
-// mark's out bits, already adjacent), bits R..2R-1 = arcs s_0..s_{R-1} -> u
-// (its in bits, at stride k-1)
-template <int K>
-__device__ __forceinline__ uint32_t cell_of(uint32_t m)
-{
-    constexpr int R = kCoreR<K>;
-    uint32_t c = (m >> EnumState<K>::OUTB) & ((1u << R) - 1u);
-#pragma unroll
-    for (int d = 0; d < R; ++d) c |= ((m >> (d * (K - 1))) & 1u) << (R + d);
-    return c;
-}
-
-// inverse of cell_of
-template <int K>
-__device__ __forceinline__ uint32_t mark_of_cell(uint32_t c)
-{
-    constexpr int R = kCoreR<K>;
-    uint32_t m = (c & ((1u << R) - 1u)) << EnumState<K>::OUTB;
-#pragma unroll
-    for (int d = 0; d < R; ++d) m |= ((c >> (R + d)) & 1u) << (d * (K - 1));
-    return m;
+    const int cells = 1 << (2 * (k == 3 ? 2 : k - 2));
+    return 4 * cells + 2 * cells + 4 * 3 * agg_cells(k) * (agg_cells(k) + 1) / 2;
 }
 
 // mark bits of member positions below d
 template <int K>
 __device__ __forceinline__ uint32_t lower_members(int d)
 {
-    uint32_t m = 0;
-#pragma unroll
-    for (int q = 0; q < kCoreR<K>; ++q)
-        if (q < d) m |= (1u << (q * (K - 1))) | (1u << (EnumState<K>::OUTB + q));
-    return m;
+    const uint32_t low = (1u << d) - 1u;
+    return low | (low << EnumState<K, kVarCore>::OUTB);
 }
 
 // s_D := x for the last member of a core: marks only (no extension segment)
@@ -147,7 +113,7 @@ __device__ __forceinline__ void push_marks(EnumState<K, V> &s, int x)
         if (e < r1) {
             const uint32_t ent = s.uadj[e];
             const int y = (int)(ent >> 2);
-            s.mark[y] = (MarkT<K>)(s.mark[y] | mark_bits<K>(D, ent & 3u));
+            s.mark[y] = (MarkT<K, V>)(s.mark[y] | mark_bits<K>(D, ent & 3u));
         }
     }
     __syncthreads();
@@ -172,36 +138,33 @@ __device__ __forceinline__ Held push_marks_held(EnumState<K, V> &s, int x)
         h.ent = s.uadj[r0 + lane];
         const int y = (int)(h.ent >> 2);
         h.m = s.mark[y];
-        s.mark[y] = (MarkT<K>)(h.m | mark_bits<K>(D, h.ent & 3u));
+        s.mark[y] = (MarkT<K, V>)(h.m | mark_bits<K>(D, h.ent & 3u));
     }
     __syncthreads();
     return h;
 }
 
-// pop_held<D>(x) for the core walk: a long list's pop also clears the
-// position bits of the vertices it leaves without any relation bit (a short
-// list's pop restores the marks from before the push, where a vertex
-// without relation bits had no position bits either)
-template <int K, int D, int V>
-__device__ __forceinline__ void core_pop(EnumState<K, V> &s, int x, const Held &h)
+// Zero the marks of the first NM members (lane d holds member d); returns
+// the lane's old mark for restore_members.
+template <int K, int NM, int V>
+__device__ __forceinline__ uint32_t hide_members(EnumState<K, V> &s, const int (&mem)[K], int *id)
 {
-    if (h.n <= kWave) {
-        pop_held<K, D>(s, x, h);
-        return;
+    int x = mem[0];
+#pragma unroll
+    for (int d = 1; d < NM; ++d) x = lane_id() == d ? mem[d] : x;
+    *id = x;
+    uint32_t old = 0;
+    if (lane_id() < NM) {
+        old = s.mark[x];
+        s.mark[x] = 0;
     }
-    const int lane = lane_id();
-    const int r0 = uniform(s.urow[x]);
-    const int r1 = uniform(s.urow[x + 1]);
-    const uint32_t keep = ~mark_bits<K>(D, 3u);
-    for (int base = r0; base < r1; base += kWave) {
-        const int e = base + lane;
-        if (e < r1) {
-            const int y = (int)(s.uadj[e] >> 2);
-            uint32_t m = s.mark[y] & keep;
-            if (!(m & ~kMemberFlag<K>)) m = 0u;
-            s.mark[y] = (MarkT<K, V>)m;
-        }
-    }
+    return old;
+}
+
+template <int K, int NM, int V>
+__device__ __forceinline__ void restore_members(EnumState<K, V> &s, int id, uint32_t old)
+{
+    if (lane_id() < NM) s.mark[id] = (MarkT<K, V>)old;
     __syncthreads();
 }
 
@@ -243,14 +206,14 @@ __device__ __forceinline__ int member_entry(const int (&pre)[R + 1], const int (
 // Flat scan over the vertices u taken from the lists of members
 // from..NM-1 (first-seen -- no mark bits of a lower member -- and not a
 // member): every entry of u's own list is handed to
-// arc(edge, u, v, mark u, mark v, arc type), edge = v has a mark, is not a
-// member, and keep(v, u, mark v).  Padding lanes get edge = false.
-template <int K, int NM, int V, typename Keep, typename Arc>
+// arc(edge, u, v, w, mark v, arc type) with w = mark u | pos << 8 (pos the
+// list position of u's cell, with Pos), edge = v has a mark and keep(v, u,
+// mark v).  Padding lanes get edge = false.
+template <int K, int NM, bool Pos, int V, typename Keep, typename Arc>
 __device__ __forceinline__ void scan_taken(EnumState<K, V> &s, const CoreLds &c,
                                            const int (&pre)[NM + 1], const int (&r0)[NM],
                                            int from, Keep keep, Arc arc)
 {
-    constexpr uint32_t FLAG = kMemberFlag<K>;
     const int lane = lane_id();
     uint32_t *srcb = s.scratch, *start = s.scratch + kWave, *cw = s.scratch + 2 * kWave;
     for (int base = pre[from]; base < pre[NM]; base += kWave) {
@@ -262,45 +225,36 @@ __device__ __forceinline__ void scan_taken(EnumState<K, V> &s, const CoreLds &c,
             const int e = member_entry<NM>(pre, r0, a, &d);
             u = (int)(s.uadj[e] >> 2);
             const uint32_t m = s.mark[u];
-            if (!is_member<K>(m) && !(m & lower_members<K>(d))) {
+            if (m != 0u && !(m & lower_members<K>(d))) {
                 row = s.urow[u];
                 deg = s.urow[u + 1] - row;
                 mu = m;
+                if constexpr (Pos) mu |= (uint32_t)c.pos[m] << 8;
             }
         }
         int incl = deg;
         incl = wave_incl_sum(incl);
         const int tot = __builtin_amdgcn_readlane(incl, kWave - 1);
         start[lane] = (uint32_t)(row - (incl - deg));  // flat entry f at start + f
-        if constexpr (kPackedUid<K>) {
-            cw[lane] = mu | ((uint32_t)u << 16);
-        } else {
-            cw[lane] = mu;
-            c.uid[lane] = (uint32_t)u;
-        }
+        cw[lane] = mu | ((uint32_t)u << 16);           // LDS marks mean ids below 8,192
         __syncthreads();
         for (int fb = 0; fb < tot; fb += kWave) {
             const int f = fb + lane;
             bool edge = false;
             int uu = 0, v = 0;
-            uint32_t m_u = 0, mv = 0, t = 0;
+            uint32_t w_u = 0, mv = 0, t = 0;
             const int lo = flat_source(srcb, incl, deg, fb);
             if (f < tot) {
                 const uint32_t ent = s.uadj[start[lo] + (uint32_t)f];
                 v = (int)(ent >> 2);
                 mv = s.mark[v];
                 const uint32_t w = cw[lo];
-                if constexpr (kPackedUid<K>) {
-                    uu = (int)(w >> 16);
-                    m_u = w & 0xFFFFu;
-                } else {
-                    uu = (int)c.uid[lo];
-                    m_u = w;
-                }
+                uu = (int)(w >> 16);
+                w_u = w & 0xFFFFu;
                 t = ent & 3u;
-                edge = mv != 0u && !is_member<K>(mv) && keep(v, uu, mv);
+                edge = mv != 0u && keep(v, uu, mv);
             }
-            arc(edge, uu, v, m_u, mv, t);
+            arc(edge, uu, v, w_u, mv, t);
         }
         __syncthreads();
     }
@@ -312,11 +266,8 @@ __device__ __forceinline__ void scan_taken(EnumState<K, V> &s, const CoreLds &c,
 template <int K, int NP, int V>
 __device__ int parent_arcs(EnumState<K, V> &s, const CoreLds &c, const int (&mem)[K])
 {
-    constexpr uint32_t FLAG = kMemberFlag<K>;
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 0; d < NP; ++d)
-        if (lane == d) s.mark[mem[d]] = (MarkT<K>)(s.mark[mem[d]] | FLAG);
+    int id;
+    const uint32_t old = hide_members<K, NP>(s, mem, &id);
     int r0[NP], pre[NP + 1];
     pre[0] = 0;
 #pragma unroll
@@ -326,7 +277,7 @@ __device__ int parent_arcs(EnumState<K, V> &s, const CoreLds &c, const int (&mem
     }
     __syncthreads();
     int nap = 0;
-    scan_taken<K, NP>(
+    scan_taken<K, NP, false>(
         s, c, pre, r0, 0, [](int v, int u, uint32_t) { return v > u; },
         [&](bool edge, int u, int v, uint32_t, uint32_t, uint32_t t) {
             const unsigned long long bal = __ballot(edge);
@@ -335,10 +286,7 @@ __device__ int parent_arcs(EnumState<K, V> &s, const CoreLds &c, const int (&mem
                 c.ap[at] = (uint32_t)u | ((uint32_t)v << 13) | (t << 26);
             nap += __popcll(bal);
         });
-#pragma unroll
-    for (int d = 0; d < NP; ++d)
-        if (lane == d) s.mark[mem[d]] = (MarkT<K>)(s.mark[mem[d]] & ~FLAG);
-    __syncthreads();
+    restore_members<K, NP>(s, id, old);
     return nap > (int)kParentArcCap ? -1 : nap;
 }
 
@@ -351,15 +299,13 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
                           int nap)
 {
     constexpr int R = kCoreR<K>;
-    constexpr uint32_t FLAG = kMemberFlag<K>;
     // arc bits between positions k-2 and k-1
     constexpr int B_YZ = (K - 2) * (K - 1) + (K - 1) - 1;
     constexpr int B_ZY = (K - 1) * (K - 1) + (K - 2);
     const int lane = lane_id();
 
-#pragma unroll
-    for (int d = 0; d < R; ++d)
-        if (lane == d) s.mark[mem[d]] = (MarkT<K>)(s.mark[mem[d]] | FLAG);
+    int id;
+    const uint32_t old = hide_members<K, R>(s, mem, &id);
     int r0[R], pre[R + 1];
     pre[0] = 0;
 #pragma unroll
@@ -375,14 +321,12 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
     for (int base = 0; base < total; base += kWave) {
         const int a = base + lane;
         bool mine = false;
-        uint32_t cell = 0, vid = 0, mk = 0;
+        uint32_t cell = 0;
         if (a < total) {
             int d;
             const int e = member_entry<R>(pre, r0, a, &d);
-            vid = s.uadj[e] >> 2;
-            mk = s.mark[vid];
-            mine = !is_member<K>(mk) && !(mk & lower_members<K>(d));
-            cell = cell_of<K>(mk);
+            cell = s.mark[s.uadj[e] >> 2];
+            mine = cell != 0u && !(cell & lower_members<K>(d));
         }
         bool fresh = false;
         if (mine) fresh = atomicAdd(&c.cnt[cell], 1u) == 0u;
@@ -391,11 +335,6 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
             const int at = ncell + (int)lanes_below(bal);
             c.list[at] = (uint8_t)cell;
             c.pos[cell] = (uint8_t)at;
-        }
-        if (mine) {
-            // the cell's position into the mark's top bits (15 and up: none)
-            const uint32_t p = c.pos[cell];
-            s.mark[vid] = (MarkT<K>)((mk & ~kMemberFlag<K>) | ((p < 15u ? p : 0u) << kPosShift<K>));
         }
         ncell += __popcll(bal);
         nadj += __popcll(__ballot(mine));
@@ -408,10 +347,10 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
 
     // 2. arc pairs inside adj(X): into the table, or +1 with the arcs and -1
     // without straight into the hash
-    auto arc = [&](bool edge, int, int, uint32_t mu, uint32_t mv, uint32_t t) {
+    auto arc = [&](bool edge, int, int, uint32_t wu, uint32_t mv, uint32_t t) {
         if (agg) {
             if (edge) {
-                uint32_t ia = (mu >> kPosShift<K>) & 15u, ib = (mv >> kPosShift<K>) & 15u;
+                uint32_t ia = wu >> 8, ib = c.pos[mv];
                 if (ia > ib) {
                     const uint32_t x = ia;
                     ia = ib;
@@ -421,8 +360,7 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
                 atomicAdd(&c.agg[3u * (ib * (ib + 1u) / 2u + ia) + t - 1u], 1u);
             }
         } else {
-            const uint32_t cm = cx | code_bits<K>(mu & ~kMemberFlag<K>, K - 2) |
-                                code_bits<K>(mv & ~kMemberFlag<K>, K - 1);
+            const uint32_t cm = cx | code_bits<K>(wu & 0xFFu, K - 2) | code_bits<K>(mv, K - 1);
             const uint32_t ct = cm | ((t & 1u) << B_YZ) | ((t >> 1) << B_ZY);
             bool et = edge, em = edge;
             const uint32_t it = class_of<K>(s, et, ct), im = class_of<K>(s, em, cm);
@@ -432,30 +370,30 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
         }
     };
     if (nap >= 0) {
-        // the parent's arc pairs, less those at z
-        const int z = mem[R - 1];
+        // the parent's arc pairs, less those at X's last member (whose mark
+        // reads zero)
         for (int ib = 0; ib < nap; ib += kWave) {
             const int i = ib + lane;
             bool edge = false;
             uint32_t mu = 0, mv = 0, t = 0;
             if (i < nap) {
                 const uint32_t ent = c.ap[i];
-                const int u = (int)(ent & 0x1FFFu), v = (int)((ent >> 13) & 0x1FFFu);
                 t = ent >> 26;
-                edge = u != z && v != z;
-                mu = s.mark[u];
-                mv = s.mark[v];
+                mu = s.mark[ent & 0x1FFFu];
+                mv = s.mark[(ent >> 13) & 0x1FFFu];
+                edge = mu != 0u && mv != 0u;
+                mu |= (uint32_t)c.pos[mu] << 8;
             }
             arc(edge, 0, 0, mu, mv, t);
         }
         // arcs at the vertices z brings (no mark bits of P): to any vertex
         // of adj(P), or to another new one above them
         const uint32_t of_p = lower_members<K>(R - 1);
-        scan_taken<K, R>(
+        scan_taken<K, R, true>(
             s, c, pre, r0, R - 1,
             [of_p](int v, int u, uint32_t mv) { return (mv & of_p) != 0u || v > u; }, arc);
     } else {
-        scan_taken<K, R>(s, c, pre, r0, 0, [](int v, int u, uint32_t) { return v > u; }, arc);
+        scan_taken<K, R, true>(s, c, pre, r0, 0, [](int v, int u, uint32_t) { return v > u; }, arc);
     }
 
     // 3. pairs of cells (Y <= Z): C(|Y|,2) or |Y||Z| k-sets of motif(X, Y, Z),
@@ -467,7 +405,7 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
         uint32_t code = 0, w = 0, e1 = 0, e2 = 0, e3 = 0;
         if (p < npairs) {
             // p = z(z+1)/2 + y with y <= z
-            int z = (int)((__builtin_sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
+            int z = (int)((__builtin_amdgcn_sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
             if ((z + 1) * (z + 2) / 2 <= p) ++z;
             if (z * (z + 1) / 2 > p) --z;
             const int y = p - z * (z + 1) / 2;
@@ -482,8 +420,7 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
                 row[0] = row[1] = row[2] = 0u;
                 w -= e1 + e2 + e3;
             }
-            code = cx | code_bits<K>(mark_of_cell<K>(cy), K - 2) |
-                   code_bits<K>(mark_of_cell<K>(cz), K - 1);
+            code = cx | code_bits<K>(cy, K - 2) | code_bits<K>(cz, K - 1);
             valid = w > 0;
         }
         if (!(agg && __ballot(e1 | e2 | e3))) {
@@ -533,12 +470,9 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
         }
     }
 
-    // reset the cell counts and the member flags
+    // reset the cell counts and the members' marks
     for (int i = lane; i < ncell; i += kWave) c.cnt[c.list[i]] = 0u;
-#pragma unroll
-    for (int d = 0; d < R; ++d)
-        if (lane == d) s.mark[mem[d]] = (MarkT<K>)(s.mark[mem[d]] & ~FLAG);
-    __syncthreads();
+    restore_members<K, R>(s, id, old);
 }
 
 // node with members s_0..s_D (D < k-3): its children jlo..jhi-1 become
@@ -577,12 +511,12 @@ __device__ void visit_core(EnumState<K, V> &s, const CoreLds &c, const int (&st)
         }
         const int x = uniform((int)s.seg[L * s.seg_cap + o]);
         const uint32_t ccode =
-            code | code_bits<K>((uint32_t)uniform((int)s.mark[x]) & ~kMemberFlag<K>, D + 1);
+            code | code_bits<K>((uint32_t)uniform((int)s.mark[x]), D + 1);
         mem[D + 1] = x;
         if constexpr (D + 1 == K - 3) {
             const Held held = push_marks_held<K, D + 1>(s, x);
             core_node<K>(s, c, mem, ccode, nap);
-            core_pop<K, D + 1>(s, x, held);
+            pop_held<K, D + 1>(s, x, held);
         } else {
             const Held held = push_held<K, D + 1>(s, x);
             int cst[K - 1];
@@ -590,7 +524,7 @@ __device__ void visit_core(EnumState<K, V> &s, const CoreLds &c, const int (&st)
             for (int q = 0; q < K - 1; ++q)
                 cst[q] = q < L ? s.len[q] : (q == L ? o + 1 : (q <= D ? st[q] : 0));
             visit_core<K, D + 1>(s, c, cst, ccode, 0, INT_MAX, mem);
-            core_pop<K, D + 1>(s, x, held);
+            pop_held<K, D + 1>(s, x, held);
         }
     }
 }
@@ -608,17 +542,17 @@ __device__ void run_core_unit(EnumState<K, V> &s, const CoreLds &c, int v, int i
     if constexpr (K == 3) {
         const Held held0 = push_marks_held<K, 0>(s, v);
         core_node<K>(s, c, mem, 0u, -1);
-        core_pop<K, 0>(s, v, held0);
+        pop_held<K, 0>(s, v, held0);
     } else {
         const Held held0 = push_held<K, 0>(s, v);
         if (i < s.len[0]) {
             const int x = uniform((int)s.seg[i]);
-            const uint32_t code = code_bits<K>((uint32_t)uniform((int)s.mark[x]) & ~kMemberFlag<K>, 1);
+            const uint32_t code = code_bits<K>((uint32_t)uniform((int)s.mark[x]), 1);
             mem[1] = x;
             if constexpr (K == 4) {
                 const Held held1 = push_marks_held<K, 1>(s, x);
                 core_node<K>(s, c, mem, code, -1);
-                core_pop<K, 1>(s, x, held1);
+                pop_held<K, 1>(s, x, held1);
             } else {
                 const Held held1 = push_held<K, 1>(s, x);
                 int st[K - 1];
@@ -628,12 +562,12 @@ __device__ void run_core_unit(EnumState<K, V> &s, const CoreLds &c, int v, int i
                 const bool full = range == kFullChild;
                 visit_core<K, 1>(s, c, st, code, full ? 0 : (int)(range & 0xFFFFu),
                                  full ? INT_MAX : (int)(range >> 16), mem);
-                core_pop<K, 1>(s, x, held1);
+                pop_held<K, 1>(s, x, held1);
             }
         } else if (lane_id() == 0) {
             atomicAdd(s.errors, 1u);
         }
-        core_pop<K, 0>(s, v, held0);
+        pop_held<K, 0>(s, v, held0);
     }
 }
 
@@ -645,15 +579,13 @@ __device__ __forceinline__ void core_body(const DevGraph *graphs, const int4 *un
 {
     extern __shared__ uint32_t lds[];
     EnumState<K, V> s;
-    const LdsLayout lay = lds_layout(K, cfg.max_n, cfg.seg_cap, cfg.hash_bits, false, kCoreSegs<K>);
+    const LdsLayout lay = lds_layout(K, cfg.max_n, cfg.seg_cap, cfg.hash_bits, V);
     char *base = reinterpret_cast<char *>(lds);
     CoreLds c;
     c.cnt = reinterpret_cast<uint32_t *>(base + lay.total);
     c.list = reinterpret_cast<uint8_t *>(c.cnt + kCells<K>);
-    c.pos = c.list + ((kCells<K> + 3) & ~3);
-    uint32_t *after_pos = reinterpret_cast<uint32_t *>(c.pos + ((kCells<K> + 3) & ~3));
-    c.uid = kPackedUid<K> ? nullptr : after_pos;
-    c.agg = kPackedUid<K> ? after_pos : after_pos + kWave;
+    c.pos = c.list + kCells<K>;
+    c.agg = reinterpret_cast<uint32_t *>(c.pos + kCells<K>);
     c.ap = cfg.wave_scratch ? cfg.wave_scratch + (size_t)blockIdx.x * kParentArcCap : nullptr;
     for (int i = lane_id(); i < kCells<K>; i += kWave) c.cnt[i] = 0u;
     for (int i = lane_id(); i < kAggWords<K>; i += kWave) c.agg[i] = 0u;
@@ -678,7 +610,7 @@ __global__ __launch_bounds__(kWave) void core_kernel(const DevGraph *graphs, con
                                                      unsigned long long *hist_base,
                                                      EnumConfig cfg)
 {
-    core_body<K, 0>(graphs, units, unit_cap, unit_end, counters, table, num_classes, hist_base, cfg);
+    core_body<K, kVarCore>(graphs, units, unit_cap, unit_end, counters, table, num_classes, hist_base, cfg);
 }
 
 // the build that honours the test hooks of the hash
@@ -690,8 +622,8 @@ __global__ __launch_bounds__(kWave) void core_debug_kernel(const DevGraph *graph
                                                            unsigned long long *hist_base,
                                                            EnumConfig cfg)
 {
-    core_body<K, kVarDebug>(graphs, units, unit_cap, unit_end, counters, table, num_classes,
-                            hist_base, cfg);
+    core_body<K, kVarCore | kVarDebug>(graphs, units, unit_cap, unit_end, counters, table,
+                                       num_classes, hist_base, cfg);
 }
 
 // hist[g][c] := raw / core_mult[c]; a raw count that is not a multiple (or
@@ -748,9 +680,8 @@ __global__ void hist_finish_kernel(const unsigned long long *src, uint32_t copie
 // Per-wave hash slots of the core kernel (keys are class ids).  Its LDS
 // sets how many waves a CU holds, and the kernel's speed follows that
 // count, so the hash trades capacity for waves: on the k = 5 batch 256
-// slots flushed at three quarters (7.5 KB of LDS a wave) take 21.2 ms, 512
-// slots 23.9 ms and 128 slots 28.2 ms at three quarters; flushed at half,
-// 256 slots took 27.5 ms.
+// slots flushed at three quarters (6.3 KB of LDS a wave) take 16.0 ms, 512
+// slots 17.6 ms.
 #ifndef MK_CORE_HASH_BITS_K5
 #define MK_CORE_HASH_BITS_K5 8
 #endif
@@ -758,7 +689,7 @@ int core_hash_bits(int k) { return k == 5 ? MK_CORE_HASH_BITS_K5 : kHashBits; }
 
 int core_lds_bytes(int k, int max_n, int seg_cap)
 {
-    return lds_layout(k, max_n, seg_cap, core_hash_bits(k), false, k - 3).total + core_extra_bytes(k);
+    return lds_layout(k, max_n, seg_cap, core_hash_bits(k), kVarCore).total + core_extra_bytes(k);
 }
 
 template <int K>

@@ -13,10 +13,10 @@
 //
 // Per wave, LDS holds
 //   mark[n]        for every vertex x, its relation to the current members
-//                  s_0..s_d of the growing subgraph: "in" bit d(k-1) set iff
-//                  arc s_d -> x, "out" bit OUTB+d set iff arc x -> s_d.  The
-//                  in bits are already spread at stride k-1, so the code
-//                  bits that a vertex adds when it joins at position p are
+//                  s_0..s_d of the growing subgraph: "in" bit d set iff arc
+//                  s_d -> x, "out" bit OUTB+d set iff arc x -> s_d.  With the
+//                  in bits spread at stride k-1, the code bits that a vertex
+//                  adds when it joins at position p are
 //                      (out << p(k-1)) | (in << (p-1))
 //                  -- exactly bits b(i,p) = i(k-1)+p-1 and b(p,i) = p(k-1)+i
 //                  of the adjacency code.  mark[x] == 0 also says "x is
@@ -646,7 +646,7 @@ __device__ __forceinline__ void enum_body(const DevGraph *graphs, const int4 *un
 {
     extern __shared__ uint32_t lds[];
     EnumState<K, V> s;
-    const LdsLayout lay = lds_layout(K, cfg.max_n, cfg.seg_cap, cfg.hash_bits, (V & kVarGlobal) != 0);
+    const LdsLayout lay = lds_layout(K, cfg.max_n, cfg.seg_cap, cfg.hash_bits, V);
     init_state(s, reinterpret_cast<char *>(lds), lay, cfg, counters, table, num_classes);
     for_each_unit<false, K>(s, graphs, units, unit_cap, unit_end, counters, hist_base, cfg,
                      [&](int v, int i, uint32_t range) { run_unit<K>(s, v, i, range); });
@@ -692,7 +692,7 @@ int enum_hash_bits(int) { return kHashBits; }
 
 int enum_lds_bytes(int k, int max_n, int seg_cap, int variant)
 {
-    return lds_layout(k, max_n, seg_cap, enum_hash_bits(k), (variant & kVarGlobal) != 0).total;
+    return lds_layout(k, max_n, seg_cap, enum_hash_bits(k), variant).total;
 }
 
 // the instantiated variants: bit matrices, list search, list search with

@@ -17,10 +17,11 @@
 //
 // Per wave, LDS holds
 //   mark[n]        for every vertex x, its relation to the current members
-//                  s_0..s_d of the growing subgraph: "in" bit d(k-1) set iff
-//                  arc s_d -> x, "out" bit OUTB+d set iff arc x -> s_d.  The
-//                  in bits are already spread at stride k-1, so the code
-//                  bits that a vertex adds when it joins at position p are
+//                  s_0..s_d of the growing subgraph: "in" bit d set iff arc
+//                  s_d -> x, "out" bit OUTB+d set iff arc x -> s_d.  With the
+//                  in bits spread at stride k-1 (spread_in: one multiply and
+//                  a mask), the code bits that a vertex adds when it joins
+//                  at position p are
 //                      (out << p(k-1)) | (in << (p-1))
 //                  -- exactly bits b(i,p) = i(k-1)+p-1 and b(p,i) = p(k-1)+i
 //                  of the adjacency code.  mark[x] == 0 also says "x is
@@ -87,18 +88,26 @@ constexpr int kRowMin = MK_ROW_MIN;
 template <int V>
 using SegT = typename std::conditional<(V & kVarGlobal) != 0, uint32_t, uint16_t>::type;
 
-// Byte offsets of one wave's LDS: marks (n x 2 or 4 bytes; none when they
+// Bytes of one vertex's mark (the size of MarkT<K, V> below).
+__host__ __device__ inline int mark_size(int k, int variant)
+{
+    return (variant & kVarCore) != 0 ? 1 : (k <= 5 && (variant & kVarGlobal) == 0 ? 2 : 4);
+}
+
+// Byte offsets of one wave's LDS: marks (n x mark_size; none when they
 // are in global memory), extension segments (u16, or u32 with global
-// marks), scratch, hash keys and counts; each part 4-byte aligned.
+// marks), scratch, hash keys and counts; each part 4-byte aligned.  The core
+// walk fills one segment less (a core's last member only marks).
 struct LdsLayout {
     int seg, scratch, total;
 };
 
 __host__ __device__ inline LdsLayout lds_layout(int k, int max_n, int seg_cap, int hash_bits,
-                                                bool global_marks = false, int segs = -1)
+                                                int variant)
 {
-    if (segs < 0) segs = k == 3 ? 2 : k - 2;
-    const int mark_bytes = global_marks ? 0 : (((k <= 5 ? 2 : 4) * max_n + 3) & ~3);
+    const bool global_marks = (variant & kVarGlobal) != 0;
+    const int segs = (variant & kVarCore) != 0 ? k - 3 : (k == 3 ? 2 : k - 2);
+    const int mark_bytes = global_marks ? 0 : ((mark_size(k, variant) * max_n + 3) & ~3);
     const int seg_bytes = ((global_marks ? 4 : 2) * segs * seg_cap + 3) & ~3;
     LdsLayout l;
     l.seg = mark_bytes;
@@ -107,19 +116,21 @@ __host__ __device__ inline LdsLayout lds_layout(int k, int max_n, int seg_cap, i
     return l;
 }
 
-// Marks hold, for members at positions 0..kSegments-1, the "in" bits spread
-// at stride k-1 (highest at (kSegments-1)(k-1)) and then one "out" bit per
-// position: 5 / 6 / 12 / 20 bits for k = 3 / 4 / 5 / 6, so 16-bit marks do
-// for k <= 5 in LDS.  Marks in device memory are 32-bit for every k (room
-// for the extension-list tags of last_two_cells).
+// Marks hold, for members at positions 0..S-1 (S = kSegments), S "in" bits
+// and then S "out" bits: 4 / 4 / 6 / 8 / 10 bits for k = 3..7.  The core
+// walk needs nothing else of a vertex, so its marks are bytes; the
+// enumeration's are 16-bit for k <= 5 in LDS and 32-bit otherwise (room for
+// the extension-list tags of last_two_cells).
 template <int K, int V = 0>
-using MarkT = typename std::conditional<K <= 5 && (V & kVarGlobal) == 0, uint16_t, uint32_t>::type;
+using MarkT = typename std::conditional<
+    (V & kVarCore) != 0, uint8_t,
+    typename std::conditional<K <= 5 && (V & kVarGlobal) == 0, uint16_t, uint32_t>::type>::type;
 
 template <int K, int V = 0>
 struct EnumState {
-    static constexpr int OUTB = (kSegments<K> - 1) * (K - 1) + 1;
+    static constexpr int OUTB = kSegments<K>;
     static constexpr uint32_t INMASK = (1u << OUTB) - 1u;
-    static_assert(OUTB + kSegments<K> <= 8 * (int)sizeof(MarkT<K, V>), "mark bits do not fit");
+    static_assert(2 * OUTB <= 8 * (int)sizeof(MarkT<K, V>), "mark bits do not fit");
     MarkT<K, V> *mark;          // LDS, or this wave's global array (kVarGlobal)
     SegT<V> *seg;               // vertex ids
     int seg_cap;
@@ -207,14 +218,37 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask)
 template <int K>
 __device__ __forceinline__ uint32_t mark_bits(int d, uint32_t t)
 {
-    return ((t & 1u) << (d * (K - 1))) | (((t >> 1) & 1u) << (EnumState<K>::OUTB + d));
+    return ((t & 1u) << d) | (((t >> 1) & 1u) << (EnumState<K>::OUTB + d));
+}
+
+// A mark's in bits moved from stride 1 to stride k-1: with S = k-2 in bits,
+// copies of them at shifts 0, S, 2S.. do not overlap, and bit d of copy d
+// sits at d + dS = d(k-1).
+template <int K>
+__device__ __forceinline__ uint32_t spread_in(uint32_t m)
+{
+    constexpr int S = kSegments<K>;
+    const uint32_t in = m & EnumState<K>::INMASK;
+    if constexpr (K == 3) {
+        return (in & 1u) | ((in & 2u) << 1);
+    } else {
+        uint32_t copies = 0, keep = 0;
+#pragma unroll
+        for (int d = 0; d < S; ++d) {
+            copies |= 1u << (d * S);
+            keep |= 1u << (d * (K - 1));
+        }
+        return (uint32_t)__umul24(in, copies) & keep;
+    }
 }
 
 // code bits contributed by a vertex with mark m joining at position p >= 1
+// (bits of m above the relation bits are ignored)
 template <int K>
 __device__ __forceinline__ uint32_t code_bits(uint32_t m, int p)
 {
-    return ((m >> EnumState<K>::OUTB) << (p * (K - 1))) | ((m & EnumState<K>::INMASK) << (p - 1));
+    return (((m >> EnumState<K>::OUTB) & EnumState<K>::INMASK) << (p * (K - 1))) |
+           (spread_in<K>(m) << (p - 1));
 }
 
 // s_D := x.  Builds seg[D] (new exclusive extension vertices, ascending) and
@@ -458,8 +492,10 @@ __device__ __forceinline__ void init_state(EnumState<K, V> &s, char *base, const
     s.uadj = nullptr;
     s.hist = nullptr;
     // global marks are zeroed when allocated and every pop restores them
-    if constexpr ((V & kVarGlobal) == 0)
-        for (int i = lane_id(); i < cfg.max_n; i += kWave) s.mark[i] = 0;
+    if constexpr ((V & kVarGlobal) == 0) {
+        uint32_t *w = reinterpret_cast<uint32_t *>(base);
+        for (int i = lane_id(); i < lay.seg / 4; i += kWave) w[i] = 0u;
+    }
     __syncthreads();
 }
 

@@ -229,9 +229,12 @@ constexpr uint32_t kAllUnits = 0xFFFFFFFFu;
 //   kVarDebug   the kernel honours the kDebug* test hooks of EnumConfig
 //               (the production kernels leave their checks out: about 2%
 //               of the k = 6 kernel's time per hash insert).
+//   kVarCore    the core kernel's walk (core.hip): byte marks, no extension
+//               segment for a core's last member.
 constexpr int kVarSearch = 1;
 constexpr int kVarGlobal = 2;
 constexpr int kVarDebug = 4;
+constexpr int kVarCore = 8;
 
 struct EnumConfig {
     int max_n;       // largest n of the batch (LDS marks)

@@ -78,8 +78,8 @@ __host__ __device__ constexpr int bit7(int i, int j) { return i * 6 + j - (j > i
 // code bits of a vertex with mark m joining at position p (1..6)
 __device__ __forceinline__ Code7 code_bits7(uint32_t m, int p)
 {
-    return ((Code7)(m >> EnumState<7>::OUTB) << (p * 6)) |
-           ((Code7)(m & EnumState<7>::INMASK) << (p - 1));
+    return ((Code7)((m >> EnumState<7>::OUTB) & EnumState<7>::INMASK) << (p * 6)) |
+           ((Code7)spread_in<7>(m) << (p - 1));
 }
 
 // i-th set bit (0-based) of a 7-bit mask
@@ -723,7 +723,7 @@ __device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const 
 // extension tags (a byte per vertex)
 static __host__ __device__ int k7_hash_offset(int max_n, int seg_cap, bool global)
 {
-    return (lds_layout(7, max_n, seg_cap, 0, global).total + 7) & ~7;
+    return (lds_layout(7, max_n, seg_cap, 0, global ? kVarGlobal : 0).total + 7) & ~7;
 }
 
 static __host__ __device__ int k7_cells_offset(int max_n, int seg_cap, bool global)
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(kWave) void k7_kernel(const DevGraph *graphs, const
     extern __shared__ uint32_t lds[];
     char *base = reinterpret_cast<char *>(lds);
     EnumState<7, V> s;
-    const LdsLayout lay = lds_layout(7, cfg.max_n, cfg.seg_cap, 0, kGlobal);
+    const LdsLayout lay = lds_layout(7, cfg.max_n, cfg.seg_cap, 0, V);
     init_state(s, base, lay, cfg, counters, nullptr, 0u);
     K7Wave w7;
     w7.hkey = reinterpret_cast<Code7 *>(base + k7_hash_offset(cfg.max_n, cfg.seg_cap, kGlobal));
