@@ -546,18 +546,37 @@ __device__ __forceinline__ void unit_loop(EnumState<K, V> &s, const DevGraph *gr
         run(uniform(u.y), uniform(u.z), (uint32_t)uniform(u.w));
         after_unit();
     };
+    // Range x: the units [lo_x, lo_{x+1}) of the launch, or (mix) every eighth
+    // grab of all units.  A grab: its first unit and one past its last.
     const int home = (int)(blockIdx.x % kQueues);
+    const bool mix = cfg.mix != 0;
+    // Ranges a wave looks into after its own.  A visit is an atomic on a head
+    // that all eight XCDs share, about 10 ns one after another, and most
+    // visits find the range empty.  So launches with many units a wave visit
+    // every range (the walk's time hides it, and ranges of unlike graphs
+    // need it); in the others a wave tries one, in turn.  8,327 units on 6,144
+    // waves (k = 4, n = 2000, m = 10000): 7 visits 0.181 ms of kernel, 2
+    // 0.109, 1 0.096, none 0.090; k = 5 by enumeration, n = 1000, m = 3000,
+    // 26,895 units on 7,168 waves: 0.62 ms with 1 or 2, 0.64 with none.
+    // (Launches of 8 waves and more have a home wave on every range, which
+    // empties it whoever else comes.)
+    const int tries =
+        span / gridDim.x >= 16u || gridDim.x < 8u * kQueues ? kQueues - 1 : 1;
+    const uint32_t turn = tries < kQueues - 1 ? blockIdx.x / kQueues : 0u;
     for (int sweep = two ? 0 : 1; sweep < 2; ++sweep) {
         const uint32_t ch = sweep == 0 ? chunk0 : chunk;
-        for (int q = 0; q < kQueues; ++q) {
-            const int x = (home + q) % kQueues;
-            const uint32_t lo = begin + (uint32_t)((uint64_t)span * x / kQueues);
-            const uint32_t hi = begin + (uint32_t)((uint64_t)span * (x + 1) / kQueues);
+        for (int t = 0; t <= tries; ++t) {
+            const int x = t == 0 ? home
+                                 : (int)((home + 1 + (turn + (uint32_t)t - 1u) % (kQueues - 1)) % kQueues);
             uint32_t *head = &counters[(sweep == 0 ? kHeavyHeads : kQueueHeads) + x * kHeadStride];
+            const uint32_t lo = mix ? begin + (uint32_t)x * ch : begin + (uint32_t)((uint64_t)span * x / kQueues);
+            const uint32_t hi = mix ? end : begin + (uint32_t)((uint64_t)span * (x + 1) / kQueues);
             for (;;) {
                 uint32_t idx = 0;
                 if (lane_id() == 0) idx = atomicAdd(head, ch);
-                idx = lo + (uint32_t)uniform((int)idx);
+                idx = (uint32_t)uniform((int)idx) * (mix ? (uint32_t)kQueues : 1u);
+                if (idx >= span) break;  // also keeps lo + idx in 32 bits
+                idx += lo;
                 if (idx >= hi) break;
                 const uint32_t stop = idx + ch < hi ? idx + ch : hi;
                 if (sweep == 0) {

@@ -246,6 +246,7 @@ struct EnumConfig {
     int variant;             // kVar* bits of the enumeration kernel (esu.h)
     void *marks;             // kVarGlobal: grid x mark_stride marks, all zero
     size_t mark_stride;      //   marks per workgroup (>= max_n)
+    uint32_t mix;            // 1: the queues deal the units out in turn, 0: a range each
     uint32_t hist_copies;    // copies of the histograms the waves add to (0 or 1: one)
     size_t copy_stride;      //   u64 words from one copy to the next
 };

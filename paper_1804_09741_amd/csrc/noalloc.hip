@@ -186,6 +186,7 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     cfg.max_n = g->n;
     cfg.seg_cap = seg_cap;
     cfg.hash_bits = enum_hash_bits(k);
+    cfg.mix = 1;  // one graph: see enum_config of the prepared batches
     cfg.hist_copies = copies;
     cfg.copy_stride = hist_copy_stride(1, nc);
     if (!rc)
