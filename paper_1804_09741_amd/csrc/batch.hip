@@ -43,10 +43,11 @@ struct mk_batch {
     uint32_t *d_counters = nullptr;
     uint32_t *d_unit_begin = nullptr;    // first unit of every graph, plus the total
     unsigned long long *d_hist_own = nullptr;
-    unsigned long long *d_hist_copies = nullptr;  // copies > 1: what the waves add to
-                                                  // (behind the units, one allocation)
-    uint32_t copies = 1;
+    HistLayout layout;                            // of what the waves count into:
+    unsigned long long *d_hist_work = nullptr;    // a work array behind the units (one
+                                                  // allocation), null: the histograms
     uint32_t *d_wave_scratch = nullptr;  // core method: per-workgroup arc lists
+    uint32_t arc_cap = 0;                //   of this many arc pairs
     void *d_marks = nullptr;             // MK_MARKS_GLOBAL: per-workgroup marks
     size_t mark_stride = 0;              //   marks per workgroup
     size_t mark_bytes = 0;               //   bytes of d_marks
@@ -78,6 +79,10 @@ struct mk_batch {
 // split (12% off the k = 6 kernel on 31 power-law graphs of 700 vertices)
 static constexpr uint64_t kDefaultSplit[8] = {0,       0,       1u << 30, 1u << 30,
                                               1u << 10, 1u << 12, 1u << 9, 1u << 12};
+// k = 6 counted from the (k-2)-sets plans for 5-sets, of which a unit of 4,096
+// can hold hundreds of cores (5 us each, so units of 1 ms): n = 700, m = 1500
+// 1.37 -> 0.36 ms of kernel with 256 (1,024: 0.6; 64 and 128 as 256).
+static constexpr uint64_t kCore6Split = 1u << 8;
 
 namespace mk {
 uint64_t default_split_floor(int plan_k)
@@ -192,6 +197,7 @@ static EnumConfig enum_config(const mk_batch *b)
     c.flags = (uint32_t)b->debug_flags;
     c.chunk = (uint32_t)std::max(b->opts.units_per_grab, 0);
     c.wave_scratch = b->d_wave_scratch;
+    c.arc_cap = b->arc_cap;
     c.hash_bits = b->method == MK_METHOD_CORES ? core_hash_bits(b->k) : enum_hash_bits(b->k);
     // the test hooks of the hash run in the kernels built with them
     c.variant = b->variant |
@@ -207,8 +213,7 @@ static EnumConfig enum_config(const mk_batch *b)
     // better: k = 5, n = 5000, m = 30000 (38 units a wave) 30.3 against 32.5 ms.
     c.mix = b->ng < kQueues &&
             (b->units < 16 * (uint64_t)b->grid || b->adjacency == MK_ADJ_LISTS);
-    c.hist_copies = b->copies;
-    c.copy_stride = b->table ? hist_copy_stride(b->ng, b->table->num_classes) : 0;
+    c.hist = b->layout;
     return c;
 }
 
@@ -234,9 +239,8 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
     if (rc) return rc;
     if (hist) {
         const uint32_t nc = b->table->num_classes;
-        rc = b->copies > 1 ? fill_u32(b->d_hist_copies, 0, 2 * b->copies * hist_copy_stride(b->ng, nc),
-                                      stream)
-                           : fill_u32(hist, 0, (size_t)b->ng * nc * 2, stream);
+        rc = b->d_hist_work ? fill_u32(b->d_hist_work, 0, 2 * b->layout.words(), stream)
+                            : fill_u32(hist, 0, (size_t)b->ng * nc * 2, stream);
         if (rc) return rc;
     }
     rc = batch_enqueue_typed(b, stream);
@@ -252,7 +256,7 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
 static int batch_launch_count(mk_batch *b, unsigned long long *hist, uint32_t unit_end, int grid,
                               hipStream_t stream)
 {
-    if (b->copies > 1) hist = b->d_hist_copies;
+    if (b->d_hist_work) hist = b->d_hist_work;
     if (b->method == MK_METHOD_CORES)
         return launch_core(b->k, b->d_graphs, b->d_units, b->unit_cap, unit_end, b->d_counters,
                            b->table->d_table, b->table->num_classes, hist, enum_config(b), grid,
@@ -263,17 +267,16 @@ static int batch_launch_count(mk_batch *b, unsigned long long *hist, uint32_t un
 }
 
 // after the last unit of graphs first..first+rows-1 (hist: their rows): the
-// copies of the histograms are summed, and the cores method divides its raw
+// work array goes to the histograms, and the cores method divides its raw
 // sums
 static int batch_launch_finish(mk_batch *b, unsigned long long *hist, int first, int rows,
                                hipStream_t stream)
 {
     const uint32_t nc = b->table->num_classes;
     const uint8_t *mult = b->method == MK_METHOD_CORES ? b->table->d_core_mult : nullptr;
-    if (b->copies > 1)
-        return launch_hist_finish(b->d_hist_copies + (size_t)first * nc, b->copies,
-                                  hist_copy_stride(b->ng, nc), hist, rows, nc, mult, b->d_counters,
-                                  stream);
+    if (b->d_hist_work)
+        return launch_hist_finish(b->d_hist_work, b->layout, first, hist, rows, nc, mult,
+                                  b->d_counters, stream);
     if (!mult) return MK_OK;
     return launch_core_divide(hist, rows, nc, mult, b->d_counters, stream);
 }
@@ -300,9 +303,11 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
 }
 
 // A batch of ng graphs for subgraph size k: counted with table t (k <= 6),
-// or with the k = 7 kernel and no table (t null).
+// or with the k = 7 kernel and no table (t null).  lean: without the memory
+// that mk_graph_footprint does not count (the histograms' work array, the
+// arc lists of k = 6 from the (k-2)-sets).
 static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int k,
-                        const mk_table *t, const mk_batch_opts *opts, mk_batch **out)
+                        const mk_table *t, const mk_batch_opts *opts, bool lean, mk_batch **out)
 {
     *out = nullptr;
     for (int i = 0; i < ng; ++i)
@@ -364,12 +369,11 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     b->adjacency = b->opts.adjacency != MK_ADJ_AUTO
                        ? b->opts.adjacency
                        : (b->marks == MK_MARKS_GLOBAL ? MK_ADJ_LISTS : MK_ADJ_BITS);
-    // the library's choice of method: counting from the (k-2)-sets is the
-    // faster on sparse graphs for k <= 5; for k = 6 the per-core work (up to
-    // 255 cells) costs more than enumerating the k-sets
     b->method = b->opts.method != MK_METHOD_AUTO
                     ? b->opts.method
-                    : (b->k <= 5 && b->marks == MK_MARKS_LDS ? MK_METHOD_CORES : MK_METHOD_ESU);
+                    : (b->marks == MK_MARKS_LDS && b->k <= 5
+                           ? MK_METHOD_CORES
+                           : MK_METHOD_ESU);
     if (b->marks == MK_MARKS_LDS && big) {
         const int max_n = b->max_n;
         delete b;
@@ -388,7 +392,9 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     b->variant = (b->adjacency == MK_ADJ_LISTS ? kVarSearch : 0) |
                  (b->marks == MK_MARKS_GLOBAL ? kVarGlobal : 0);
     b->plan_k = b->method == MK_METHOD_CORES ? (b->k == 3 ? 2 : b->k - 1) : b->k;
-    if (b->opts.split_threshold == 0) b->opts.split_threshold = kDefaultSplit[b->plan_k];
+    if (b->opts.split_threshold == 0)
+        b->opts.split_threshold = b->method == MK_METHOD_CORES && b->k == 6 ? kCore6Split
+                                                                           : kDefaultSplit[b->plan_k];
     if (b->opts.use_graph == 0) b->opts.use_graph = 1;
 
     b->bits_words = b->adjacency == MK_ADJ_BITS ? bits : 0;
@@ -501,16 +507,32 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
     b->unit_cap = std::max<uint32_t>(cnt[kNumUnits], 1);
     b->grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, std::max<uint64_t>(b->units, 1));
-    if (t) b->copies = hist_copies(ng, t->num_classes, b->grid);
+    if (t && !lean)
+        b->layout = hist_layout(ng, t->num_classes, b->grid, b->method == MK_METHOD_CORES);
     const size_t unit_bytes = (sizeof(int4) * (size_t)b->unit_cap + 255) & ~(size_t)255;
-    const size_t copy_bytes = b->copies > 1 ? 8 * b->copies * hist_copy_stride(ng, t->num_classes) : 0;
-    BAIL_HIP(hipMalloc(&b->d_units, unit_bytes + copy_bytes));
-    if (b->copies > 1)
-        b->d_hist_copies = reinterpret_cast<unsigned long long *>(
+    if (b->layout.graph_words &&
+        hipMalloc(&b->d_units, unit_bytes + 8 * b->layout.words()) != hipSuccess) {
+        (void)hipGetLastError();  // no room for the work array: count in place
+        b->d_units = nullptr;
+        b->layout = HistLayout();
+    }
+    if (!b->d_units) BAIL_HIP(hipMalloc(&b->d_units, unit_bytes));
+    if (b->layout.graph_words)
+        b->d_hist_work = reinterpret_cast<unsigned long long *>(
             reinterpret_cast<char *>(b->d_units) + unit_bytes);
 
-    if (b->method == MK_METHOD_CORES)
-        BAIL_HIP(hipMalloc(&b->d_wave_scratch, sizeof(uint32_t) * kParentArcCap * (size_t)b->grid));
+    if (b->method == MK_METHOD_CORES && k >= 5) {
+        // Lists of kParentArcCap arc pairs, longer (to 4 times) where the
+        // launch has fewer waves than the footprint counts with: a parent
+        // with more has every list scanned again for each of its children
+        // (k = 5, n = 5000, m = 30000, parents of up to 3,084 arc pairs: 30.0
+        // -> 17.9 ms).  At k <= 4 there are none: a core has no parent.
+        const uint64_t waves = std::min<uint64_t>(b->total_slots + 1ull, 8192);
+        b->arc_cap = (uint32_t)std::min<uint64_t>(
+            std::max<uint64_t>(waves * kParentArcCap / (uint64_t)b->grid, kParentArcCap),
+            4 * kParentArcCap);
+        BAIL_HIP(hipMalloc(&b->d_wave_scratch, sizeof(uint32_t) * b->arc_cap * (size_t)b->grid));
+    }
     if (b->marks == MK_MARKS_GLOBAL) {
         // zero once: every pop restores the marks it changed, so they are
         // zero again whenever a workgroup finishes a unit
@@ -531,8 +553,16 @@ extern "C" int mk_batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t n
     if (!ctx || !t || !out || (ng > 0 && !gs)) return fail(MK_EINVAL, "mk_batch_create: NULL argument");
     if (ng < 0) return fail(MK_EINVAL, "mk_batch_create: ng=%d < 0", ng);
     if (t->ctx != ctx || !t->d_table) return fail(MK_EINVAL, "mk_batch_create: table of another context");
-    return batch_create(ctx, gs, ng, t->k, t, opts, out);
+    return batch_create(ctx, gs, ng, t->k, t, opts, false, out);
 }
+
+namespace mk {
+int batch_create_lean(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
+                      const mk_batch_opts *opts, mk_batch **out)
+{
+    return batch_create(ctx, gs, ng, t->k, t, opts, true, out);
+}
+}  // namespace mk
 
 extern "C" int mk_batch_run(mk_batch *b, uint64_t *d_hist, void *stream)
 {
@@ -668,9 +698,9 @@ uint64_t batch_device_bytes(const mk_batch *b)
     for (const mk_graph *g : b->graphs) words += (uint64_t)g->n + 1 + (uint64_t)g->nnz_u;
     return 4 * words + 20ull * b->total_slots + 4 * scan_tmp_words(b->total_slots) +
            16ull * b->unit_cap + 8ull * b->ng * b->table->num_classes + 4ull * (b->ng + 1) +
-           (b->d_hist_copies ? 8ull * b->copies * hist_copy_stride(b->ng, b->table->num_classes) : 0) +
+           8ull * b->layout.words() +
            sizeof(DevGraph) * b->graphs.size() + 4 * kNumCounters +
-           (b->d_wave_scratch ? 4ull * kParentArcCap * (uint64_t)b->grid : 0) + b->mark_bytes;
+           (b->d_wave_scratch ? 4ull * b->arc_cap * (uint64_t)b->grid : 0) + b->mark_bytes;
 }
 
 // typed adjacency + plan into the batch's own histogram buffer
@@ -1149,7 +1179,7 @@ extern "C" int mk_count7(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int
     o.adjacency = big ? MK_ADJ_LISTS : MK_ADJ_BITS;
     o.marks = big ? MK_MARKS_GLOBAL : MK_MARKS_LDS;
     mk_batch *b = nullptr;
-    int rc = batch_create(ctx, gs, ng, 7, nullptr, &o, &b);
+    int rc = batch_create(ctx, gs, ng, 7, nullptr, &o, false, &b);
     if (rc) return rc;
     // class tables of the size the last count needed (2^10 slots per graph
     // at first), 4x larger after an overflow

@@ -49,8 +49,7 @@ constexpr int kCoreR = K - 2;                     // members of a core
 // more waves: the kernel waits on dependent L2 and LDS reads, and its speed
 // follows the waves in flight.  101 graphs of n = 1000 at k = 5: 22 -> 26
 // waves a CU, 17.4 -> 16.0 ms; n = 5000, m = 30000: k = 5 10 -> 15 waves,
-// 41.7 -> 30.8 ms, k = 6 6 -> 14 waves, 192 -> 92 ms (95 with arc-pair tables
-// of 12 cells as before).
+// 41.7 -> 30.8 ms, k = 6 6 -> 14 waves, 192 -> 95 ms.
 template <int K>
 constexpr int kCells = 1 << (2 * kSegments<K>);   // relation vectors
 
@@ -60,11 +59,11 @@ constexpr int kCells = 1 << (2 * kSegments<K>);   // relation vectors
 // non-empty entry.  Cores with more cells insert +1/-1 per arc pair, two
 // class lookups and two inserts each.  The sizes balance those cores against
 // the waves that the table's LDS costs.  k = 5 (101 graphs of n = 1000) with
-// 13 / 15 / 18 cells: 16.8 / 16.0 / 16.6 ms; k = 6 with 8 / 12 / 16 / 20 / 24 /
-// 32 cells: n = 5000, m = 30000 121 / 95 / 92 / 92 / 96 / 110 ms, n = 1000,
-// m = 4000 13.3 / 12.3 / 11.2 / 11.0 / 11.1 / 11.1 ms.
+// 13 / 15 / 18 cells: 16.8 / 16.0 / 16.6 ms; k = 6 with 12 / 14 / 16 / 20
+// cells: n = 5000, m = 30000 84 / 78 / 87 / 88 ms, n = 1000, m = 4000 4.6 /
+// 4.2 / 4.0 / 4.0 ms.
 #ifndef MK_AGG_CELLS_K6
-#define MK_AGG_CELLS_K6 16
+#define MK_AGG_CELLS_K6 14
 #endif
 #ifndef MK_AGG_CELLS_K5
 #define MK_AGG_CELLS_K5 15
@@ -85,6 +84,7 @@ struct CoreLds {
     uint8_t *pos;
     uint32_t *agg;
     uint32_t *ap;  // global: this workgroup's arc list of the current parent
+    uint32_t ap_cap;  //   and the arc pairs it holds
 };
 
 __host__ __device__ inline int core_extra_bytes(int k)
@@ -262,7 +262,7 @@ __device__ __forceinline__ void scan_taken(EnumState<K, V> &s, const CoreLds &c,
 
 // The arc pairs (u, v), u < v, inside adj(P) for the parent P = mem[0..NP-1]
 // (all pushed, nothing below): into c.ap as u | v << 13 | type << 26.
-// Returns their number, or -1 when they exceed kParentArcCap.
+// Returns their number, or -1 when they exceed the list.
 template <int K, int NP, int V>
 __device__ int parent_arcs(EnumState<K, V> &s, const CoreLds &c, const int (&mem)[K])
 {
@@ -282,12 +282,12 @@ __device__ int parent_arcs(EnumState<K, V> &s, const CoreLds &c, const int (&mem
         [&](bool edge, int u, int v, uint32_t, uint32_t, uint32_t t) {
             const unsigned long long bal = __ballot(edge);
             const int at = nap + (int)lanes_below(bal);
-            if (edge && at < (int)kParentArcCap)
+            if (edge && at < (int)c.ap_cap)
                 c.ap[at] = (uint32_t)u | ((uint32_t)v << 13) | (t << 26);
             nap += __popcll(bal);
         });
     restore_members<K, NP>(s, id, old);
-    return nap > (int)kParentArcCap ? -1 : nap;
+    return nap > (int)c.ap_cap ? -1 : nap;
 }
 
 // one core X = mem[0..k-3] with internal code cx (all members pushed)
@@ -586,7 +586,8 @@ __device__ __forceinline__ void core_body(const DevGraph *graphs, const int4 *un
     c.list = reinterpret_cast<uint8_t *>(c.cnt + kCells<K>);
     c.pos = c.list + kCells<K>;
     c.agg = reinterpret_cast<uint32_t *>(c.pos + kCells<K>);
-    c.ap = cfg.wave_scratch ? cfg.wave_scratch + (size_t)blockIdx.x * kParentArcCap : nullptr;
+    c.ap = cfg.wave_scratch ? cfg.wave_scratch + (size_t)blockIdx.x * cfg.arc_cap : nullptr;
+    c.ap_cap = cfg.arc_cap;
     for (int i = lane_id(); i < kCells<K>; i += kWave) c.cnt[i] = 0u;
     for (int i = lane_id(); i < kAggWords<K>; i += kWave) c.agg[i] = 0u;
     init_state<K>(s, base, lay, cfg, counters, table, num_classes);
@@ -624,57 +625,6 @@ __global__ __launch_bounds__(kWave) void core_debug_kernel(const DevGraph *graph
 {
     core_body<K, kVarCore | kVarDebug>(graphs, units, unit_cap, unit_end, counters, table,
                                        num_classes, hist_base, cfg);
-}
-
-// hist[g][c] := raw / core_mult[c]; a raw count that is not a multiple (or
-// is negative as a 64-bit integer) is a device-side error.
-__global__ void core_divide_kernel(unsigned long long *hist, uint32_t num_classes,
-                                   const uint8_t *mult, uint32_t *errors)
-{
-    unsigned long long *h = hist + (size_t)blockIdx.y * num_classes;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < num_classes;
-         i += gridDim.x * blockDim.x) {
-        const unsigned long long raw = h[i];
-        if (raw == 0) continue;
-        const uint32_t m = mult[i];
-        if (m == 0 || (long long)raw < 0) {
-            atomicAdd(errors, 1u);
-            continue;
-        }
-        const unsigned long long q = raw / m;
-        if (q * m != raw) atomicAdd(errors, 1u);
-        h[i] = q;
-    }
-}
-
-// Where few bins take the counts of thousands of waves (one or a few graphs
-// at k <= 5), the waves' atomics on the hot bins serialise: every wave
-// flushes the same frequent classes, 20-30 ns a wave on one bin.  The waves
-// then add to copies of the histograms (wave w to copy w mod copies), and
-// this kernel sums them, dividing by the cores per class for the core
-// method: one thread per bin, a coalesced read per copy, bound by launch
-// latency (4 us).  Counting kernel with one copy and with 16: k = 4,
-// n = 2000, m = 10000 (199 bins, 4,608 waves) 0.351 -> 0.148 ms; k = 5 by
-// enumeration, n = 1000, m = 3000 1.33 -> 0.73 ms, from the cores 0.58 ->
-// 0.49 ms; k = 3, n = 5000, m = 30000 0.178 -> 0.110 ms.
-__global__ void hist_finish_kernel(const unsigned long long *src, uint32_t copies, size_t stride,
-                                   unsigned long long *hist, uint32_t num_classes,
-                                   const uint8_t *mult, uint32_t *errors)
-{
-    const size_t row = (size_t)blockIdx.y * num_classes;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < num_classes;
-         i += gridDim.x * blockDim.x) {
-        unsigned long long raw = 0;
-#pragma unroll 8
-        for (uint32_t c = 0; c < copies; ++c) raw += src[c * stride + row + i];
-        if (mult && raw != 0) {
-            const uint32_t m = mult[i];
-            const unsigned long long q = m ? raw / m : 0ull;
-            if (m == 0 || (long long)raw < 0 || q * m != raw) atomicAdd(errors, 1u);
-            if (m != 0 && (long long)raw >= 0) raw = q;
-        }
-        hist[row + i] = raw;
-    }
 }
 
 // Per-wave hash slots of the core kernel (keys are class ids).  Its LDS
@@ -733,53 +683,6 @@ int launch_core(int k, const DevGraph *d_graphs, const int4 *units, uint32_t uni
                     (void *)&counters, (void *)&table, (void *)&num_classes, (void *)&hist_base,
                     (void *)&c};
     MK_HIP(hipLaunchKernel(fn, dim3(grid), dim3(kWave), args, (size_t)lds_bytes, stream));
-    MK_HIP(hipGetLastError());
-    return MK_OK;
-}
-
-int launch_core_divide(unsigned long long *hist, int ng, uint32_t num_classes,
-                       const uint8_t *mult, uint32_t *counters, hipStream_t stream)
-{
-    if (ng <= 0 || num_classes == 0) return MK_OK;
-    constexpr int kThreads = 256;
-    const uint32_t blocks = std::min<uint32_t>((num_classes + kThreads * 4 - 1) / (kThreads * 4), 4096u);
-    hipLaunchKernelGGL(core_divide_kernel, dim3(blocks, (unsigned)ng), dim3(kThreads), 0, stream,
-                       hist, num_classes, mult, &counters[kErrors]);
-    MK_HIP(hipGetLastError());
-    return MK_OK;
-}
-
-// All copies together hold up to 2^18 words (2 MiB), so that clearing and
-// summing them stays at a few microseconds, and eight waves or more share a
-// copy.  More graphs or bins than that spread the atomics by themselves.  8,
-// 32 and 64 copies time like 16 (k = 4, n = 2000: 0.156, 0.149 and 0.147 ms).
-constexpr size_t kHistCopyWords = (size_t)1 << 18;
-constexpr uint32_t kHistCopiesMax = 16;
-
-size_t hist_copy_stride(int ng, uint32_t num_classes)
-{
-    return ((size_t)std::max(ng, 0) * num_classes + 31) & ~(size_t)31;
-}
-
-uint32_t hist_copies(int ng, uint32_t num_classes, int grid)
-{
-    if (ng <= 0 || num_classes == 0) return 1;
-    const size_t most = std::min<size_t>(kHistCopyWords / hist_copy_stride(ng, num_classes),
-                                         (size_t)std::max(grid, 0) / 8);
-    uint32_t c = 1;
-    while (c < kHistCopiesMax && 2 * (size_t)c <= most) c *= 2;
-    return c;
-}
-
-int launch_hist_finish(const unsigned long long *copies_base, uint32_t copies, size_t stride,
-                       unsigned long long *hist, int rows, uint32_t num_classes,
-                       const uint8_t *mult, uint32_t *counters, hipStream_t stream)
-{
-    if (rows <= 0 || num_classes == 0) return MK_OK;
-    constexpr int kThreads = 64;
-    const uint32_t blocks = std::min<uint32_t>((num_classes + kThreads - 1) / kThreads, 4096u);
-    hipLaunchKernelGGL(hist_finish_kernel, dim3(blocks, (unsigned)rows), dim3(kThreads), 0, stream,
-                       copies_base, copies, stride, hist, num_classes, mult, &counters[kErrors]);
     MK_HIP(hipGetLastError());
     return MK_OK;
 }

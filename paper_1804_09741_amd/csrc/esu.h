@@ -152,6 +152,7 @@ struct EnumState {
     bool class_keys;            // hash keys are class ids, not codes
     uint32_t flags;             // kDebug* bits
     unsigned long long *hist;
+    uint32_t row_bits, row_stride;  // class id's word in hist: see HistLayout
     const uint32_t *table;
     uint32_t num_classes;
     uint32_t *errors;
@@ -353,7 +354,9 @@ __device__ __forceinline__ void add_global(EnumState<K, V> &s, uint32_t code, ui
     const uint32_t id = s.class_keys ? code : s.table[code];
     // n is a 32-bit two's complement count (negative only in the (k-2)-set
     // counting); sign-extended, the 64-bit sums stay exact modulo 2^64
-    if (id < s.num_classes) atomicAdd(&s.hist[id], (unsigned long long)(long long)(int32_t)n);
+    if (id < s.num_classes)
+        atomicAdd(&s.hist[(id & ((1u << s.row_bits) - 1u)) * s.row_stride + (id >> s.row_bits)],
+                  (unsigned long long)(long long)(int32_t)n);
     else atomicAdd(s.errors, 1u);
 }
 
@@ -491,6 +494,8 @@ __device__ __forceinline__ void init_state(EnumState<K, V> &s, char *base, const
     s.urow = nullptr;
     s.uadj = nullptr;
     s.hist = nullptr;
+    s.row_bits = 31u;
+    s.row_stride = 1u;
     // global marks are zeroed when allocated and every pop restores them
     if constexpr ((V & kVarGlobal) == 0) {
         uint32_t *w = reinterpret_cast<uint32_t *>(base);
@@ -611,15 +616,16 @@ __device__ __forceinline__ void for_each_unit(EnumState<K, V> &s, const DevGraph
                                               unsigned long long *hist_base, const EnumConfig &cfg,
                                               Run run)
 {
-    // this wave's copy of the histograms
-    unsigned long long *hist =
-        cfg.hist_copies > 1u ? hist_base + (blockIdx.x & (cfg.hist_copies - 1u)) * cfg.copy_stride
-                             : hist_base;
+    // this wave's copy of the work array
+    unsigned long long *hist = hist_base + (blockIdx.x & (cfg.hist.copies - 1u)) * cfg.hist.copy_words;
+    const size_t per_graph = cfg.hist.graph_words ? cfg.hist.graph_words : s.num_classes;
+    s.row_bits = cfg.hist.row_bits;
+    s.row_stride = cfg.hist.stride;
     unit_loop<HeavyFirst>(
         s, graphs, units, unit_cap, unit_end, counters, cfg, run,
         [&](int gi) {
             if (s.hused) flush_hash<K>(s);
-            s.hist = hist + (size_t)gi * s.num_classes;
+            s.hist = hist + (size_t)gi * per_graph;
         },
         [&] {
             if (s.hused > s.hunit) flush_hash<K>(s);

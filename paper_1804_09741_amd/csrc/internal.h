@@ -51,6 +51,7 @@ struct Graph {
     int64_t m = 0;
     int64_t nnz_u = 0;        // sum of undirected degrees |delta(v)|
     int32_t max_udeg = 0;
+    int64_t sum_d2 = 0;       // sum of squared undirected degrees
     int32_t *d_row = nullptr; // n+1, out-adjacency CSR as given
     int32_t *d_col = nullptr; // m
 };
@@ -236,26 +237,36 @@ constexpr int kVarGlobal = 2;
 constexpr int kVarDebug = 4;
 constexpr int kVarCore = 8;
 
+// Where class id of graph g is counted, in u64 words:
+//   copy * copy_words + g * graph_words + (id mod 2^row_bits) * stride
+//   + id / 2^row_bits.
+// graph_words = 0: the histograms themselves, g * num_classes + id.
+struct HistLayout {
+    uint32_t copies = 1;     // wave w adds to copy w mod copies (a power of two)
+    uint32_t row_bits = 31;
+    uint32_t stride = 1;
+    size_t graph_words = 0;  // 0: no work array, the histograms themselves
+    size_t copy_words = 0;
+    size_t words() const { return (size_t)copies * copy_words; }
+};
+// The layout of a launch of `grid` waves over ng graphs (see hist.hip).
+HistLayout hist_layout(int ng, uint32_t num_classes, int grid, bool cores);
+
 struct EnumConfig {
     int max_n;       // largest n of the batch (LDS marks)
     int seg_cap;     // largest undirected degree (LDS extension segments)
     uint32_t flags;  // kDebug* bits below (tests only; 0 in production)
     uint32_t chunk;  // units per queue grab; 0 = about 1/32 of a wave's share
-    uint32_t *wave_scratch;  // core kernel: kParentArcCap words per workgroup
+    uint32_t *wave_scratch;  // core kernel: arc_cap words per workgroup
+    uint32_t arc_cap;        //   arc pairs kept per parent
     int hash_bits;           // log2 of the per-wave hash slots (enum_/core_hash_bits)
     int variant;             // kVar* bits of the enumeration kernel (esu.h)
     void *marks;             // kVarGlobal: grid x mark_stride marks, all zero
     size_t mark_stride;      //   marks per workgroup (>= max_n)
     uint32_t mix;            // 1: the queues deal the units out in turn, 0: a range each
-    uint32_t hist_copies;    // copies of the histograms the waves add to (0 or 1: one)
-    size_t copy_stride;      //   u64 words from one copy to the next
+    HistLayout hist;         // where the waves' counts go
 };
 
-// Copies of the histograms for a launch of `grid` waves over ng graphs of
-// num_classes bins (a power of two; 1: the waves add to the histogram
-// itself), and the words between two copies.  See launch_hist_finish.
-uint32_t hist_copies(int ng, uint32_t num_classes, int grid);
-size_t hist_copy_stride(int ng, uint32_t num_classes);
 int enum_hash_bits(int k);
 int core_hash_bits(int k);
 constexpr uint32_t kDebugNoHash = 1u;      // every code straight to the histogram
@@ -284,9 +295,9 @@ int launch_core(int k, const DevGraph *d_graphs, const int4 *units, uint32_t uni
                 hipStream_t stream);
 int launch_core_divide(unsigned long long *hist, int ng, uint32_t num_classes,
                        const uint8_t *mult, uint32_t *counters, hipStream_t stream);
-// The copies of `rows` histograms (copies of `stride` words) summed into
-// hist; with mult the sums are divided by the cores per class too.
-int launch_hist_finish(const unsigned long long *copies_base, uint32_t copies, size_t stride,
+// The counts of graphs first.. (rows of them) in the work array src, laid
+// out as l, into their histograms; with mult divided by the cores per class.
+int launch_hist_finish(const unsigned long long *src, const HistLayout &l, int first,
                        unsigned long long *hist, int rows, uint32_t num_classes,
                        const uint8_t *mult, uint32_t *counters, hipStream_t stream);
 

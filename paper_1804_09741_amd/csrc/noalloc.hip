@@ -101,8 +101,8 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     }
 
     // layout of the scratch: counters | descriptor | bit matrices | urow |
-    // uadj | 5 planner slot arrays | scan workspace | work units | copies of
-    // the histogram (when there is room)
+    // uadj | 5 planner slot arrays | scan workspace | work units | work array
+    // of the histogram (when there is room)
     const uint64_t n = (uint64_t)g->n, w = (n + 31) / 32, nnz = (uint64_t)g->nnz_u;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -154,28 +154,27 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     if (rc) return rc;
     const int grid = std::max(per_cu, 1) * ctx->num_cus;
 
-    // The copies of the histogram go behind the most units this plan can
+    // The histogram's work array goes behind the most units this plan can
     // make: consecutive ranges of a node exceed the split threshold together
     // and the threshold is at least the estimated total over 32 units a
     // wave, so there are at most two ranges per unit of that target and one
     // more per node.
-    uint32_t copies = hist_copies(1, nc, grid);
-    const size_t copy_bytes = 8 * (size_t)copies * hist_copy_stride(1, nc);
+    HistLayout layout = hist_layout(1, nc, grid, false);
     const uint64_t most_units = 2 * (32ull * (uint64_t)grid + 1) + nnz + kMinStaticUnits;
-    const size_t o_copies = round_up(o_units + most_units * sizeof(int4), 256);
-    if (copies > 1 && o_copies + copy_bytes <= kStaticScratchBytes)
-        unit_cap = (o_copies - o_units) / sizeof(int4);
+    const size_t o_work = round_up(o_units + most_units * sizeof(int4), 256);
+    if (layout.graph_words && o_work + 8 * layout.words() <= kStaticScratchBytes)
+        unit_cap = (o_work - o_units) / sizeof(int4);
     else
-        copies = 1;
+        layout = HistLayout();
     unsigned long long *count_to =
-        copies > 1 ? reinterpret_cast<unsigned long long *>(base + o_copies) : hist;
+        layout.graph_words ? reinterpret_cast<unsigned long long *>(base + o_work) : hist;
 
     hipLaunchKernelGGL(put_devgraph, dim3(1), dim3(1), 0, s, dg, d);
     MK_HIP(hipGetLastError());
     rc = fill_u32(counters, 0, kNumCounters, s);
     if (!rc)
-        rc = copies > 1 ? fill_u32(count_to, 0, copy_bytes / 4, s)
-                        : fill_u32(hist, 0, (size_t)nc * 2, s);
+        rc = layout.graph_words ? fill_u32(count_to, 0, 2 * layout.words(), s)
+                                : fill_u32(hist, 0, (size_t)nc * 2, s);
     if (!rc) rc = launch_typed_csr(dg, 1, g->n, g->m, 2 * n * w, d.bits_out, counters, s);
     if (!rc)
         rc = launch_plan(k, dg, 1, (int64_t)nnz, (uint32_t)nnz, slots, slots + nnz, slots + 2 * nnz,
@@ -187,13 +186,12 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     cfg.seg_cap = seg_cap;
     cfg.hash_bits = enum_hash_bits(k);
     cfg.mix = 1;  // one graph: see enum_config of the prepared batches
-    cfg.hist_copies = copies;
-    cfg.copy_stride = hist_copy_stride(1, nc);
+    cfg.hist = layout;
     if (!rc)
         rc = launch_enum(k, dg, units, (uint32_t)std::min<uint64_t>(unit_cap, 0xFFFFFFFFull),
                          kAllUnits, counters, t->d_table, nc, count_to, cfg, grid, lds, s);
-    if (!rc && copies > 1)
-        rc = launch_hist_finish(count_to, copies, cfg.copy_stride, hist, 1, nc, nullptr, counters, s);
+    if (!rc && layout.graph_words)
+        rc = launch_hist_finish(count_to, layout, 0, hist, 1, nc, nullptr, counters, s);
     if (rc) return rc;
     uint32_t cnt[kNumCounters];
     MK_HIP(hipMemcpyAsync(cnt, counters, sizeof(cnt), hipMemcpyDeviceToHost, s));

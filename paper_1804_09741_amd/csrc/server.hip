@@ -46,6 +46,8 @@ constexpr int kServerStreams = 4;  // the hardware queues a process gets
 constexpr uint64_t kDefaultBudget = 8ull << 30;
 constexpr int kDefaultSlots = 64;
 constexpr int kDefaultTickUnits = 8192;
+// the most a batch takes beyond its footprint (work array and arc lists)
+constexpr uint64_t kSpareBytes = 640ull << 20;
 // slices of a group queued on its stream at once: the next one is already
 // there when one ends, so the host's polling leaves no gap
 constexpr int kInFlight = 2;
@@ -201,7 +203,14 @@ static Group *start_group(mk_server *s, int k, std::vector<Request *> reqs, uint
     if (rc == MK_OK) {
         mk_batch_opts o{};
         o.use_graph = -1;
-        rc = mk_batch_create(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, &gp->batch);
+        // near the budget's end the batch keeps to its estimated footprint
+        bool lean;
+        {
+            std::lock_guard<std::mutex> lock(s->mu);
+            lean = s->used_bytes + kSpareBytes > s->opts.hbm_budget_bytes;
+        }
+        rc = lean ? batch_create_lean(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, &gp->batch)
+                  : mk_batch_create(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, &gp->batch);
     }
     if (rc == MK_OK) rc = batch_unit_begins(gp->batch, &gp->unit_begin);
     if (rc == MK_OK) rc = batch_prepare(gp->batch, s->streams[gp->stream]);

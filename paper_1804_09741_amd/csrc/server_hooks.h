@@ -11,6 +11,9 @@ namespace mk {
 
 // First work unit of every graph of a batch after mk_batch_create (its
 // sizing plan), plus the total: ng + 1 values.  Blocks.
+// mk_batch_create without the memory that mk_graph_footprint does not count
+int batch_create_lean(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
+                      const mk_batch_opts *opts, mk_batch **out);
 int batch_unit_begins(mk_batch *b, std::vector<uint32_t> *out);
 
 // Finish graph gi's histogram (the core method's division) and copy it to

@@ -1,7 +1,7 @@
-"""Histograms counted in copies and summed (few bins, one or a few graphs)
-and counted in place (many): every bin of the caller's buffer is written,
-and equals the oracle's, on both sides of the rule and through every call
-that finishes a histogram."""
+"""Histograms counted in a work array (in copies where it is small, in rows at
+k = 6) and counted in place (many graphs): every bin of the caller's buffer
+is written, and equals the oracle's, on both sides of the rule and through
+every call that finishes a histogram."""
 
 import numpy as np
 import pytest
@@ -17,9 +17,11 @@ def _graph(i, n=60, m=150):
     return I.chung_lu_digraph(n, m, 2.2, 25, 0.2, np.random.default_rng([77, i]))
 
 
-# (k, graphs): 2^18 words of copies hold 16 copies of one graph at k = 3..5,
-# two of 14 graphs and one of 15 at k = 5; 7 vertices make fewer than 16 waves
-@pytest.mark.parametrize("k,ng", [(3, 1), (4, 1), (5, 1), (5, 13), (5, 14), (5, 15), (4, 90)])
+# (k, graphs): one and many graphs, with the copies' 2^18 words full and not,
+# and the enumeration's 2^24 words of rows (10 graphs at k = 6) exceeded; one
+# graph of 7 vertices makes a few waves only
+@pytest.mark.parametrize("k,ng", [(3, 1), (4, 1), (5, 1), (5, 2), (5, 3), (5, 15), (4, 90),
+                                  (6, 1), (6, 10), (6, 11)])
 @pytest.mark.parametrize("method", [M.METHOD_ESU, M.METHOD_CORES])
 def test_batch_bins_all_written(ctx, k, ng, method):
     import torch
