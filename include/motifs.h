@@ -229,7 +229,8 @@ typedef struct mk_batch_opts {
                                  unit (the planner raises it so that the
                                  whole batch makes about units_per_wave
                                  units per wave); 0: 512 for k = 6 by
-                                 enumeration, 1024 for k = 5 by counting
+                                 enumeration and 256 by counting from
+                                 (k-2)-sets, 1024 for k = 5 by counting
                                  from (k-2)-sets and k = 4 by enumeration,
                                  else 4096 (nodes planned for sets of 3 or
                                  fewer vertices are not split) */
@@ -267,7 +268,8 @@ typedef struct mk_batch_opts {
      of one class at once, each arc inside adj(X) moves one k-set to its
      true class, and the sums are divided by the cores per class
      (mk_table_core_mult). */
-/* MK_METHOD_AUTO: MK_METHOD_CORES for k <= 5, MK_METHOD_ESU for k = 6 and
+/* MK_METHOD_AUTO: MK_METHOD_CORES for k <= 5 and, by the batch's degrees and
+   number of graphs, for k = 6 where it is the faster; MK_METHOD_ESU else and
    for graphs with more than MK_LDS_MARKS_MAX_VERTICES vertices (which
    MK_METHOD_CORES rejects with MK_ERANGE). */
 #define MK_METHOD_AUTO 0

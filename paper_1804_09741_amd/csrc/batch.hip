@@ -302,6 +302,31 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
     return MK_OK;
 }
 
+// The library's choice of method at k = 6.  (For k <= 5 counting from the
+// (k-2)-sets is the faster throughout: k = 5, n = 1000, m = 3000 0.5 against
+// 0.7 ms, 101 such graphs 16 against 54 ms.)  A core costs about the same
+// whatever it closes, so the counting pays where cores close many k-sets:
+// where a vertex reached along an edge has many neighbours, q = sum d^2 / sum
+// d of them, and four members' neighbours hardly overlap.  Pass times by
+// enumeration and from the (k-2)-sets over 90 graphs and batches of n =
+// 100..5000, m = 1.2 n..6 n: with n >= 40 q the ratio is 0.9 to 4.6 for up to
+// 15 graphs (n = 5000, m = 30000: 510 and 78 ms; n = 700, m = 1500: 1.0 and
+// 0.5 ms), below that 0.4 to 1.3 (n = 172, m = 609: 0.55 and 0.63 ms).
+// Batches of 16 and more light graphs fill the chip either way and add the
+// division's pass over the bins: 0.75 to 0.95 with q up to 6.5 (31 graphs of
+// n = 700, m = 1500: 2.95 and 3.1 ms), 1.02 to 1.7 from 7.5 on (16 of n =
+// 1142, m = 1737: 10.7 and 6.3 ms).
+static bool cores6(const mk_batch *b)
+{
+    double d1 = 0, d2 = 0;
+    for (const mk_graph *g : b->graphs) {
+        d1 += (double)g->nnz_u;
+        d2 += (double)g->sum_d2;
+    }
+    const double q = d1 > 0 ? d2 / d1 : 0.0;
+    return 40.0 * q <= (double)b->max_n && (b->ng < 16 || q >= 7.5);
+}
+
 // A batch of ng graphs for subgraph size k: counted with table t (k <= 6),
 // or with the k = 7 kernel and no table (t null).  lean: without the memory
 // that mk_graph_footprint does not count (the histograms' work array, the
@@ -371,7 +396,7 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                        : (b->marks == MK_MARKS_GLOBAL ? MK_ADJ_LISTS : MK_ADJ_BITS);
     b->method = b->opts.method != MK_METHOD_AUTO
                     ? b->opts.method
-                    : (b->marks == MK_MARKS_LDS && b->k <= 5
+                    : (b->marks == MK_MARKS_LDS && (b->k <= 5 || (b->k == 6 && !lean && cores6(b)))
                            ? MK_METHOD_CORES
                            : MK_METHOD_ESU);
     if (b->marks == MK_MARKS_LDS && big) {
