@@ -8,21 +8,29 @@
 // classes.
 //
 // Build, all on the GPU:
-//   1. canon pass: every lane owns 32 codes, spaced one wavefront apart so
-//      that stores coalesce, and walks all k! relabelings of them with one
-//      adjacent transposition per step (Steinhaus-Johnson-Trotter order).
-//      Swapping vertices a and a+1 of a code is two delta swaps: rows a and
-//      a+1 trade places as whole (k-1)-bit fields, and in every other row the
-//      two neighbouring column bits for a and a+1 trade places.  The running
-//      minimum is the canonical code.  A wavefront ballot marks the codes
-//      that are their own canonical form and connected ("representatives").
+//   1. canon pass: every code descends: it is replaced by the least of itself
+//      and its images under the k-1 adjacent transpositions, in turn, until a
+//      round changes nothing.  (Swapping vertices a and a+1 of a code is two
+//      delta swaps: rows a and a+1 trade places as whole (k-1)-bit fields, and
+//      in every other row the two neighbouring column bits for a and a+1
+//      trade places.)  The code it ends at, in the same class, is a local
+//      minimum, and its table entry is what the code's own will be.  Codes
+//      that do not move (for k = 6 one in 119: 9.0 M of 2^30) are gathered in
+//      LDS and walk all k! relabelings, full waves of them, one adjacent
+//      transposition per step (Steinhaus-Johnson-Trotter order); the least
+//      code met is the canonical one.  Those that are their own canonical
+//      form and connected are marked as representatives in a bitmap.
 //   2. rank: exclusive prefix sum of the popcounts of the representative
 //      bitmap.
-//   3. class list (representatives in rank order) and final pass: entry c
-//      becomes rank(canonical(c)) or MK_INVALID_CLASS.
+//   3. class list (representatives in rank order); the entries of the local
+//      minima become the ranks of their canonical codes; and every other
+//      entry takes its local minimum's.
 //
-// The pass is plain integer ALU work: k = 6 is 2^30 codes x 719 steps of
-// about nine VALU operations each.
+// k = 6: a wave's 64 codes take about 4 rounds of 5 transpositions, 200 VALU
+// operations, where walking every code through 719 steps took 6,500: the
+// canon pass 180 -> 8.5 ms.  The last pass gathers 2^30 entries from 9.0 M
+// places, bound by those reads (7.1 ms; reading and writing the table alone
+// would take 1.5 ms); the whole build 188 -> 17 ms.
 #include <algorithm>
 #include <numeric>
 #include <set>
@@ -120,40 +128,97 @@ __device__ __forceinline__ bool code_connected(uint32_t c)
     return reach == (1u << K) - 1;
 }
 
-template <int K, int NJ>
-__global__ __launch_bounds__(256) void canon_kernel(uint32_t *table, uint32_t *repbits,
-                                                    uint64_t ncodes, int steps)
+// Table entries while the table is built: bits 30..31 say what the rest is
+// (a class id or MK_INVALID_CLASS once final).
+constexpr uint32_t kTagShift = 30;
+constexpr uint32_t kTagEnd = 1u;    // the local minimum that the code descends to
+constexpr uint32_t kTagCanon = 2u;  // a local minimum's canonical code
+constexpr uint32_t kTagMask = (1u << kTagShift) - 1u;
+
+template <int K>
+__device__ __forceinline__ uint32_t swap_vertices(uint32_t v, uint32_t row, uint32_t col)
 {
-    const int lane = threadIdx.x % kWave;
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const uint64_t base = wave * (uint64_t)(kWave * NJ);
-    if (base >= ncodes) return;
-    uint32_t x[NJ], best[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) x[j] = best[j] = (uint32_t)(base + j * kWave + lane);
-    for (int s = 0; s < steps; ++s) {
-        const uint32_t rm = c_swaps[s].row;
-        const uint32_t cm = c_swaps[s].col;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            uint32_t v = x[j];
-            uint32_t t = ((v >> (K - 1)) ^ v) & rm;
-            v ^= t | (t << (K - 1));
-            t = ((v >> 1) ^ v) & cm;
-            v ^= t | (t << 1);
-            x[j] = v;
-            best[j] = min(best[j], v);
+    uint32_t t = ((v >> (K - 1)) ^ v) & row;
+    v ^= t | (t << (K - 1));
+    t = ((v >> 1) ^ v) & col;
+    return v ^ (t | (t << 1));
+}
+
+// masks of the swap of vertices a and a+1
+template <int K>
+__device__ __forceinline__ constexpr uint32_t row_mask(int a)
+{
+    return ((1u << (K - 1)) - 1u) << (a * (K - 1));
+}
+template <int K>
+__device__ __forceinline__ constexpr uint32_t col_mask(int a)
+{
+    uint32_t m = 0;
+    for (int r = 0; r < K; ++r)
+        if (r != a && r != a + 1) m |= 1u << (r * (K - 1) + a - (a > r ? 1 : 0));
+    return m;
+}
+
+constexpr int kCanonThreads = 256;
+constexpr int kCanonRounds = 128;  // codes per thread of a workgroup
+
+template <int K>
+__global__ __launch_bounds__(kCanonThreads) void canon_kernel(uint32_t *table, uint32_t *repbits,
+                                                              uint32_t ncodes, int steps)
+{
+    __shared__ uint32_t pend[2 * kCanonThreads];
+    __shared__ uint32_t npend;
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) npend = 0;
+    __syncthreads();
+    // the relabelings of the last n codes of the list, one a thread
+    auto walk = [&](uint32_t n) {
+        const uint32_t first = npend - n;
+        if (tid < n) {
+            const uint32_t c = pend[first + tid];
+            uint32_t v = c, best = c;
+            for (int s = 0; s < steps; ++s) {
+                v = swap_vertices<K>(v, c_swaps[s].row, c_swaps[s].col);
+                best = min(best, v);
+            }
+            const bool conn = code_connected<K>(c);
+            table[c] = conn ? best | (kTagCanon << kTagShift) : MK_INVALID_CLASS;
+            if (conn && best == c) atomicOr(&repbits[c >> 5], 1u << (c & 31u));
         }
-    }
+        __syncthreads();
+        if (tid == 0) npend = first;
+        __syncthreads();
+    };
+    const uint32_t base = blockIdx.x * (uint32_t)(kCanonThreads * kCanonRounds);
+    for (int r = 0; r < kCanonRounds; ++r) {
+        const uint32_t c = base + (uint32_t)r * kCanonThreads + tid;
+        if (base + (uint32_t)r * kCanonThreads >= ncodes) break;  // small tables
+        const bool in = c < ncodes;
+        uint32_t x = c;
+        for (;;) {
+            uint32_t y = x;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const uint32_t c = (uint32_t)(base + j * kWave + lane);
-        const bool conn = code_connected<K>(c);
-        table[c] = conn ? best[j] : (best[j] | 0x80000000u);
-        const unsigned long long rep = __ballot(conn && best[j] == c);
-        if (lane == 0)
-            reinterpret_cast<unsigned long long *>(repbits)[(base + j * kWave) / kWave] = rep;
+            for (int a = K - 2; a >= 0; --a) y = min(y, swap_vertices<K>(y, row_mask<K>(a), col_mask<K>(a)));
+            const bool moved = y != x;
+            x = y;
+            if (!__any(moved)) break;
+        }
+        if (in && x != c) table[c] = x | (kTagEnd << kTagShift);
+        const bool still = in && x == c;
+        const unsigned long long m = __ballot(still);
+        if (m) {
+            uint32_t at = 0;
+            if (tid % kWave == 0) at = atomicAdd(&npend, (uint32_t)__popcll(m));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+            const uint32_t below =
+                __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (still) pend[at + below] = c;
+        }
+        __syncthreads();
+        if (npend >= (uint32_t)kCanonThreads) walk(kCanonThreads);
+        else __syncthreads();  // npend is read before the next round adds to it
     }
+    if (npend > 0) walk(npend);
 }
 
 __global__ void classlist_kernel(const uint32_t *repbits, const uint32_t *rankbase,
@@ -170,30 +235,54 @@ __global__ void classlist_kernel(const uint32_t *repbits, const uint32_t *rankba
     }
 }
 
-__global__ void assign_kernel(uint32_t *table, const uint32_t *repbits, const uint32_t *rankbase,
-                              uint64_t ncodes)
+// the local minima's entries: canonical code -> its rank
+__global__ void rank_kernel(uint32_t *table, const uint32_t *repbits, const uint32_t *rankbase,
+                            uint32_t ncodes)
 {
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (; i < ncodes; i += stride) {
-        const uint32_t x = table[i];
-        if (x & 0x80000000u) {
-            table[i] = MK_INVALID_CLASS;
-        } else {
-            const uint32_t w = x >> 5;
-            table[i] = rankbase[w] + (uint32_t)__popc(repbits[w] & ((1u << (x & 31)) - 1u));
-        }
+    uint4 *t4 = reinterpret_cast<uint4 *>(table);
+    auto rank = [&](uint32_t x) {
+        if (x >> kTagShift != kTagCanon) return x;
+        x &= kTagMask;
+        const uint32_t w = x >> 5;
+        return rankbase[w] + (uint32_t)__popc(repbits[w] & ((1u << (x & 31)) - 1u));
+    };
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < ncodes / 4; i += stride) {
+        uint4 v = t4[i];
+        const bool any = v.x >> kTagShift == kTagCanon || v.y >> kTagShift == kTagCanon ||
+                         v.z >> kTagShift == kTagCanon || v.w >> kTagShift == kTagCanon;
+        if (!any) continue;
+        v.x = rank(v.x);
+        v.y = rank(v.y);
+        v.z = rank(v.z);
+        v.w = rank(v.w);
+        t4[i] = v;
     }
 }
 
-template <int K, int NJ>
+// every other entry: its local minimum's (final since rank_kernel)
+__global__ void assign_kernel(uint32_t *table, uint32_t ncodes)
+{
+    uint4 *t4 = reinterpret_cast<uint4 *>(table);
+    auto end = [&](uint32_t x) { return x >> kTagShift == kTagEnd ? table[x & kTagMask] : x; };
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < ncodes / 4; i += stride) {
+        uint4 v = t4[i];
+        v.x = end(v.x);
+        v.y = end(v.y);
+        v.z = end(v.z);
+        v.w = end(v.w);
+        t4[i] = v;
+    }
+}
+
+template <int K>
 static int launch_canon(uint32_t *table, uint32_t *repbits, uint64_t ncodes, int steps,
                         hipStream_t stream)
 {
-    const uint64_t waves = ncodes / (kWave * NJ);
-    const uint64_t blocks = (waves * kWave + 255) / 256;
-    hipLaunchKernelGGL((canon_kernel<K, NJ>), dim3((unsigned)blocks), dim3(256), 0, stream, table,
-                       repbits, ncodes, steps);
+    constexpr uint64_t kTile = (uint64_t)kCanonThreads * kCanonRounds;
+    hipLaunchKernelGGL((canon_kernel<K>), dim3((unsigned)((ncodes + kTile - 1) / kTile)),
+                       dim3(kCanonThreads), 0, stream, table, repbits, (uint32_t)ncodes, steps);
     MK_HIP(hipGetLastError());
     return MK_OK;
 }
@@ -309,11 +398,12 @@ int build_table(Table *t, hipStream_t stream)
     TRYHIP(hipEventRecord(e0, stream));
 
     const int steps = (int)seq.size();
+    TRY(fill_u32(repbits, 0, nwords, stream));
     switch (k) {
-    case 3: TRY((launch_canon<3, 1>(t->d_table, repbits, ncodes, steps, stream))); break;
-    case 4: TRY((launch_canon<4, 32>(t->d_table, repbits, ncodes, steps, stream))); break;
-    case 5: TRY((launch_canon<5, 32>(t->d_table, repbits, ncodes, steps, stream))); break;
-    case 6: TRY((launch_canon<6, 32>(t->d_table, repbits, ncodes, steps, stream))); break;
+    case 3: TRY(launch_canon<3>(t->d_table, repbits, ncodes, steps, stream)); break;
+    case 4: TRY(launch_canon<4>(t->d_table, repbits, ncodes, steps, stream)); break;
+    case 5: TRY(launch_canon<5>(t->d_table, repbits, ncodes, steps, stream)); break;
+    case 6: TRY(launch_canon<6>(t->d_table, repbits, ncodes, steps, stream)); break;
     default: cleanup(); return fail(MK_ERANGE, "k=%d outside 3..6", k);
     }
     TRY(scan_u32(repbits, rankbase, nwords, 1, d_total, tmp, stream));
@@ -329,9 +419,12 @@ int build_table(Table *t, hipStream_t stream)
     hipLaunchKernelGGL(classlist_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0,
                        stream, repbits, rankbase, nwords, t->d_classes);
     TRYHIP(hipGetLastError());
-    const uint64_t ablocks = std::min<uint64_t>((ncodes + 255) / 256, 1u << 20);
+    const uint64_t ablocks = std::min<uint64_t>((ncodes / 4 + 255) / 256, 1u << 16);
+    hipLaunchKernelGGL(rank_kernel, dim3((unsigned)ablocks), dim3(256), 0, stream, t->d_table,
+                       repbits, rankbase, (uint32_t)ncodes);
+    TRYHIP(hipGetLastError());
     hipLaunchKernelGGL(assign_kernel, dim3((unsigned)ablocks), dim3(256), 0, stream, t->d_table,
-                       repbits, rankbase, ncodes);
+                       (uint32_t)ncodes);
     TRYHIP(hipGetLastError());
     TRYHIP(hipMalloc(&t->d_core_mult, (size_t)num));
     TRY(launch_core_mult(k, t->d_classes, num, t->d_core_mult, stream));
