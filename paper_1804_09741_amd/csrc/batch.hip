@@ -2,10 +2,12 @@
 //
 // A batch holds the device workspace of ng graphs counted with one class
 // table, and runs the whole path as one stream sequence:
-//   reset counters and histograms (fill kernels) -> typed adjacency (Section
-//   2's A/B/C lists) -> work-unit plan -> persistent enumeration kernel
-// with no host synchronisation in between.  The ten small preparation
-// kernels are captured once as a hipGraph and replayed; the enumeration
+//   reset counters, bit matrices and histograms (one clearing kernel) ->
+//   typed adjacency (Section 2's A/B/C lists) -> work-unit plan -> persistent
+//   enumeration kernel
+// with no host synchronisation in between.  The small preparation kernels
+// (seven on bit matrices: 0.05 ms for one graph of n = 2000 at k = 4, 0.19
+// with twelve) are captured once as a hipGraph and replayed; the enumeration
 // kernel follows as one launch between two HIP events (its timing).  Every
 // graph of the batch shares one queue and one launch; histograms are
 // [ng][num_classes] uint64.
@@ -218,36 +220,33 @@ static EnumConfig enum_config(const mk_batch *b)
 }
 
 // typed adjacency of every graph (from bit matrices or by sorting lists)
+// (the bit matrices are clear)
 static int batch_enqueue_typed(mk_batch *b, hipStream_t stream)
 {
     if (b->adjacency == MK_ADJ_LISTS)
         return launch_typed_lists(b->d_graphs, b->ng, b->max_n, b->max_m, b->total_n, b->total_m,
                                   2 * b->seg_cap, b->d_ws, b->d_counters, stream);
-    return launch_typed_csr(b->d_graphs, b->ng, b->max_n, b->max_m, b->bits_words, b->d_ws,
-                            b->d_counters, stream);
+    return launch_typed_csr(b->d_graphs, b->ng, b->max_n, b->max_m, b->d_counters, stream);
 }
 
 // enqueue the preparation part of one pass on stream: counters and
 // histograms cleared, typed adjacency, work-unit plan (captured as a
-// hipGraph).  (Clearing the histograms from extra workgroups of the
+// hipGraph); a planned threshold is the sizing plan's, so d_slot_off keeps
+// that plan's offsets.  (Clearing the histograms from extra workgroups of the
 // latency-bound plan passes instead was measured slower: the streaming
-// stores raise the latency of the passes' dependent loads, 0.24 ms for the
-// k = 6 batch's preparation either way.)
+// stores raise the latency of the passes' dependent loads.)
 static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t stream)
 {
-    int rc = fill_u32(b->d_counters, 0, kNumCounters, stream);
+    ClearRange bins{nullptr, 0};
+    if (hist && b->d_hist_work) bins = {b->d_hist_work, 2 * b->layout.words()};
+    else if (hist) bins = {hist, 2 * (size_t)b->ng * b->table->num_classes};
+    int rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, bins, stream);
     if (rc) return rc;
-    if (hist) {
-        const uint32_t nc = b->table->num_classes;
-        rc = b->d_hist_work ? fill_u32(b->d_hist_work, 0, 2 * b->layout.words(), stream)
-                            : fill_u32(hist, 0, (size_t)b->ng * nc * 2, stream);
-        if (rc) return rc;
-    }
     rc = batch_enqueue_typed(b, stream);
     if (rc) return rc;
     return launch_plan(b->plan_k, b->d_graphs, b->ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                        b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                       b->d_units, b->unit_cap, b->opts.split_threshold, b->spec_threshold,
+                       b->d_units, b->unit_cap, b->opts.split_threshold, b->spec_threshold, true,
                        (uint32_t)b->max_grid, (uint32_t)std::max(b->opts.units_per_wave, 0),
                        b->d_counters, stream);
 }
@@ -486,7 +485,8 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     BAIL_HIP(hipMalloc(&b->d_slot_est, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
     BAIL_HIP(hipMalloc(&b->d_slot_vi, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
     BAIL_HIP(hipMalloc(&b->d_slot_l2, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_scan_tmp, sizeof(uint32_t) * scan_tmp_words(slots)));
+    BAIL_HIP(hipMalloc(&b->d_scan_tmp,
+                       sizeof(uint32_t) * plan_tmp_words(ng, b->max_nnz, (uint32_t)slots)));
     BAIL_HIP(hipMalloc(&b->d_counters, sizeof(uint32_t) * kNumCounters));
     BAIL_HIP(hipMalloc(&b->d_unit_begin, sizeof(uint32_t) * ((size_t)ng + 1)));
     for (hipEvent_t &e : b->ev) BAIL_HIP(hipEventCreate(&e));
@@ -512,12 +512,13 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     }
 
     // sizing pass: typed adjacency + unit counts only
-    rc = fill_u32(b->d_counters, 0, kNumCounters, ctx->stream);
+    rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
+                      ctx->stream);
     if (!rc) rc = batch_enqueue_typed(b, ctx->stream);
     if (!rc)
         rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                          b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                         nullptr, 0, b->opts.split_threshold, 0, (uint32_t)b->max_grid,
+                         nullptr, 0, b->opts.split_threshold, 0, false, (uint32_t)b->max_grid,
                          (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
                          ctx->stream);
     if (rc) return bail(rc);
@@ -721,7 +722,7 @@ uint64_t batch_device_bytes(const mk_batch *b)
     uint64_t words = b->adjacency == MK_ADJ_BITS ? b->bits_words
                                                  : list_ws_words(b->total_n, b->total_m);
     for (const mk_graph *g : b->graphs) words += (uint64_t)g->n + 1 + (uint64_t)g->nnz_u;
-    return 4 * words + 20ull * b->total_slots + 4 * scan_tmp_words(b->total_slots) +
+    return 4 * words + 20ull * b->total_slots + 4 * plan_tmp_words(b->ng, b->max_nnz, b->total_slots) +
            16ull * b->unit_cap + 8ull * b->ng * b->table->num_classes + 4ull * (b->ng + 1) +
            8ull * b->layout.words() +
            sizeof(DevGraph) * b->graphs.size() + 4 * kNumCounters +

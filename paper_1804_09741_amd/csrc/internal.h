@@ -120,12 +120,11 @@ enum Counter : int {
     kErrors = 2,      // device-side consistency failures (must stay 0)
     kSplitPairs = 3,  // (root, first neighbour) pairs split at the second level
     kAdjOverflow = 4, // typed adjacency larger than reserved (must stay 0)
-    kSpecSplitPairs = 5,  // kSplitPairs at the floor threshold (estimate pass)
-    kEstTotal = 6,    // words 6-7: u64 estimated total cost (planner)
     kPlanThreshold = 8,  // words 8-9: u64 split threshold of the last count pass
     kQueueHeads = 16, // kQueues heads, one per XCD, kHeadStride words apart
     kHeavyHeads = 16 + 8 * 16,  // the first sweep's kQueues heads, likewise
-    kNumCounters = 16 + 2 * 8 * 16,
+    kPlanSums = 16 + 2 * 8 * 16,  // the estimate pass's sums: a line per XCD (plan.hip)
+    kNumCounters = kPlanSums + 8 * 32,
 };
 constexpr int kQueues = 8;       // one queue per XCD of the MI355X
 constexpr int kHeadStride = 16;  // 64 bytes: one cache line per head
@@ -154,19 +153,28 @@ struct Ctx {
 // popcount != 0) into out; the grand total goes to *d_total.  tmp must hold
 // scan_tmp_words(n) words.  Everything is on `stream`, asynchronous.
 size_t scan_tmp_words(size_t n);
+// words of launch_plan's scan workspace
+size_t plan_tmp_words(int ng, int64_t max_nnz, uint32_t total_slots);
 int scan_u32(const uint32_t *in, uint32_t *out, size_t n, int popcount, uint32_t *d_total,
              uint32_t *tmp, hipStream_t stream);
 
 // Fill n 32-bit words with value (a kernel, so it can live in a captured
 // hipGraph).
 int fill_u32(void *dst, uint32_t value, size_t n, hipStream_t stream);
+// Zero up to three ranges of 32-bit words in one launch.
+struct ClearRange {
+    void *p;
+    size_t words;
+};
+int clear_ranges(ClearRange a, ClearRange b, ClearRange c, hipStream_t stream);
 
 // Class table build for k (3..6).  Allocates and fills t->d_table,
 // t->d_classes, t->num_classes.  Synchronous.
 int build_table(Table *t, hipStream_t stream);
 
-// Typed symmetric adjacency of every graph of a batch (bit matrices
-// zeroed, arcs set, degrees counted and scanned, lists written).
+// Typed symmetric adjacency of every graph of a batch (arcs set in the bit
+// matrices, which the caller has zeroed, degrees counted and scanned, lists
+// written).
 // Typed adjacency without bit matrices: raw out/in entries per vertex,
 // sorted and merged per vertex.  `lists` holds list_ws_words() words.
 uint64_t list_ws_words(uint64_t total_n, uint64_t total_m);
@@ -174,8 +182,7 @@ int launch_typed_lists(const DevGraph *d_graphs, int ng, int max_n, int64_t max_
                        uint64_t total_n, uint64_t total_m, int max_raw, uint32_t *lists,
                        uint32_t *counters, hipStream_t stream);
 int launch_typed_csr(const DevGraph *d_graphs, int ng, int max_n, int64_t max_m,
-                     uint64_t bits_words_total, uint32_t *bits_base, uint32_t *counters,
-                     hipStream_t stream);
+                     uint32_t *counters, hipStream_t stream);
 
 // Work-unit planner: cost estimate, counts per slot, scan, emit (units ==
 // nullptr: sizing only).  k = 2 plans one unit per vertex with a neighbour.
@@ -186,12 +193,15 @@ int launch_typed_csr(const DevGraph *d_graphs, int ng, int max_n, int64_t max_m,
 // by the estimate pass, read by the count and emit passes).
 // spec_threshold (0: the floor): the threshold at which the estimate pass
 // also counts each slot's units; the count pass keeps those counts when the
-// threshold comes out equal to it (a batch passes the one its sizing plan
-// found, read from counters[kPlanThreshold]).
+// threshold comes out equal to it.  sized: the threshold is known to come out
+// as spec_threshold (a batch passes the one its sizing plan of the same
+// graphs found, read from counters[kPlanThreshold]): there is no count pass,
+// and the emit pass finds its offsets itself where the estimate's workgroups
+// are few enough (a threshold that differs is a device error).
 int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                 uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                 uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                uint64_t split_threshold, uint64_t spec_threshold, uint32_t waves,
+                uint64_t split_threshold, uint64_t spec_threshold, bool sized, uint32_t waves,
                 uint32_t units_per_wave, uint32_t *counters, hipStream_t stream);
 
 // Enumeration + code + lookup + histogram over the queued units.

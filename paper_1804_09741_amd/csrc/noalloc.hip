@@ -171,16 +171,14 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
 
     hipLaunchKernelGGL(put_devgraph, dim3(1), dim3(1), 0, s, dg, d);
     MK_HIP(hipGetLastError());
-    rc = fill_u32(counters, 0, kNumCounters, s);
-    if (!rc)
-        rc = layout.graph_words ? fill_u32(count_to, 0, 2 * layout.words(), s)
-                                : fill_u32(hist, 0, (size_t)nc * 2, s);
-    if (!rc) rc = launch_typed_csr(dg, 1, g->n, g->m, 2 * n * w, d.bits_out, counters, s);
+    rc = clear_ranges({counters, kNumCounters}, {d.bits_out, 2 * n * w},
+                      {count_to, 2 * (layout.graph_words ? layout.words() : (size_t)nc)}, s);
+    if (!rc) rc = launch_typed_csr(dg, 1, g->n, g->m, counters, s);
     if (!rc)
         rc = launch_plan(k, dg, 1, (int64_t)nnz, (uint32_t)nnz, slots, slots + nnz, slots + 2 * nnz,
                          slots + 3 * nnz, slots + 4 * nnz, reinterpret_cast<uint32_t *>(base + o_scan),
                          units, (uint32_t)std::min<uint64_t>(unit_cap, 0xFFFFFFFFull),
-                         default_split_floor(k), 0, (uint32_t)grid, 0u, counters, s);
+                         default_split_floor(k), 0, false, (uint32_t)grid, 0u, counters, s);
     EnumConfig cfg{};
     cfg.max_n = g->n;
     cfg.seg_cap = seg_cap;

@@ -13,9 +13,11 @@
 // shared by many wavefronts while sparse parts stay one unit per node.
 //
 // Slots are the entries of the typed adjacency lists (one per (v, u) with
-// u in delta(v)); a slot with u > v is a first-level node.  Pass one counts
-// the units of every slot, a scan gives offsets, pass two writes the units.
-// The order is graph by graph, root by root.
+// u in delta(v)); a slot with u > v is a first-level node.  The estimate pass
+// adds up the nodes' costs and counts units; where the split threshold that
+// follows from the costs is a new one, a second pass counts again and a scan
+// gives offsets; the last pass writes the units.  The order is graph by
+// graph, root by root.
 #include <algorithm>
 
 #include "internal.h"
@@ -23,7 +25,44 @@
 
 namespace mk {
 
-constexpr int kPlanThreads = 256;
+// A workgroup takes kPlanSlots slots, a thread each of its first wave; its
+// other waves join in the walks, where there are any (K > 3): 1,024 threads,
+// so that every node has a team of lanes of its own, where two such
+// workgroups fit each CU (94 workgroups, one graph of n = 1000 at k = 5: the
+// preparation 104 us, 176 with 256 threads), else 256 (9,500 workgroups, that
+// graph and 100 random versions: 338 us, 549 with 1,024).
+constexpr int kPlanSlots = kWave;
+constexpr int kPlanThreads = 256, kPlanThreadsFew = 1024;
+constexpr uint64_t kPlanFewBlocks = 512;
+
+static int plan_threads(int k, dim3 grid)
+{
+    if (k <= 3) return kPlanSlots;
+    return (uint64_t)grid.x * grid.y <= kPlanFewBlocks ? kPlanThreadsFew : kPlanThreads;
+}
+
+// The estimate pass's sums at counters[kPlanSums], one line per XCD
+// (workgroup b runs on XCD b % kQueues; an add to a line that all XCDs share
+// takes its turn at 10 ns): the estimated cost (u64), the split nodes, and
+// the units of every kSumBlocks = 64 workgroups of the XCD, in a window of
+// kQueues * kSumBlocks workgroups.
+constexpr int kSumLine = 32, kSumSplit = 2, kSumUnits = 4;
+constexpr uint32_t kSumWindow = 64 * kQueues;
+constexpr uint32_t kSumWindows = kSumLine - kSumUnits;
+
+__device__ __forceinline__ uint32_t plan_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
+__device__ __forceinline__ uint32_t *sum_line(uint32_t *counters, uint32_t xcd)
+{
+    return counters + kPlanSums + xcd * kSumLine;
+}
+
+__device__ __forceinline__ uint32_t spec_split_pairs(uint32_t *counters)
+{
+    uint32_t n = 0;
+    for (int x = 0; x < kQueues; ++x) n += sum_line(counters, x)[kSumSplit];
+    return n;
+}
 
 __device__ __forceinline__ uint64_t choose_small(int64_t n, int r)
 {
@@ -123,11 +162,14 @@ __device__ __forceinline__ uint64_t units_per_wave(const PlanGraph &g)
 }
 
 template <int K>
-__device__ __forceinline__ uint64_t effective_threshold(const PlanGraph &g,
-                                                        const uint32_t *counters, uint64_t floor_t,
-                                                        uint32_t waves, uint32_t upw)
+__device__ __forceinline__ uint64_t effective_threshold(const PlanGraph &g, uint32_t *counters,
+                                                        uint64_t floor_t, uint32_t waves,
+                                                        uint32_t upw)
 {
-    const uint64_t total = *reinterpret_cast<const unsigned long long *>(counters + kEstTotal);
+    uint64_t total = 0;
+#pragma unroll
+    for (int x = 0; x < kQueues; ++x)
+        total += *reinterpret_cast<const unsigned long long *>(sum_line(counters, x));
     const uint64_t per_wave = upw ? (uint64_t)upw : units_per_wave<K>(g);
     const uint64_t adaptive = total / ((uint64_t)waves * per_wave + 1);
     return adaptive > floor_t ? adaptive : floor_t;
@@ -140,61 +182,6 @@ __device__ __forceinline__ uint64_t effective_threshold(const PlanGraph &g,
 constexpr int kViShift = 20;
 constexpr uint32_t kViMask = (1u << kViShift) - 1u;
 constexpr uint32_t kNoNode = 0xFFFFFFFFu;
-
-// greedy ranges over the children of (v, w_i): calls put(r, j0 | j1 << 16,
-// estimated cost) for every range when EMIT, returns the number of ranges
-template <int K, bool EMIT, typename Put>
-__device__ __forceinline__ uint32_t split_children(const PlanGraph &g, int v, int first, int r1,
-                                                   int i, int y, int L2, uint64_t threshold,
-                                                   uint64_t *est, Put put)
-{
-    uint32_t cnt = 0;
-    int j = 0, j0 = 0;
-    uint64_t acc = 0;
-    auto child = [&](int dx) {
-        const uint64_t cj = choose_small(L2 - j - 1 + dx - 1, K - 3) + 1;
-        *est += cj;
-        if (j > j0 && acc + cj > threshold) {
-            if (EMIT) put(cnt, (uint32_t)j0 | ((uint32_t)j << 16), acc);
-            ++cnt;
-            j0 = j;
-            acc = 0;
-        }
-        acc += cj;
-        ++j;
-    };
-    // unrolled: the iterations' loads do not depend on one another
-#pragma unroll 4
-    for (int t = first + i + 1; t < r1; ++t) {
-        const int x = (int)(g.uadj[t] >> 2);
-        child(g.urow[x + 1] - g.urow[x]);
-    }
-    const int y0 = g.urow[y], y1 = g.urow[y + 1];
-#pragma unroll 4
-    for (int t = y0; t < y1; ++t) {
-        const int x = (int)(g.uadj[t] >> 2);
-        const int dx = g.urow[x + 1] - g.urow[x];
-        if (exclusive_above(g, v, x)) child(dx);
-    }
-    if (L2 > j0) {
-        if (EMIT) put(cnt, (uint32_t)j0 | ((uint32_t)L2 << 16), acc);
-        ++cnt;
-    }
-    return cnt;
-}
-
-// extension length L2 of the node (v, w_i = y)
-__device__ __forceinline__ int ext_len(const PlanGraph &g, int v, int ext_v, int i, int y)
-{
-    int fresh = 0;
-    const int y0 = g.urow[y], y1 = g.urow[y + 1];
-#pragma unroll 8
-    for (int t = y0; t < y1; ++t) {
-        const int x = (int)(g.uadj[t] >> 2);
-        fresh += (int)exclusive_above(g, v, x);
-    }
-    return ext_v - i - 1 + fresh;
-}
 
 #ifndef MK_HEAVY_SHIFT
 #define MK_HEAVY_SHIFT 1  // k = 5 core kernel 17.5 ms with 1, 17.8 with 2, 18.8 with 0
@@ -214,14 +201,150 @@ __device__ __forceinline__ bool node_split(uint32_t sest, uint64_t threshold)
     return K > 3 && (sest == 0xFFFFFFFFu || sest > threshold);
 }
 
-// One workgroup per (graph, 256 slots): blockIdx.y is the graph.  The
-// estimate pass also counts each slot's units at the threshold spec_t (its
-// walk over the children is the one the count pass would repeat); when the
-// threshold comes out equal to spec_t -- the floor, or for a batch the
-// threshold its sizing plan found, since a batch plans the same graphs
-// every pass -- the count pass keeps those counts and returns at once.
+// The walk over a node's children: bound by the latency of the chain from a
+// list entry to its vertex's degree and bits.  A team of 16 lanes takes 16
+// children at a time, with the next 16 entries on their way, so that lists
+// are read in order and a wave waits for the longest of four nodes, not of
+// 64.  (Estimate and emit passes with a thread a node, 101 graphs of n = 1000
+// at k = 5: 277 + 125 us, one of them by enumeration 103 + 91, one of n = 700
+// at k = 6 37 + 31; so 137 + 85, 39 + 46 and 14 + 16.  Teams of 32: the same.)
+constexpr int kTeam = 16;
+
+__device__ __forceinline__ uint32_t team_ballot(bool p)
+{
+    return (uint32_t)(__ballot(p) >> (threadIdx.x % kWave / kTeam * kTeam)) & 0xFFFFu;
+}
+
+// inclusive prefix sum over the team
+__device__ __forceinline__ uint64_t team_incl_sum(uint64_t x)
+{
+    const int sub = threadIdx.x % kTeam;
+#pragma unroll
+    for (int d = 1; d < kTeam; d <<= 1) {
+        const unsigned long long o = __shfl_up((unsigned long long)x, d, kTeam);
+        if (sub >= d) x += o;
+    }
+    return x;
+}
+
+// A first-level node (v, w_i = y): E_v[i+1:] is uadj[t0, r1).
+struct PlanNode {
+    int v, i, y, t0, r1;
+};
+
+// its extension length L2
+__device__ __forceinline__ int team_ext_len(const PlanGraph &g, const PlanNode &n)
+{
+    int len = n.r1 - n.t0;
+    const int y0 = g.urow[n.y], y1 = g.urow[n.y + 1];
+    int at = y0 + (int)(threadIdx.x % kTeam);
+    uint32_t next = at < y1 ? g.uadj[at] : 0u;
+    for (int t = y0; t < y1; t += kTeam, at += kTeam) {
+        const int x = (int)(next >> 2);
+        if (at + kTeam < y1) next = g.uadj[at + kTeam];
+        const bool ex = at < y1 && exclusive_above(g, n.v, x);
+        len += __popc(team_ballot(ex));
+    }
+    return len;
+}
+
+// Greedy ranges over its children: calls put(r, j0 | j1 << 16, estimated
+// cost) for every range on the team's first lane when EMIT, returns the
+// number of ranges; *est gets the sum of the costs.
+template <int K, bool EMIT, typename Put>
+__device__ __forceinline__ uint32_t team_split(const PlanGraph &g, const PlanNode &n, int L2,
+                                               uint64_t threshold, uint64_t *est, Put put)
+{
+    const int sub = threadIdx.x % kTeam;
+    uint32_t cnt = 0;
+    int jb = 0, j0 = 0;             // children taken; first child of the open range
+    uint64_t acc = 0, total = 0;    // cost of the open range; of all children
+    const int y0 = g.urow[n.y], y1 = g.urow[n.y + 1];
+    const int first = n.r1 - n.t0, all = first + (y1 - y0);
+    // the entries of E_v[i+1:], then those of y's list
+    const auto entry = [&](int a) {
+        return a < all ? g.uadj[a < first ? n.t0 + a : y0 + (a - first)] : 0u;
+    };
+    uint32_t next = entry(sub);
+    for (int b = 0; b < all; b += kTeam) {
+        const int a = b + sub;
+        const int x = (int)(next >> 2);
+        next = entry(a + kTeam);
+        bool child = a < all;
+        int dx = 0;
+        if (child) {
+            dx = g.urow[x + 1] - g.urow[x];
+            child = exclusive_above(g, n.v, x) || a < first;
+        }
+        const uint32_t m = team_ballot(child);
+        const int j = jb + __popc(m & ((1u << sub) - 1u));
+        const uint64_t c = child ? choose_small(L2 - j - 1 + dx - 1, K - 3) + 1 : 0;
+        const uint64_t incl = team_incl_sum(c);
+        uint64_t closed = 0;  // cost of these children in ranges that are closed
+        for (;;) {
+            const uint32_t over = team_ballot(child && j > j0 && acc + (incl - closed) > threshold);
+            if (!over) break;
+            const int l = __builtin_ctz(over);
+            const int jc = __shfl(j, l, kTeam);
+            const uint64_t before = __shfl((unsigned long long)(incl - c), l, kTeam);
+            if (EMIT && sub == 0) put(cnt, (uint32_t)j0 | ((uint32_t)jc << 16), acc + (before - closed));
+            ++cnt;
+            j0 = jc;
+            acc = 0;
+            closed = before;
+        }
+        const uint64_t sum = __shfl((unsigned long long)incl, kTeam - 1, kTeam);
+        acc += sum - closed;
+        total += sum;
+        jb += __popc(m);
+    }
+    if (L2 > j0) {
+        if (EMIT && sub == 0) put(cnt, (uint32_t)j0 | ((uint32_t)L2 << 16), acc);
+        ++cnt;
+    }
+    *est = total;
+    return cnt;
+}
+
+// First unit of a slot (cnt units, threads 0..kPlanSlots-1) in a sized plan:
+// the units of all workgroups before this one and of the slots before in the
+// workgroup.  The last workgroup writes the total.  (In place of the count
+// pass and a scan over all slots: four launches, 18 us for one graph.)
+__device__ __forceinline__ uint32_t sized_offset(uint32_t cnt, const uint32_t *block_sums,
+                                                 uint32_t *counters)
+{
+    __shared__ uint32_t before;
+    const uint32_t at = plan_block(), w = at / kSumWindow;
+    if (threadIdx.x == 0) before = 0;
+    __syncthreads();
+    uint32_t b = 0;
+    for (uint32_t i = threadIdx.x; i < w * kQueues; i += blockDim.x)
+        b += sum_line(counters, i % kQueues)[kSumUnits + i / kQueues];
+    for (uint32_t i = w * kSumWindow + threadIdx.x; i < at; i += blockDim.x)
+        b += block_sums[i];
+    if (b) atomicAdd(&before, b);
+    __syncthreads();
+    uint32_t incl = cnt;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(incl, d, kWave);
+        if ((int)threadIdx.x % kWave >= d) incl += o;
+    }
+    if (threadIdx.x == kPlanSlots - 1 && at == gridDim.x * gridDim.y - 1u)
+        counters[kNumUnits] = before + incl;
+    return before + incl - cnt;
+}
+
+// One workgroup per (graph, kPlanSlots slots): blockIdx.y is the graph.  A
+// thread a slot finds its node; teams walk the nodes' children; the slots'
+// threads write.  The estimate pass also counts each slot's units at the
+// threshold spec_t (its walk over the children is the one the count pass
+// would repeat); when the threshold comes out equal to spec_t -- the floor,
+// or for a batch the threshold its sizing plan found, since a batch plans the
+// same graphs every pass -- the count pass keeps those counts and returns at
+// once, and a sized plan goes without it.
 template <int K, int PASS>
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(const DevGraph *graphs,
+__global__ __launch_bounds__(kPlanThreadsFew) void plan_kernel(const DevGraph *graphs,
                                                             uint32_t *slot_cnt,
                                                             const uint32_t *slot_off,
                                                             uint32_t *slot_est, uint32_t *slot_vi,
@@ -229,137 +352,209 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(const DevGraph *grap
                                                             int4 *units, uint32_t unit_cap,
                                                             uint64_t floor_t, uint64_t spec_t,
                                                             uint32_t waves,
-                                                            uint32_t upw, uint32_t *counters)
+                                                            uint32_t upw, uint32_t *counters,
+                                                            uint32_t *block_sums)
 {
+    __shared__ PlanNode node[kPlanSlots];      // nodes to walk, in list order
+    __shared__ int node_slot[kPlanSlots];      //   their slots' threads
+    __shared__ uint32_t node_arg[kPlanSlots];  //   emit: first unit
+    __shared__ uint64_t got_est[kPlanSlots];   // by slot thread
+    __shared__ uint32_t got_cnt[kPlanSlots];
+    __shared__ int got_l2[kPlanSlots];
+    __shared__ int nodes;
     const int gi = blockIdx.y;
     const PlanGraph g = plan_graph(graphs[gi]);
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    uint64_t est = 0;  // kEstimate: this slot's estimated cost
-    const bool live = g.n > 0 && e < min(g.urow[g.n], (int)g.nnz_cap);
+    const int tid = threadIdx.x;
+    const int e = blockIdx.x * kPlanSlots + tid;
+    const bool lead = gi == 0 && blockIdx.x == 0 && tid == 0;
+    const bool live = tid < kPlanSlots && g.n > 0 && e < min(g.urow[g.n], (int)g.nnz_cap);
+    const uint32_t slot = g.slot_base + (uint32_t)e;
     const uint64_t threshold = PASS == kEstimate ? ~0ull : effective_threshold<K>(g, counters, floor_t, waves, upw);
     if (PASS == kCount) {
-        if (gi == 0 && e == 0)
-            *reinterpret_cast<unsigned long long *>(counters + kPlanThreshold) = threshold;
+        if (lead) *reinterpret_cast<unsigned long long *>(counters + kPlanThreshold) = threshold;
         if (threshold == spec_t) {
-            if (gi == 0 && e == 0) counters[kSplitPairs] = counters[kSpecSplitPairs];
+            if (lead) counters[kSplitPairs] = spec_split_pairs(counters);
             return;
         }
     }
+    uint32_t first_unit = 0;  // emit: the slot's
+    if (PASS == kEmit) {
+        if (block_sums) {
+            first_unit = sized_offset(live ? slot_cnt[slot] : 0u, block_sums, counters);
+            if (threshold != spec_t) {
+                if (lead) atomicOr(&counters[kErrors], 1u);
+                return;
+            }
+            if (lead) {
+                *reinterpret_cast<unsigned long long *>(counters + kPlanThreshold) = threshold;
+                counters[kSplitPairs] = spec_split_pairs(counters);
+            }
+        } else if (live) {
+            first_unit = slot_off[slot];
+        }
+    }
+    if (tid == 0) nodes = 0;
+    __syncthreads();
+
+    // the slots' nodes
+    uint32_t vi = kNoNode, sest = 0;
+    bool walk = false;
     if (live) {
-        const uint32_t slot = g.slot_base + (uint32_t)e;
-        const int y = (int)(g.uadj[e] >> 2);
+        PlanNode n;
+        n.y = (int)(g.uadj[e] >> 2);
         if (PASS == kEstimate) {
-            // the full walk: owner, position, extension length, child costs
-            const int v = owner_of(g.urow, g.n, e);
-            uint32_t vi = kNoNode, ranges = 0;
+            n.v = owner_of(g.urow, g.n, e);
             if constexpr (K == 2) {
                 // one unit per vertex, on its first list entry
-                if (e == g.urow[v]) {
-                    est = 1;
-                    vi = (uint32_t)v;
-                }
-            } else if (y > v) {
-                const int r1 = g.urow[v + 1];
-                const int first = first_above(g.uadj, g.urow[v], r1, v);
-                const int i = e - first;
-                const int L2 = ext_len(g, v, r1 - first, i, y);
-                slot_l2[slot] = (uint32_t)L2;
-                if constexpr (K == 3) est = (uint64_t)L2 + 1;
-                else ranges = split_children<K, false>(g, v, first, r1, i, y, L2, spec_t, &est,
-                                                       [](uint32_t, uint32_t, uint64_t) {});
-                vi = (uint32_t)v | ((uint32_t)i << kViShift);
+                if (e == g.urow[n.v]) vi = (uint32_t)n.v;
+            } else if (n.y > n.v) {
+                n.r1 = g.urow[n.v + 1];
+                vi = (uint32_t)n.v |
+                     ((uint32_t)(e - first_above(g.uadj, g.urow[n.v], n.r1, n.v)) << kViShift);
+                walk = K > 3;  // smaller sets' nodes are never cut
             }
-            slot_vi[slot] = vi;
-            const uint32_t sest = est > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)est;
-            slot_est[slot] = sest;
-            uint32_t cnt = 0;  // units at the threshold spec_t
+        } else {
+            vi = slot_vi[slot];
+            sest = slot_est[slot];
             if (vi != kNoNode) {
-                cnt = node_split<K>(sest, spec_t) ? ranges : ((K > 3 && sest == 0u) ? 0u : 1u);
-                if (cnt > 1) atomicAdd(&counters[kSpecSplitPairs], 1u);
+                n.v = (int)(vi & kViMask);
+                n.r1 = g.urow[n.v + 1];
+                walk = node_split<K>(sest, threshold);
+            }
+        }
+        if (walk) {
+            n.i = (int)(vi >> kViShift);
+            n.t0 = e + 1;
+            const int at = atomicAdd(&nodes, 1);
+            node[at] = n;
+            node_slot[at] = tid;
+            node_arg[at] = first_unit;
+            if (PASS != kEstimate) got_l2[tid] = (int)slot_l2[slot];
+        }
+    }
+    __syncthreads();
+
+    // their children
+    if constexpr (K > 3) {
+        for (int q = tid / kTeam; q < nodes; q += (int)blockDim.x / kTeam) {
+            const PlanNode n = node[q];
+            const int of = node_slot[q];
+            const uint32_t base = node_arg[q];
+            auto put = [&](uint32_t r, uint32_t w, uint64_t c) {
+                const uint32_t idx = base + r;
+                if (idx < unit_cap)
+                    units[idx] = make_int4(unit_x(gi, c, threshold), n.v, n.i, (int)w);
+                else
+                    atomicOr(&counters[kErrors], 1u);
+            };
+            const int L2 = PASS == kEstimate ? team_ext_len(g, n) : got_l2[of];
+            uint64_t est = 0;
+            const uint32_t cnt = team_split<K, PASS == kEmit>(
+                g, n, L2, PASS == kEstimate ? spec_t : threshold, &est, put);
+            if (tid % kTeam == 0) {
+                got_est[of] = est;
+                got_cnt[of] = cnt;
+                got_l2[of] = L2;
+            }
+        }
+        __syncthreads();
+    }
+
+    if (PASS == kEstimate) {
+        uint64_t est = 0;
+        uint32_t cnt = 0;  // units at the threshold spec_t
+        if (live) {
+            est = walk ? got_est[tid] : (vi != kNoNode ? 1u : 0u);
+            if (walk) slot_l2[slot] = (uint32_t)got_l2[tid];
+            sest = est > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)est;
+            slot_vi[slot] = vi;
+            slot_est[slot] = sest;
+            if (vi != kNoNode) {
+                // a node without children (estimate 0) has no unit
+                cnt = node_split<K>(sest, spec_t) ? got_cnt[tid] : ((K > 3 && sest == 0u) ? 0u : 1u);
             }
             slot_cnt[slot] = cnt;
-        } else {
-            const uint32_t vi = slot_vi[slot];
-            const uint32_t sest = slot_est[slot];
-            uint32_t cnt = 0;
-            if (vi != kNoNode) {
-                const int v = (int)(vi & kViMask), i = (int)(vi >> kViShift);
-                const bool split = node_split<K>(sest, threshold);
-                if (K <= 3) {
-                    cnt = 1;
-                } else if (sest <= 1 && !split) {
-                    // no children below (v, w_i): L2 == 0 gives est 0
-                    cnt = sest == 0 ? 0 : 1;
-                } else if (!split) {
-                    cnt = 1;
-                } else if constexpr (K > 3) {
-                    const int r1 = g.urow[v + 1];
-                    const int first = e - i;
-                    const int L2 = (int)slot_l2[slot];  // from the estimate pass
-                    uint32_t base = 0;
-                    if (PASS == kEmit) base = slot_off[slot];
-                    auto put = [&](uint32_t r, uint32_t w, uint64_t c) {
-                        const uint32_t idx = base + r;
-                        if (idx < unit_cap) units[idx] = make_int4(unit_x(gi, c, threshold), v, i, (int)w);
-                        else atomicOr(&counters[kErrors], 1u);
-                    };
-                    uint64_t dummy = 0;
-                    cnt = PASS == kEmit
-                              ? split_children<K, true>(g, v, first, r1, i, y, L2, threshold, &dummy, put)
-                              : split_children<K, false>(g, v, first, r1, i, y, L2, threshold, &dummy, put);
-                    if (PASS == kCount && cnt > 1) atomicAdd(&counters[kSplitPairs], 1u);
-                }
-                if (PASS == kEmit && cnt == 1 && !(K > 3 && split)) {
-                    const uint32_t idx = slot_off[slot];
-                    if (idx < unit_cap)
-                        units[idx] = make_int4(unit_x(gi, sest, threshold), v, i, (int)kFullChild);
-                    else atomicOr(&counters[kErrors], 1u);
-                }
-            }
-            if (PASS == kCount) slot_cnt[slot] = cnt;
         }
-    }
-    if (PASS == kEstimate) {
-        // workgroup sum, one 64-bit atomic per workgroup
-        __shared__ unsigned long long part[kPlanThreads / kWave];
+        // the workgroup's sums (its slots are in the first wave)
+        const uint64_t cut = __ballot(cnt > 1);
         unsigned long long x = est;
 #pragma unroll
-        for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_down(x, d, kWave);
-        if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = x;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long sum = 0;
-            for (int w = 0; w < kPlanThreads / kWave; ++w) sum += part[w];
-            if (sum) atomicAdd(reinterpret_cast<unsigned long long *>(counters + kEstTotal), sum);
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            x += __shfl_down(x, d, kWave);
+            cnt += __shfl_down(cnt, d, kWave);
+        }
+        if (tid == 0) {
+            const uint32_t at = plan_block();
+            uint32_t *line = sum_line(counters, at % kQueues);
+            if (x) atomicAdd(reinterpret_cast<unsigned long long *>(line), x);
+            if (cut) atomicAdd(&line[kSumSplit], (uint32_t)__popcll(cut));
+            if (block_sums) {
+                block_sums[at] = cnt;
+                if (cnt) atomicAdd(&line[kSumUnits + at / kSumWindow], cnt);
+            }
+        }
+    } else if (live) {
+        uint32_t cnt = 0;
+        if (vi != kNoNode) cnt = walk ? got_cnt[tid] : ((K > 3 && sest == 0u) ? 0u : 1u);
+        if (PASS == kCount) {
+            if (cnt > 1) atomicAdd(&counters[kSplitPairs], 1u);
+            slot_cnt[slot] = cnt;
+        } else if (cnt == 1 && !walk) {
+            if (first_unit < unit_cap)
+                units[first_unit] = make_int4(unit_x(gi, sest, threshold), (int)(vi & kViMask),
+                                              (int)(vi >> kViShift), (int)kFullChild);
+            else
+                atomicOr(&counters[kErrors], 1u);
         }
     }
+}
+
+// Workgroups of a sized plan at most (14,336: the windows of a line); more
+// take the scan over all slots.
+constexpr uint32_t kSizedBlocks = kSumWindow * kSumWindows;
+
+static dim3 plan_grid(int ng, int64_t max_nnz)
+{
+    return dim3((unsigned)std::max<int64_t>((max_nnz + kPlanSlots - 1) / kPlanSlots, 1),
+                (unsigned)ng);
+}
+
+size_t plan_tmp_words(int ng, int64_t max_nnz, uint32_t total_slots)
+{
+    const dim3 grid = plan_grid(std::max(ng, 1), max_nnz);
+    return std::max(scan_tmp_words(total_slots),
+                    std::min<size_t>((size_t)grid.x * grid.y, kSizedBlocks));
 }
 
 template <int K>
 static int plan_k(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                   uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                   uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                  uint64_t threshold, uint64_t spec, uint32_t waves, uint32_t upw,
+                  uint64_t threshold, uint64_t spec, bool sized, uint32_t waves, uint32_t upw,
                   uint32_t *counters, hipStream_t stream)
 {
-    const dim3 grid((unsigned)std::max<int64_t>((max_nnz + kPlanThreads - 1) / kPlanThreads, 1),
-                    (unsigned)ng);
+    const dim3 grid = plan_grid(ng, max_nnz), threads((unsigned)plan_threads(K, grid));
+    const uint64_t spec_t = spec ? spec : threshold;
+    sized = sized && units && (uint64_t)grid.x * grid.y <= kSizedBlocks;
+    uint32_t *sums = sized ? scan_tmp : nullptr;
     // the estimate total (counters[kEstTotal]) starts at zero: the callers
     // clear all counters before every plan
-    hipLaunchKernelGGL((plan_kernel<K, kEstimate>), grid, dim3(kPlanThreads), 0, stream, d_graphs,
+    hipLaunchKernelGGL((plan_kernel<K, kEstimate>), grid, threads, 0, stream, d_graphs,
                        slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
-                       spec ? spec : threshold, waves, upw, counters);
+                       spec_t, waves, upw, counters, sums);
     MK_HIP(hipGetLastError());
-    hipLaunchKernelGGL((plan_kernel<K, kCount>), grid, dim3(kPlanThreads), 0, stream, d_graphs,
+    if (!sized) {
+        hipLaunchKernelGGL((plan_kernel<K, kCount>), grid, threads, 0, stream, d_graphs,
+                           slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap,
+                           threshold, spec_t, waves, upw, counters, sums);
+        MK_HIP(hipGetLastError());
+        int rc = scan_u32(slot_cnt, slot_off, total_slots, 0, &counters[kNumUnits], scan_tmp, stream);
+        if (rc != MK_OK) return rc;
+        if (!units) return MK_OK;  // sizing pass
+    }
+    hipLaunchKernelGGL((plan_kernel<K, kEmit>), grid, threads, 0, stream, d_graphs,
                        slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
-                       spec ? spec : threshold, waves, upw, counters);
-    MK_HIP(hipGetLastError());
-    int rc = scan_u32(slot_cnt, slot_off, total_slots, 0, &counters[kNumUnits], scan_tmp, stream);
-    if (rc != MK_OK) return rc;
-    if (!units) return MK_OK;  // sizing pass
-    hipLaunchKernelGGL((plan_kernel<K, kEmit>), grid, dim3(kPlanThreads), 0, stream, d_graphs,
-                       slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
-                       spec ? spec : threshold, waves, upw, counters);
+                       spec_t, waves, upw, counters, sums);
     MK_HIP(hipGetLastError());
     return MK_OK;
 }
@@ -395,14 +590,14 @@ int launch_unit_begins(const DevGraph *d_graphs, int ng, const uint32_t *slot_of
 int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                 uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                 uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                uint64_t split_threshold, uint64_t spec_threshold, uint32_t waves,
+                uint64_t split_threshold, uint64_t spec_threshold, bool sized, uint32_t waves,
                 uint32_t units_per_wave, uint32_t *counters, hipStream_t stream)
 {
     if (ng <= 0) return MK_OK;
 #define MK_PLAN(KK)                                                                         \
     plan_k<KK>(d_graphs, ng, max_nnz, total_slots, slot_cnt, slot_off, slot_est, slot_vi,  \
-               slot_l2, scan_tmp, units, unit_cap, split_threshold, spec_threshold, waves, \
-               units_per_wave, counters, stream)
+               slot_l2, scan_tmp, units, unit_cap, split_threshold, spec_threshold, sized, \
+               waves, units_per_wave, counters, stream)
     switch (k) {
     case 2: return MK_PLAN(2);
     case 3: return MK_PLAN(3);

@@ -1,5 +1,6 @@
 // Error strings, fill and prefix-sum kernels shared by the rest of the
 // library.
+#include <algorithm>
 #include <cstdio>
 
 #include "internal.h"
@@ -58,6 +59,46 @@ int fill_u32(void *dst, uint32_t value, size_t n, hipStream_t stream)
         hipLaunchKernelGGL(fill_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
                            (uint32_t *)dst, value, n);
     }
+    MK_HIP(hipGetLastError());
+    return MK_OK;
+}
+
+// The words of three ranges, taken one after another; ranges of 4 MiB and
+// more by streaming stores, smaller ones are read soon and stay in the
+// caches.  A pass clears its counters, histograms and bit matrices at once:
+// one launch for three (4.5 us each inside a captured graph).
+constexpr size_t kStreamWords = (size_t)1 << 20;
+__global__ void clear_kernel(ClearRange a, ClearRange b, ClearRange c)
+{
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    const u32x4_t zero = {0u, 0u, 0u, 0u};
+    const ClearRange rs[3] = {a, b, c};
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        uint32_t *p = (uint32_t *)rs[q].p;
+        const size_t n = rs[q].words;
+        // up to three words before the first 16-byte boundary, and after the last
+        const size_t head = (((uintptr_t)p & 15) ? (16 - ((uintptr_t)p & 15)) / 4 : 0);
+        const size_t lead = head < n ? head : n;
+        const size_t n4 = (n - lead) >> 2;
+        u32x4_t *d4 = reinterpret_cast<u32x4_t *>(p + lead);
+        if (n >= kStreamWords)
+            for (size_t i = t; i < n4; i += stride) __builtin_nontemporal_store(zero, d4 + i);
+        else
+            for (size_t i = t; i < n4; i += stride) d4[i] = zero;
+        const size_t done = lead + 4 * n4;
+        if (t < lead) p[t] = 0u;
+        if (t < n - done) p[done + t] = 0u;
+    }
+}
+
+int clear_ranges(ClearRange a, ClearRange b, ClearRange c, hipStream_t stream)
+{
+    const size_t most = std::max(a.words, std::max(b.words, c.words));
+    if (most == 0) return MK_OK;
+    const size_t blocks = std::min<size_t>((most / 4 + 255) / 256 + 1, 65536);
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a, b, c);
     MK_HIP(hipGetLastError());
     return MK_OK;
 }
