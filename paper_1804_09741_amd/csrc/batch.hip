@@ -85,6 +85,9 @@ static constexpr uint64_t kDefaultSplit[8] = {0,       0,       1u << 30, 1u << 
 // can hold hundreds of cores (5 us each, so units of 1 ms): n = 700, m = 1500
 // 1.37 -> 0.36 ms of kernel with 256 (1,024: 0.6; 64 and 128 as 256).
 static constexpr uint64_t kCore6Split = 1u << 8;
+#ifndef MK_CORE_SLICE
+#define MK_CORE_SLICE 512
+#endif
 
 namespace mk {
 uint64_t default_split_floor(int plan_k)
@@ -229,6 +232,14 @@ static int batch_enqueue_typed(mk_batch *b, hipStream_t stream)
     return launch_typed_csr(b->d_graphs, b->ng, b->max_n, b->max_m, b->d_counters, stream);
 }
 
+// the planner's least cost of a slice: below it, setting up the node again
+// for every slice costs more than the shorter end saves (a unit of the core
+// kernel sets up a node of two members less than its 4-sets, of 5 us each)
+static uint32_t slice_least(const mk_batch *b)
+{
+    return b->method == MK_METHOD_ESU ? kSliceLeast : MK_CORE_SLICE;
+}
+
 // enqueue the preparation part of one pass on stream: counters and
 // histograms cleared, typed adjacency, work-unit plan (captured as a
 // hipGraph); a planned threshold is the sizing plan's, so d_slot_off keeps
@@ -247,7 +258,7 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
     return launch_plan(b->plan_k, b->d_graphs, b->ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                        b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
                        b->d_units, b->unit_cap, b->opts.split_threshold, b->spec_threshold, true,
-                       (uint32_t)b->max_grid, (uint32_t)std::max(b->opts.units_per_wave, 0),
+                       slice_least(b), (uint32_t)b->max_grid, (uint32_t)std::max(b->opts.units_per_wave, 0),
                        b->d_counters, stream);
 }
 
@@ -518,7 +529,8 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     if (!rc)
         rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                          b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                         nullptr, 0, b->opts.split_threshold, 0, false, (uint32_t)b->max_grid,
+                         nullptr, 0, b->opts.split_threshold, 0, false,
+                         slice_least(b), (uint32_t)b->max_grid,
                          (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
                          ctx->stream);
     if (rc) return bail(rc);

@@ -476,10 +476,12 @@ __device__ void core_node(EnumState<K, V> &s, const CoreLds &c, const int (&mem)
 }
 
 // node with members s_0..s_D (D < k-3): its children jlo..jhi-1 become
-// member D+1; at D+1 = k-3 each child completes a core
+// member D+1; at D+1 = k-3 each child completes a core; slice (D = 1): of the
+// one child's children, the given slice only
 template <int K, int D, int V>
 __device__ void visit_core(EnumState<K, V> &s, const CoreLds &c, const int (&st)[K - 1],
-                           uint32_t code, int jlo, int jhi, int (&mem)[K])
+                           uint32_t code, int jlo, int jhi, int (&mem)[K],
+                           uint32_t slice = 0u)
 {
     int rem[D + 1];
     int total = 0;
@@ -523,7 +525,11 @@ __device__ void visit_core(EnumState<K, V> &s, const CoreLds &c, const int (&st)
 #pragma unroll
             for (int q = 0; q < K - 1; ++q)
                 cst[q] = q < L ? s.len[q] : (q == L ? o + 1 : (q <= D ? st[q] : 0));
-            visit_core<K, D + 1>(s, c, cst, ccode, 0, INT_MAX, mem);
+            // cores cost alike, so a slice is a share of them (r = 1)
+            int lo2 = 0, hi2 = INT_MAX;
+            if constexpr (D == 1)
+                if (slice) slice_children(s, cst, slice, 1, lo2, hi2);
+            visit_core<K, D + 1>(s, c, cst, ccode, lo2, hi2, mem);
             pop_held<K, D + 1>(s, x, held);
         }
     }
@@ -532,8 +538,9 @@ __device__ void visit_core(EnumState<K, V> &s, const CoreLds &c, const int (&st)
 // A unit: k = 3, the core {v}; k = 4, the core {v, w_i}; k >= 5, the cores
 // below children jlo..jhi-1 of the node (v, w_i).
 template <int K, int V>
-__device__ void run_core_unit(EnumState<K, V> &s, const CoreLds &c, int v, int i, uint32_t range)
+__device__ void run_core_unit(EnumState<K, V> &s, const CoreLds &c, int v, int iz, uint32_t range)
 {
+    const int i = iz & ((1 << kSliceShift) - 1);
     int mem[K];
 #pragma unroll
     for (int q = 0; q < K; ++q) mem[q] = 0;
@@ -561,7 +568,8 @@ __device__ void run_core_unit(EnumState<K, V> &s, const CoreLds &c, int v, int i
                 st[0] = i + 1;
                 const bool full = range == kFullChild;
                 visit_core<K, 1>(s, c, st, code, full ? 0 : (int)(range & 0xFFFFu),
-                                 full ? INT_MAX : (int)(range >> 16), mem);
+                                 full ? INT_MAX : (int)(range >> 16), mem,
+                                 (uint32_t)iz >> kSliceShift);
                 pop_held<K, 1>(s, x, held1);
             }
         } else if (lane_id() == 0) {

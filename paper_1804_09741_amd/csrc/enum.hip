@@ -570,9 +570,11 @@ __device__ void last_two(EnumState<K, V> &s, const int (&st)[K - 1], uint32_t co
 }
 
 // node with members s_0..s_D: visit children jlo..jhi-1 of its extension
-// list (the tails seg[q][st[q]:] for q <= D, in order)
+// list (the tails seg[q][st[q]:] for q <= D, in order); slice (D = 1): of the
+// one child's children, the given slice only
 template <int K, int D, int V>
-__device__ void visit(EnumState<K, V> &s, const int (&st)[K - 1], uint32_t code, int jlo, int jhi)
+__device__ void visit(EnumState<K, V> &s, const int (&st)[K - 1], uint32_t code, int jlo, int jhi,
+                      uint32_t slice = 0u)
 {
     if constexpr (K == 3 && D == 1) {
         leaf<K>(s, st, code);
@@ -610,15 +612,19 @@ __device__ void visit(EnumState<K, V> &s, const int (&st)[K - 1], uint32_t code,
 #pragma unroll
             for (int q = 0; q < K - 1; ++q)
                 cst[q] = q < L ? s.len[q] : (q == L ? o + 1 : (q <= D ? st[q] : 0));
-            visit<K, D + 1>(s, cst, ccode, 0, INT_MAX);
+            int lo2 = 0, hi2 = INT_MAX;
+            if constexpr (D == 1)
+                if (slice) slice_children(s, cst, slice, K - 3, lo2, hi2);
+            visit<K, D + 1>(s, cst, ccode, lo2, hi2);
             pop_held<K, D + 1>(s, x, held);
         }
     }
 }
 
 template <int K, int V>
-__device__ void run_unit(EnumState<K, V> &s, int v, int i, uint32_t range)
+__device__ void run_unit(EnumState<K, V> &s, int v, int iz, uint32_t range)
 {
+    const int i = iz & ((1 << kSliceShift) - 1);
     s.root = v;
     const Held held0 = push_held<K, 0>(s, v);
     if (i < s.len[0]) {
@@ -630,7 +636,8 @@ __device__ void run_unit(EnumState<K, V> &s, int v, int i, uint32_t range)
         for (int q = 0; q < K - 1; ++q) st[q] = 0;
         st[0] = i + 1;
         const bool full = range == kFullChild;
-        visit<K, 1>(s, st, code, full ? 0 : (int)(range & 0xFFFFu), full ? INT_MAX : (int)(range >> 16));
+        visit<K, 1>(s, st, code, full ? 0 : (int)(range & 0xFFFFu), full ? INT_MAX : (int)(range >> 16),
+                    (uint32_t)iz >> kSliceShift);
         pop_held<K, 1>(s, x, held1);
     } else if (lane_id() == 0) {
         atomicAdd(s.errors, 1u);

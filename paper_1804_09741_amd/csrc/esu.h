@@ -504,6 +504,33 @@ __device__ __forceinline__ void init_state(EnumState<K, V> &s, char *base, const
     __syncthreads();
 }
 
+// Child t of a node with `total` children where slice s of n begins, for
+// subtrees of r more members: children t.. hold about C(total - t, r) of the
+// node's C(total, r) sets, so equal slices begin where ((total - t) / total)^r
+// = 1 - s / n.  (The steps of 1 / n, at least 1 / 1023, are far above the
+// error of the power, so the begins do not decrease with s.)
+__device__ __forceinline__ int slice_begin(uint32_t s, uint32_t n, int total, int r)
+{
+    if (s == 0u) return 0;
+    if (s >= n) return total;
+    const float left = (float)(n - s) / (float)n;
+    const float keep = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(left) / (float)r);
+    const int t = (int)((float)total * (1.0f - keep));
+    return uniform(t < total ? t : total);
+}
+
+// the children [lo, hi) that a unit's slice bits leave of a node with members
+// s_0..s_2 and the tails st, whose sets have r more members
+template <int K, int V, int N>
+__device__ __forceinline__ void slice_children(const EnumState<K, V> &s, const int (&st)[N],
+                                               uint32_t slice, int r, int &lo, int &hi)
+{
+    const int total = s.len[0] - st[0] + s.len[1] - st[1] + s.len[2] - st[2];
+    const uint32_t n = slice >> 10, at = slice & 1023u;
+    lo = slice_begin(at, n, total, r);
+    hi = slice_begin(at + 1u, n, total, r);
+}
+
 // The persistent loop: take units from the kQueues queues (own XCD's range
 // first) and call run(v, i, range) for each.  When the unit's graph changes,
 // on_switch(gi) runs first (a kernel flushes what it holds for the previous

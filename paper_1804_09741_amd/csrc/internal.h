@@ -104,7 +104,9 @@ __device__ __forceinline__ uint32_t list_relation(RowPtr urow, AdjPtr uadj, uint
 
 // Work unit of the enumeration queue.
 //   x: graph index in the batch, y: root vertex v,
-//   z: index i of the first extension vertex in v's extension list,
+//   z: index i of the first extension vertex in v's extension list (12 bits),
+//      and slice_bits(s, n): slice s of n (2..1023) of the one child's
+//      children (0: all),
 //   w: kFullChild -> the whole subtree below (v, w_i);
 //      else j0 | j1 << 16 -> children j0..j1-1 of the node (v, w_i).
 // kHeavyBit in x marks a unit whose estimated cost is high (the core
@@ -112,6 +114,13 @@ __device__ __forceinline__ uint32_t list_relation(RowPtr urow, AdjPtr uadj, uint
 // masks the bit off the graph index).
 constexpr uint32_t kFullChild = 0xFFFFFFFFu;
 constexpr uint32_t kHeavyBit = 1u << 31;
+constexpr int kSliceShift = 12;
+constexpr uint32_t kMaxSlices = 1023;
+constexpr uint32_t kSliceLeast = 1u << 12;  // the enumeration's least slice (plan.hip)
+__host__ __device__ constexpr uint32_t slice_bits(uint32_t s, uint32_t n)
+{
+    return (s << kSliceShift) | (n << (kSliceShift + 10));
+}
 
 // counters[] slots shared by planner and enumeration kernels
 enum Counter : int {
@@ -197,12 +206,14 @@ int launch_typed_csr(const DevGraph *d_graphs, int ng, int max_n, int64_t max_m,
 // as spec_threshold (a batch passes the one its sizing plan of the same
 // graphs found, read from counters[kPlanThreshold]): there is no count pass,
 // and the emit pass finds its offsets itself where the estimate's workgroups
-// are few enough (a threshold that differs is a device error).
+// are few enough (a threshold that differs is a device error).  slice_least:
+// a child may be cut into units of its own children that cost this much at
+// least (plans for k >= 5; 0: children stay whole).
 int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                 uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                 uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                uint64_t split_threshold, uint64_t spec_threshold, bool sized, uint32_t waves,
-                uint32_t units_per_wave, uint32_t *counters, hipStream_t stream);
+                uint64_t split_threshold, uint64_t spec_threshold, bool sized,
+                uint32_t slice_least, uint32_t waves, uint32_t units_per_wave, uint32_t *counters, hipStream_t stream);
 
 // Enumeration + code + lookup + histogram over the queued units.
 // k = 7 (k7.hip): device tables of one count

@@ -649,10 +649,11 @@ __device__ __forceinline__ void last_two7(EnumState<7, V> &s, K7Wave &w7, const 
     }
 }
 
-// node with members s_0..s_D: children jlo..jhi-1 of its extension list
+// node with members s_0..s_D: children jlo..jhi-1 of its extension list;
+// slice (D = 1): of the one child's children, the given slice only
 template <int D, int V>
 __device__ __forceinline__ void visit7(EnumState<7, V> &s, K7Wave &w7, const K7Tables &t, const int (&st)[6],
-                       Code7 code, int jlo, int jhi)
+                       Code7 code, int jlo, int jhi, uint32_t slice = 0u)
 {
     if constexpr (D == 4) {
         last_two7(s, w7, t, st, code, jlo, jhi);
@@ -688,16 +689,20 @@ __device__ __forceinline__ void visit7(EnumState<7, V> &s, K7Wave &w7, const K7T
 #pragma unroll
             for (int q = 0; q < 6; ++q)
                 cst[q] = q < L ? s.len[q] : (q == L ? o + 1 : (q <= D ? st[q] : 0));
-            visit7<D + 1>(s, w7, t, cst, ccode, 0, INT_MAX);
+            int lo2 = 0, hi2 = INT_MAX;
+            if constexpr (D == 1)
+                if (slice) slice_children(s, cst, slice, 4, lo2, hi2);
+            visit7<D + 1>(s, w7, t, cst, ccode, lo2, hi2);
             pop_held<7, D + 1>(s, x, held);
         }
     }
 }
 
 template <int V>
-__device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const K7Tables &t, int v, int i,
+__device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const K7Tables &t, int v, int iz,
                           uint32_t range)
 {
+    const int i = iz & ((1 << kSliceShift) - 1);
     s.root = v;
     const Held held0 = push_held<7, 0>(s, v);
     if (i < s.len[0]) {
@@ -710,7 +715,7 @@ __device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const 
         st[0] = i + 1;
         const bool full = range == kFullChild;
         visit7<1>(s, w7, t, st, code, full ? 0 : (int)(range & 0xFFFFu),
-                  full ? INT_MAX : (int)(range >> 16));
+                  full ? INT_MAX : (int)(range >> 16), (uint32_t)iz >> kSliceShift);
         pop_held<7, 1>(s, x, held1);
     } else if (lane_id() == 0) {
         atomicAdd(s.errors, 1u);

@@ -158,13 +158,24 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     // make: consecutive ranges of a node exceed the split threshold together
     // and the threshold is at least the estimated total over 32 units a
     // wave, so there are at most two ranges per unit of that target and one
-    // more per node.
+    // more per node; slices of children, which cost twice the threshold at
+    // least, add up to two more per unit of the target.  A scratch without
+    // the room for those plans whole children.
     HistLayout layout = hist_layout(1, nc, grid, false);
-    const uint64_t most_units = 2 * (32ull * (uint64_t)grid + 1) + nnz + kMinStaticUnits;
-    const size_t o_work = round_up(o_units + most_units * sizeof(int4), 256);
-    if (layout.graph_words && o_work + 8 * layout.words() <= kStaticScratchBytes)
+    const uint64_t target = 32ull * (uint64_t)grid + 1;
+    const uint64_t most_whole = 2 * target + nnz + kMinStaticUnits;
+    bool slices = most_whole + 2 * target <= unit_cap;
+    size_t o_work = 0;
+    const auto work_fits = [&](uint64_t most_units) {
+        o_work = round_up(o_units + most_units * sizeof(int4), 256);
+        return o_work + 8 * layout.words() <= kStaticScratchBytes;
+    };
+    if (layout.graph_words && slices && work_fits(most_whole + 2 * target))
         unit_cap = (o_work - o_units) / sizeof(int4);
-    else
+    else if (layout.graph_words && work_fits(most_whole)) {
+        unit_cap = (o_work - o_units) / sizeof(int4);
+        slices = false;
+    } else
         layout = HistLayout();
     unsigned long long *count_to =
         layout.graph_words ? reinterpret_cast<unsigned long long *>(base + o_work) : hist;
@@ -178,7 +189,7 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
         rc = launch_plan(k, dg, 1, (int64_t)nnz, (uint32_t)nnz, slots, slots + nnz, slots + 2 * nnz,
                          slots + 3 * nnz, slots + 4 * nnz, reinterpret_cast<uint32_t *>(base + o_scan),
                          units, (uint32_t)std::min<uint64_t>(unit_cap, 0xFFFFFFFFull),
-                         default_split_floor(k), 0, false, (uint32_t)grid, 0u, counters, s);
+                         default_split_floor(k), 0, false, slices ? kSliceLeast : 0u, (uint32_t)grid, 0u, counters, s);
     EnumConfig cfg{};
     cfg.max_n = g->n;
     cfg.seg_cap = seg_cap;

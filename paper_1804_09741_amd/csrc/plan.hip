@@ -5,7 +5,8 @@
 // u > v}; choosing its i-th vertex w_i gives the node (v, w_i), whose own
 // extension list E2 is E_v[i+1:] followed by the neighbours of w_i that
 // exceed v and are not in delta(v) (L2 vertices).  A work unit is a range of
-// the children of such a node.  Child j (vertex x) of the node roots a
+// the children of such a node, or a slice of one child's own children.
+// Child j (vertex x) of the node roots a
 // subtree of roughly C(L2 - j - 1 + d(x) - 1, k - 3) subgraphs: its own
 // extension list is the rest of E2 plus at most d(x) - 1 new neighbours.
 // Children are packed greedily into ranges whose estimated sum stays under
@@ -227,6 +228,30 @@ __device__ __forceinline__ uint64_t team_incl_sum(uint64_t x)
     return x;
 }
 
+// Slices of a child of cost c (1: whole), for plans that cut children (slices;
+// not the core kernel's).  A hub's child can hold more than a wave's whole
+// share of the launch -- 2 to 6 shares at k = 7 on 16 graphs of n = 700, 25
+// to 55 on one at k = 6 -- and the launch then ends on one wave.  A slice
+// costs about twice the split threshold (k = 7, where a wave's share is 16
+// thresholds, not 32: four times) and no less than 4,096, below which setting
+// up the node again for every slice costs more than the shorter end saves.
+// Kernel ms with whole children, slices of 1, 2, 4, 8 thresholds:
+//   k = 6, n = 500, m = 1200          3.09  1.26  0.99  0.79  0.66 (= 4,096)
+//   k = 6, n = 1500, m = 9000         37.2  31.9  31.7  32.0  33.2
+//   k = 6 batch of 31, n = 700        2.77  2.77  2.63  2.54  2.51
+//   k = 6 on lists, n = 131,073       25.5  25.7  24.1  23.3  23.0 (= 4,096)
+//   k = 5 by enumeration, n = 1000    0.64  0.59  0.59  0.62  0.63 (2 = 8,192)
+//   k = 7 batch of 16, n = 700        42.3  35.2  35.0  34.1  34.7
+template <int K>
+__device__ __forceinline__ uint32_t child_slices(uint64_t c, uint64_t threshold, uint32_t least)
+{
+    constexpr uint64_t kTimes = K >= 7 ? 4 : 2;
+    if (K < 5 || least == 0u || c / kTimes <= threshold || c <= least) return 1u;
+    const uint64_t each = kTimes * threshold > least ? kTimes * threshold : least;
+    const uint64_t n = (c - 1) / each + 1;
+    return n < kMaxSlices ? (uint32_t)n : kMaxSlices;
+}
+
 // A first-level node (v, w_i = y): E_v[i+1:] is uadj[t0, r1).
 struct PlanNode {
     int v, i, y, t0, r1;
@@ -248,12 +273,14 @@ __device__ __forceinline__ int team_ext_len(const PlanGraph &g, const PlanNode &
     return len;
 }
 
-// Greedy ranges over its children: calls put(r, j0 | j1 << 16, estimated
-// cost) for every range on the team's first lane when EMIT, returns the
-// number of ranges; *est gets the sum of the costs.
+// Greedy ranges over its children, and the slices of the costliest: calls
+// put(r, slice, j0 | j1 << 16, estimated cost) for every unit on one of the
+// team's lanes when EMIT, returns the number of units; *est gets the sum of
+// the costs.
 template <int K, bool EMIT, typename Put>
 __device__ __forceinline__ uint32_t team_split(const PlanGraph &g, const PlanNode &n, int L2,
-                                               uint64_t threshold, uint64_t *est, Put put)
+                                               uint64_t threshold, uint32_t least,
+                                               uint64_t *est, Put put)
 {
     const int sub = threadIdx.x % kTeam;
     uint32_t cnt = 0;
@@ -281,17 +308,33 @@ __device__ __forceinline__ uint32_t team_split(const PlanGraph &g, const PlanNod
         const uint64_t c = child ? choose_small(L2 - j - 1 + dx - 1, K - 3) + 1 : 0;
         const uint64_t incl = team_incl_sum(c);
         uint64_t closed = 0;  // cost of these children in ranges that are closed
+        const uint32_t cut = child_slices<K>(c, threshold, least);
         for (;;) {
-            const uint32_t over = team_ballot(child && j > j0 && acc + (incl - closed) > threshold);
+            const bool sliced = child && cut > 1u && j >= j0;
+            const uint32_t over = team_ballot(
+                sliced || (child && j > j0 && acc + (incl - closed) > threshold));
             if (!over) break;
             const int l = __builtin_ctz(over);
             const int jc = __shfl(j, l, kTeam);
-            const uint64_t before = __shfl((unsigned long long)(incl - c), l, kTeam);
-            if (EMIT && sub == 0) put(cnt, (uint32_t)j0 | ((uint32_t)jc << 16), acc + (before - closed));
-            ++cnt;
+            const uint64_t cc = __shfl((unsigned long long)c, l, kTeam);
+            const uint64_t before = __shfl((unsigned long long)incl, l, kTeam) - cc;
+            const uint32_t n = __shfl(cut, l, kTeam);
+            if (jc > j0) {
+                if (EMIT && sub == 0)
+                    put(cnt, 0u, (uint32_t)j0 | ((uint32_t)jc << 16), acc + (before - closed));
+                ++cnt;
+            }
             j0 = jc;
             acc = 0;
             closed = before;
+            if (n > 1u) {  // child jc alone
+                if (EMIT)
+                    for (uint32_t r = (uint32_t)sub; r < n; r += kTeam)
+                        put(cnt + r, slice_bits(r, n), (uint32_t)jc | ((uint32_t)(jc + 1) << 16), cc / n);
+                cnt += n;
+                j0 = jc + 1;
+                closed = before + cc;
+            }
         }
         const uint64_t sum = __shfl((unsigned long long)incl, kTeam - 1, kTeam);
         acc += sum - closed;
@@ -299,7 +342,7 @@ __device__ __forceinline__ uint32_t team_split(const PlanGraph &g, const PlanNod
         jb += __popc(m);
     }
     if (L2 > j0) {
-        if (EMIT && sub == 0) put(cnt, (uint32_t)j0 | ((uint32_t)L2 << 16), acc);
+        if (EMIT && sub == 0) put(cnt, 0u, (uint32_t)j0 | ((uint32_t)L2 << 16), acc);
         ++cnt;
     }
     *est = total;
@@ -352,7 +395,8 @@ __global__ __launch_bounds__(kPlanThreadsFew) void plan_kernel(const DevGraph *g
                                                             int4 *units, uint32_t unit_cap,
                                                             uint64_t floor_t, uint64_t spec_t,
                                                             uint32_t waves,
-                                                            uint32_t upw, uint32_t *counters,
+                                                            uint32_t upw, uint32_t least,
+                                                            uint32_t *counters,
                                                             uint32_t *block_sums)
 {
     __shared__ PlanNode node[kPlanSlots];      // nodes to walk, in list order
@@ -440,17 +484,18 @@ __global__ __launch_bounds__(kPlanThreadsFew) void plan_kernel(const DevGraph *g
             const PlanNode n = node[q];
             const int of = node_slot[q];
             const uint32_t base = node_arg[q];
-            auto put = [&](uint32_t r, uint32_t w, uint64_t c) {
+            auto put = [&](uint32_t r, uint32_t slice, uint32_t w, uint64_t c) {
                 const uint32_t idx = base + r;
                 if (idx < unit_cap)
-                    units[idx] = make_int4(unit_x(gi, c, threshold), n.v, n.i, (int)w);
+                    units[idx] = make_int4(unit_x(gi, c, threshold), n.v, (int)((uint32_t)n.i | slice),
+                                           (int)w);
                 else
                     atomicOr(&counters[kErrors], 1u);
             };
             const int L2 = PASS == kEstimate ? team_ext_len(g, n) : got_l2[of];
             uint64_t est = 0;
             const uint32_t cnt = team_split<K, PASS == kEmit>(
-                g, n, L2, PASS == kEstimate ? spec_t : threshold, &est, put);
+                g, n, L2, PASS == kEstimate ? spec_t : threshold, least, &est, put);
             if (tid % kTeam == 0) {
                 got_est[of] = est;
                 got_cnt[of] = cnt;
@@ -530,8 +575,8 @@ template <int K>
 static int plan_k(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                   uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                   uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                  uint64_t threshold, uint64_t spec, bool sized, uint32_t waves, uint32_t upw,
-                  uint32_t *counters, hipStream_t stream)
+                  uint64_t threshold, uint64_t spec, bool sized, uint32_t least, uint32_t waves,
+                  uint32_t upw, uint32_t *counters, hipStream_t stream)
 {
     const dim3 grid = plan_grid(ng, max_nnz), threads((unsigned)plan_threads(K, grid));
     const uint64_t spec_t = spec ? spec : threshold;
@@ -541,12 +586,12 @@ static int plan_k(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t to
     // clear all counters before every plan
     hipLaunchKernelGGL((plan_kernel<K, kEstimate>), grid, threads, 0, stream, d_graphs,
                        slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
-                       spec_t, waves, upw, counters, sums);
+                       spec_t, waves, upw, least, counters, sums);
     MK_HIP(hipGetLastError());
     if (!sized) {
         hipLaunchKernelGGL((plan_kernel<K, kCount>), grid, threads, 0, stream, d_graphs,
                            slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap,
-                           threshold, spec_t, waves, upw, counters, sums);
+                           threshold, spec_t, waves, upw, least, counters, sums);
         MK_HIP(hipGetLastError());
         int rc = scan_u32(slot_cnt, slot_off, total_slots, 0, &counters[kNumUnits], scan_tmp, stream);
         if (rc != MK_OK) return rc;
@@ -554,7 +599,7 @@ static int plan_k(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t to
     }
     hipLaunchKernelGGL((plan_kernel<K, kEmit>), grid, threads, 0, stream, d_graphs,
                        slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
-                       spec_t, waves, upw, counters, sums);
+                       spec_t, waves, upw, least, counters, sums);
     MK_HIP(hipGetLastError());
     return MK_OK;
 }
@@ -590,14 +635,15 @@ int launch_unit_begins(const DevGraph *d_graphs, int ng, const uint32_t *slot_of
 int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
                 uint32_t *slot_cnt, uint32_t *slot_off, uint32_t *slot_est, uint32_t *slot_vi,
                 uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
-                uint64_t split_threshold, uint64_t spec_threshold, bool sized, uint32_t waves,
-                uint32_t units_per_wave, uint32_t *counters, hipStream_t stream)
+                uint64_t split_threshold, uint64_t spec_threshold, bool sized,
+                uint32_t slice_least, uint32_t waves, uint32_t units_per_wave,
+                uint32_t *counters, hipStream_t stream)
 {
     if (ng <= 0) return MK_OK;
 #define MK_PLAN(KK)                                                                         \
     plan_k<KK>(d_graphs, ng, max_nnz, total_slots, slot_cnt, slot_off, slot_est, slot_vi,  \
                slot_l2, scan_tmp, units, unit_cap, split_threshold, spec_threshold, sized, \
-               waves, units_per_wave, counters, stream)
+               slice_least, waves, units_per_wave, counters, stream)
     switch (k) {
     case 2: return MK_PLAN(2);
     case 3: return MK_PLAN(3);
