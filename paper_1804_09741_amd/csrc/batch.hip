@@ -85,9 +85,6 @@ static constexpr uint64_t kDefaultSplit[8] = {0,       0,       1u << 30, 1u << 
 // can hold hundreds of cores (5 us each, so units of 1 ms): n = 700, m = 1500
 // 1.37 -> 0.36 ms of kernel with 256 (1,024: 0.6; 64 and 128 as 256).
 static constexpr uint64_t kCore6Split = 1u << 8;
-#ifndef MK_CORE_SLICE
-#define MK_CORE_SLICE 512
-#endif
 
 namespace mk {
 uint64_t default_split_floor(int plan_k)
@@ -233,11 +230,14 @@ static int batch_enqueue_typed(mk_batch *b, hipStream_t stream)
 }
 
 // the planner's least cost of a slice: below it, setting up the node again
-// for every slice costs more than the shorter end saves (a unit of the core
-// kernel sets up a node of two members less than its 4-sets, of 5 us each)
+// for every slice costs more than the shorter end saves.  The core kernel's
+// estimates are in 5-sets, and a slice of 512 is some 32 4-sets of 5 us each
+// (k = 6, n = 500, m = 1200 0.93 -> 0.75 ms of kernel, n = 1500, m = 9000 19.7
+// -> 15.6, 0.78 and 14.8 with 2,048; 128 as 512).
+constexpr uint32_t kCoreSliceLeast = 512;
 static uint32_t slice_least(const mk_batch *b)
 {
-    return b->method == MK_METHOD_ESU ? kSliceLeast : MK_CORE_SLICE;
+    return b->method == MK_METHOD_ESU ? kSliceLeast : kCoreSliceLeast;
 }
 
 // enqueue the preparation part of one pass on stream: counters and
@@ -515,8 +515,8 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         // one private marks array per workgroup, rounded to 64 entries; all
         // of them together within 1/16 of the device memory
         b->mark_stride = ((size_t)std::max(b->max_n, 1) + 63) & ~(size_t)63;
-        // 32-bit marks in device memory (k = 7: and a tag byte per vertex)
-        const size_t per_wave = b->mark_stride * (b->k == 7 ? 5 : 4);
+        // 32-bit marks in device memory
+        const size_t per_wave = b->mark_stride * 4;
         const uint64_t budget = (uint64_t)ctx->hbm_bytes / 16;
         const uint64_t fit = std::max<uint64_t>(budget / per_wave, 1);
         b->max_grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, fit);
@@ -1107,10 +1107,6 @@ static int count7_once(mk_batch *b, int class_log2, int64_t cap, uint64_t *codes
     if (e == hipSuccess) e = alloc((void **)&a.overflow, 4);
     if (e == hipSuccess) e = alloc((void **)&d_n, 8 * (size_t)ng);
     if (e == hipSuccess) e = alloc((void **)&d_out, 16 * (size_t)ng * (size_t)cap);
-    if (e == hipSuccess && b->marks == MK_MARKS_GLOBAL) {
-        a.etag_stride = b->mark_stride;
-        e = alloc((void **)&a.etag, a.etag_stride * (size_t)b->grid);
-    }
     if (e != hipSuccess) {
         release();
         return fail(e == hipErrorOutOfMemory ? MK_ENOMEM : MK_EDEVICE, "mk_count7: allocation: %s",
@@ -1122,7 +1118,6 @@ static int count7_once(mk_batch *b, int class_log2, int64_t cap, uint64_t *codes
     if (!rc) rc = fill_u32(a.totals, 0u, 2 * (size_t)ng, st);
     if (!rc) rc = fill_u32(a.overflow, 0u, 1, st);
     if (!rc) rc = fill_u32(d_n, 0u, 2 * (size_t)ng, st);
-    if (!rc && a.etag) rc = fill_u32(a.etag, 0u, a.etag_stride * (size_t)b->grid / 4, st);
     if (!rc) rc = batch_enqueue_prep(b, nullptr, st);
     EnumConfig cfg = enum_config(b);
     cfg.hash_bits = 0;  // the k = 7 kernel keeps its own hash of 64-bit codes
@@ -1206,8 +1201,8 @@ extern "C" int mk_count7(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int
     if (ng == 0) return MK_OK;
     std::lock_guard<std::recursive_mutex> lock(ctx->mu);
     MK_HIP(hipSetDevice(ctx->device));
-    // marks in LDS with bit-matrix arc tests while they fit, else marks and
-    // extension tags in device memory with arc tests on the lists
+    // marks in LDS with bit-matrix arc tests while they fit, else marks in
+    // device memory with arc tests on the lists
     int max_n = 0;
     for (int i = 0; i < ng; ++i) max_n = std::max(max_n, gs[i]->n);
     const bool big = max_n > MK_LDS_MARKS_MAX_VERTICES;

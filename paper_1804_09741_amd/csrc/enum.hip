@@ -232,24 +232,26 @@ __device__ void last_two_small(EnumState<K, V> &s, const int (&st)[K - 1],
     __syncthreads();
 }
 
-// Nodes with at most one wave of extension vertices, when marks are 32-bit
-// (k = 6, and every k with marks in device memory): the pairs inside E are
+// Nodes with at most one wave of extension vertices (k >= 5, and every k
+// with marks in device memory; k = 5 by enumeration, n = 1000: 0.565 ms of
+// kernel with the pairs tested one by one, 0.538 so): the pairs inside E are
 // counted per pair of cells, as in Section 3's loop over L_{k-2}, with no
 // arc test between two extension vertices.  Two
 // vertices with equal marks relate alike to the members, so all pairs of E
 // from cells A and B without an arc between them have one code; there are
 // C(n_A, 2) or n_A n_B of them.  The arcs inside E are found while the
 // children's lists are scanned for Part B: E's vertices carry kETag and
-// their lane in their (32-bit) marks meanwhile, and each arc (w, u), u
+// their lane in their marks meanwhile, and each arc (w, u), u
 // after w, adds one to its own code and takes one from its cell pair's.
 // Part B is counted as in last_two_small.
-constexpr uint32_t kETag = 1u << 30;  // mark bits 24..29: the vertex's lane
+constexpr uint32_t kETag = 1u << 15;
+constexpr int kETagLane = 9;  // mark bits 9..14: the vertex's lane
 
 template <int K, int V>
 __device__ void last_two_cells(EnumState<K, V> &s, const int (&st)[K - 1],
                                const int (&rem)[K - 2], int e, uint32_t code, int jlo)
 {
-    static_assert(sizeof(MarkT<K, V>) == 4, "E tags need 32-bit marks");
+    static_assert(2 * kSegments<K> <= kETagLane, "relation bits and tags overlap");
     constexpr int NQ = K - 2;
     constexpr int P1 = K - 2, P2 = K - 1;
     constexpr int B_WU = (K - 2) * (K - 1) + (K - 2);
@@ -267,7 +269,7 @@ __device__ void last_two_cells(EnumState<K, V> &s, const int (&st)[K - 1],
         deg = s.urow[vtx + 1] - row;
     }
     if (!inE) deg = 0;
-    if (inE) s.mark[vtx] = (MarkT<K, V>)(m0 | kETag | ((uint32_t)lane << 24));
+    if (inE) s.mark[vtx] = (MarkT<K, V>)(m0 | kETag | ((uint32_t)lane << kETagLane));
     __syncthreads();
     auto tbits = [](uint32_t t) { return ((t & 1u) << B_WU) | ((t >> 1) << B_UW); };
 
@@ -292,7 +294,7 @@ __device__ void last_two_cells(EnumState<K, V> &s, const int (&st)[K - 1],
                 const uint32_t mu = s.mark[u];
                 t = ent & 3u;
                 if (mu & kETag) {
-                    q = (int)((mu >> 24) & 63u);
+                    q = (int)((mu >> kETagLane) & 63u);
                     arc = q > l;
                 } else if (u > s.root && mu == 0u) {
                     tb = t;
@@ -335,7 +337,7 @@ __device__ void last_two_cells(EnumState<K, V> &s, const int (&st)[K - 1],
             const uint32_t mu = s.mark[u];
             t = ent & 3u;
             if (mu & kETag) {
-                q = (int)((mu >> 24) & 63u);
+                q = (int)((mu >> kETagLane) & 63u);
                 arc = q > src1;
             } else {
                 bv = u > s.root && mu == 0u;
@@ -427,7 +429,7 @@ __device__ void last_two(EnumState<K, V> &s, const int (&st)[K - 1], uint32_t co
     const int hi = e < jhi ? e : jhi;
     if (jlo >= hi) return;
     if (e <= kWave && hi == e) {
-        if constexpr (sizeof(MarkT<K, V>) == 4) last_two_cells<K>(s, st, rem, e, code, jlo);
+        if constexpr (K >= 5 || (V & kVarGlobal) != 0) last_two_cells<K>(s, st, rem, e, code, jlo);
         else last_two_small<K>(s, st, rem, e, code, jlo);
         return;
     }

@@ -91,7 +91,7 @@ using SegT = typename std::conditional<(V & kVarGlobal) != 0, uint32_t, uint16_t
 // Bytes of one vertex's mark (the size of MarkT<K, V> below).
 __host__ __device__ inline int mark_size(int k, int variant)
 {
-    return (variant & kVarCore) != 0 ? 1 : (k <= 5 && (variant & kVarGlobal) == 0 ? 2 : 4);
+    return (variant & kVarCore) != 0 ? 1 : ((variant & kVarGlobal) == 0 ? 2 : 4);
 }
 
 // Byte offsets of one wave's LDS: marks (n x mark_size; none when they
@@ -119,12 +119,14 @@ __host__ __device__ inline LdsLayout lds_layout(int k, int max_n, int seg_cap, i
 // Marks hold, for members at positions 0..S-1 (S = kSegments), S "in" bits
 // and then S "out" bits: 4 / 4 / 6 / 8 / 10 bits for k = 3..7.  The core
 // walk needs nothing else of a vertex, so its marks are bytes; the
-// enumeration's are 16-bit for k <= 5 in LDS and 32-bit otherwise (room for
-// the extension-list tags of last_two_cells).
+// enumeration's are 16-bit in LDS, with room above those bits for the
+// extension-list tags of the last two levels, and 32-bit in device memory.
+// (32-bit marks in LDS at k = 6 held 6 waves per CU at n = 5000, where these
+// hold 11: m = 30000 509 -> 304 ms, n = 1500 m = 9000 31.8 -> 27.4.)
 template <int K, int V = 0>
 using MarkT = typename std::conditional<
     (V & kVarCore) != 0, uint8_t,
-    typename std::conditional<K <= 5 && (V & kVarGlobal) == 0, uint16_t, uint32_t>::type>::type;
+    typename std::conditional<(V & kVarGlobal) == 0, uint16_t, uint32_t>::type>::type;
 
 template <int K, int V = 0>
 struct EnumState {

@@ -225,8 +225,6 @@ struct K7Launch {
     unsigned long long *totals;                  // per graph: subgraphs
     uint32_t *overflow;                          // class inserts that found no slot
     uint32_t *cache_used;                        // cache slots claimed (fill level)
-    uint8_t *etag;                               // device-memory marks: tag bytes,
-    size_t etag_stride;                          //   per workgroup, all zero
 };
 int k7_lds_bytes(int max_n, int seg_cap, int variant);
 int k7_max_blocks_per_cu(int variant, int lds_bytes, int *blocks);

@@ -43,8 +43,6 @@ struct K7Tables {
     unsigned long long *totals;    // per graph: subgraphs counted
     uint32_t *overflow;            // class-table inserts that found no slot
     uint32_t *cache_used;          // cache slots claimed so far (its fill level)
-    uint8_t *etag;                 // marks in device memory: the tags too,
-    size_t etag_stride;            //   etag_stride bytes per workgroup, zero
 };
 
 // per-wave hash of pending (labeled code, count) pairs in LDS
@@ -54,8 +52,6 @@ struct K7Wave {
     int hused;
     uint32_t hpending;
     int graph;
-    uint8_t *etag;     // per vertex: 0x80 | lane while it is in a small node's E
-                       // (LDS, or device memory with the marks)
     Code7 *cc1, *cc2;  // per cell of E: code bits at positions 5 and 6
     uint32_t *csz;     //   and its size
 };
@@ -382,14 +378,24 @@ __device__ __forceinline__ Code7 from_lane64(Code7 v, int l)
     return ((Code7)from_lane7((uint32_t)(v >> 32), l) << 32) | from_lane7((uint32_t)v, l);
 }
 
-// Nodes with at most one wave of extension vertices: the pairs inside E are
+// last_two7_cells' tags in the marks
+constexpr int kTagShift7 = 2 * kSegments<7>;
+constexpr int kTagMax7 = (1 << (16 - kTagShift7)) - 1;
+static_assert(kTagMax7 == 63 && kTagMax7 < kWave, "tags: lane + 1 of a wave less one");
+
+// Nodes with at most 63 extension vertices: the pairs inside E are
 // counted per pair of cells, as in Section 3's loop over L_{k-2}.  Vertices
 // of E with equal marks relate alike to the members, so all pairs from
 // cells A and B without an arc between them have one class; there are
 // C(n_A, 2) or n_A n_B of them.  The arcs inside E are found while the
 // children's lists are scanned for their exclusive neighbours: E's vertices
 // carry a tag with their lane meanwhile, and each arc (w, u), u after w,
-// adds one to its own code and takes one from its cell pair's.  Lane l holds
+// adds one to its own code and takes one from its cell pair's.  The tag, lane
+// + 1, stands above the relation bits of the vertex's mark, so that one read
+// tells a tagged vertex, an exclusive one and the rest apart, and ten bits
+// and six fill a 16-bit mark: E has at most 63 vertices.  (32-bit marks and
+// a byte array of tags: 9.9 KB a wave at n = 700, 16 waves per CU, and two
+// dependent reads an entry; 35.1 -> 30.8 ms on 16 graphs of n = 700.)  Lane l holds
 // E[l], its code bits for positions 5 and 6 and its list row; a child of
 // degree >= kRowMin is scanned alone.
 template <int V>
@@ -399,19 +405,19 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
     constexpr int B_WU = bit7(5, 6), B_UW = bit7(6, 5);
     const int lane = lane_id();
     const bool inE = lane >= jlo && lane < e;
-    uint32_t vtx = 0;
+    uint32_t vtx = 0, m = 0;
     Code7 cb1 = 0, cb2 = 0;
     int row = 0, deg = 0;
     if (lane < e) {
         vtx = s.seg[ext_addr7<5>(s, st, rem, lane)];
-        const uint32_t m = s.mark[vtx];
+        m = s.mark[vtx];
         cb1 = code_bits7(m, 5);
         cb2 = code_bits7(m, 6);
         row = s.urow[vtx];
         deg = s.urow[vtx + 1] - row;
     }
     if (!inE) deg = 0;
-    if (inE) w7.etag[vtx] = (uint8_t)(0x80u | (uint32_t)lane);
+    if (inE) s.mark[vtx] = (MarkT<7, V>)(m | ((uint32_t)(lane + 1) << kTagShift7));
     __syncthreads();
     auto tbits = [](uint32_t tt) { return ((Code7)(tt & 1u) << B_WU) | ((Code7)(tt >> 1) << B_UW); };
 
@@ -433,12 +439,12 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
             if (e2 < bdeg) {
                 const uint32_t ent = s.uadj[brow + e2];
                 const int u = (int)(ent >> 2);
-                const uint32_t tg = w7.etag[u];
+                const uint32_t mu = s.mark[u], tg = mu >> kTagShift7;
                 tt = ent & 3u;
-                if (tg & 0x80u) {
-                    q = (int)(tg & 63u);
+                if (tg) {
+                    q = (int)tg - 1;
                     arc = q > l;
-                } else if (u > s.root && s.mark[u] == 0u) {
+                } else if (u > s.root && mu == 0u) {
                     tb = tt;
                 }
             }
@@ -476,13 +482,13 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
         if (valid) {
             const uint32_t ent = s.uadj[r1 + off];
             const int u = (int)(ent >> 2);
-            const uint32_t tg = w7.etag[u];
+            const uint32_t mu = s.mark[u], tg = mu >> kTagShift7;
             tt = ent & 3u;
-            if (tg & 0x80u) {
-                q = (int)(tg & 63u);
+            if (tg) {
+                q = (int)tg - 1;
                 arc = q > src1;
             } else {
-                bv = u > s.root && s.mark[u] == 0u;
+                bv = u > s.root && mu == 0u;
             }
         }
         const Code7 cm = code | c1 | from_lane64(cb2, q);
@@ -539,7 +545,7 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
         }
         hash7_insert(s, w7, t, valid, c, w);
     }
-    if (inE) w7.etag[vtx] = 0;
+    if (inE) s.mark[vtx] = (MarkT<7, V>)m;
     __syncthreads();
 }
 
@@ -564,7 +570,7 @@ __device__ __forceinline__ void last_two7(EnumState<7, V> &s, K7Wave &w7, const 
     }
     const int hi = e < jhi ? e : jhi;
     if (jlo >= hi) return;
-    if (e <= kWave && hi == e) {
+    if (e <= kTagMax7 && hi == e) {
         last_two7_cells(s, w7, t, st, rem, e, code, jlo);
         return;
     }
@@ -724,8 +730,7 @@ __device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const 
 }
 
 // this kernel's part of a wave's LDS, after the shared layout: the hash
-// (u64 keys, u32 counts), the cell table (2 x u64 + u32 per cell), the
-// extension tags (a byte per vertex)
+// (u64 keys, u32 counts), the cell table (2 x u64 + u32 per cell)
 static __host__ __device__ int k7_hash_offset(int max_n, int seg_cap, bool global)
 {
     return (lds_layout(7, max_n, seg_cap, 0, global ? kVarGlobal : 0).total + 7) & ~7;
@@ -737,14 +742,8 @@ static __host__ __device__ int k7_cells_offset(int max_n, int seg_cap, bool glob
            kHash7Slots * (int)(sizeof(Code7) + sizeof(uint32_t));
 }
 
-static __host__ __device__ int k7_tags_offset(int max_n, int seg_cap, bool global)
-{
-    return k7_cells_offset(max_n, seg_cap, global) +
-           kWave * (int)(2 * sizeof(Code7) + sizeof(uint32_t));
-}
-
-// V = 0: LDS marks and tags, bit-matrix arc tests; V = kVarSearch |
-// kVarGlobal: marks and tags in device memory, arc tests on the lists
+// V = 0: LDS marks, bit-matrix arc tests; V = kVarSearch | kVarGlobal: marks
+// in device memory, arc tests on the lists
 template <int V>
 __global__ __launch_bounds__(kWave) void k7_kernel(const DevGraph *graphs, const int4 *units,
                                                    uint32_t unit_cap, uint32_t unit_end,
@@ -762,13 +761,6 @@ __global__ __launch_bounds__(kWave) void k7_kernel(const DevGraph *graphs, const
     w7.cc1 = reinterpret_cast<Code7 *>(base + k7_cells_offset(cfg.max_n, cfg.seg_cap, kGlobal));
     w7.cc2 = w7.cc1 + kWave;
     w7.csz = reinterpret_cast<uint32_t *>(w7.cc2 + kWave);
-    if constexpr (kGlobal) {
-        // zeroed when allocated; every small node clears the tags it set
-        w7.etag = t.etag + (size_t)blockIdx.x * t.etag_stride;
-    } else {
-        w7.etag = reinterpret_cast<uint8_t *>(base + k7_tags_offset(cfg.max_n, cfg.seg_cap, false));
-        for (int i = lane_id(); i < cfg.max_n; i += kWave) w7.etag[i] = 0;
-    }
     w7.hused = 0;
     w7.hpending = 0;
     w7.graph = 0;
@@ -812,8 +804,8 @@ __global__ void k7_collect_kernel(const Code7 *class_key, const unsigned long lo
 
 int k7_lds_bytes(int max_n, int seg_cap, int variant)
 {
-    const bool global = (variant & kVarGlobal) != 0;
-    return k7_tags_offset(max_n, seg_cap, global) + (global ? 0 : ((max_n + 3) & ~3));
+    return k7_cells_offset(max_n, seg_cap, (variant & kVarGlobal) != 0) +
+           kWave * (int)(2 * sizeof(Code7) + sizeof(uint32_t));
 }
 
 static const void *k7_fn(int variant)
@@ -850,12 +842,10 @@ int launch_k7(const DevGraph *d_graphs, const int4 *units, uint32_t unit_cap, ui
     t.totals = a.totals;
     t.overflow = a.overflow;
     t.cache_used = a.cache_used;
-    t.etag = a.etag;
-    t.etag_stride = a.etag_stride;
     const void *fn = k7_fn(cfg.variant);
     if (!fn) return fail(MK_ERANGE, "no k = 7 kernel for variant %d", cfg.variant);
-    if ((cfg.variant & kVarGlobal) != 0 && (!cfg.marks || !a.etag))
-        return fail(MK_EINVAL, "launch_k7: device-memory variant without marks or tags");
+    if ((cfg.variant & kVarGlobal) != 0 && !cfg.marks)
+        return fail(MK_EINVAL, "launch_k7: device-memory variant without marks");
     const uint32_t end = kAllUnits;
     EnumConfig c = cfg;
     void *args[] = {(void *)&d_graphs, (void *)&units, (void *)&unit_cap, (void *)&end,
