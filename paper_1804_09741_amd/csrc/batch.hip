@@ -317,15 +317,16 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
 // 0.7 ms, 101 such graphs 16 against 54 ms.)  A core costs about the same
 // whatever it closes, so the counting pays where cores close many k-sets:
 // where a vertex reached along an edge has many neighbours, q = sum d^2 / sum
-// d of them, and four members' neighbours hardly overlap.  Pass times by
-// enumeration and from the (k-2)-sets over 90 graphs and batches of n =
-// 100..5000, m = 1.2 n..6 n: with n >= 40 q the ratio is 0.9 to 4.6 for up to
-// 15 graphs (n = 5000, m = 30000: 510 and 78 ms; n = 700, m = 1500: 1.0 and
-// 0.5 ms), below that 0.4 to 1.3 (n = 172, m = 609: 0.55 and 0.63 ms).
-// Batches of 16 and more light graphs fill the chip either way and add the
-// division's pass over the bins: 0.75 to 0.95 with q up to 6.5 (31 graphs of
-// n = 700, m = 1500: 2.95 and 3.1 ms), 1.02 to 1.7 from 7.5 on (16 of n =
-// 1142, m = 1737: 10.7 and 6.3 ms).
+// d of them, and four members' neighbours hardly overlap; and the
+// enumeration's marks leave it fewer waves the larger n is.  Pass times by
+// enumeration over those from the (k-2)-sets, 140 graphs and batches of n =
+// 100..5000, m = 1.2 n..6 n: one graph of 100..1000 vertices 0.4 to 1.1 (n =
+// 700, m = 3850: 7.7 and 16.8 ms), of 1250 and 1500 mostly 1.05 to 1.25 (0.8
+// at the least), of 2200 to 5000 1.15 to 3.5 (n = 5000, m = 30000: 304 and 78
+// ms).  From 8 graphs on, where the division's pass over the bins is the
+// smaller part: n = 700 0.85 to 1.02, 850 0.93 to 1.1, 1000 0.99 to 1.28 (20
+// of m = 3500: 56 and 45 ms), 1250 1.13 to 1.25.  With q of 5 to 6.5 (n =
+// 700, m = 1.6 n..2.2 n) 0.73 to 0.95 in every batch.
 static bool cores6(const mk_batch *b)
 {
     double d1 = 0, d2 = 0;
@@ -334,7 +335,7 @@ static bool cores6(const mk_batch *b)
         d2 += (double)g->sum_d2;
     }
     const double q = d1 > 0 ? d2 / d1 : 0.0;
-    return 40.0 * q <= (double)b->max_n && (b->ng < 16 || q >= 7.5);
+    return q >= 7.5 && b->max_n >= (b->ng < 8 ? 1200 : 900);
 }
 
 // A batch of ng graphs for subgraph size k: counted with table t (k <= 6),

@@ -1,6 +1,6 @@
 """The library's choice of method at k = 6 on both sides of its rule (the
-degrees of the batch against its vertex count, and the number of graphs), on
-loaded and on device-made graphs, against the oracle."""
+degrees of the batch, its vertex count, and the number of graphs), on loaded
+and on device-made graphs, against the oracle."""
 
 import numpy as np
 import pytest
@@ -27,15 +27,15 @@ def _union(spec, n):
     return np.concatenate([rp, np.full(n - len(rp) + 1, rp[-1], rp.dtype)]), col
 
 
-# a hub-heavy core graph padded with isolated vertices moves n past 40 q
+# a hub-heavy core graph padded with isolated vertices past the rule's n
 @pytest.mark.parametrize("pad,randoms,method", [
-    (0, 0, M.METHOD_ESU), (900, 0, M.METHOD_CORES), (900, 14, M.METHOD_CORES),
-    (900, 15, M.METHOD_CORES), (0, 15, M.METHOD_ESU), (8192, 0, M.METHOD_CORES),
-    (8193, 0, M.METHOD_ESU)])
+    (0, 0, M.METHOD_ESU), (1199, 0, M.METHOD_ESU), (1200, 0, M.METHOD_CORES),
+    (900, 6, M.METHOD_ESU), (900, 7, M.METHOD_CORES), (899, 7, M.METHOD_ESU),
+    (0, 15, M.METHOD_ESU), (8192, 0, M.METHOD_CORES), (8193, 0, M.METHOD_ESU)])
 def test_choice_and_counts(ctx, pad, randoms, method):
     spec = I.chung_lu_digraph(80, 190, 2.1, 40, 0.2, np.random.default_rng([61, 3]))
     q = _q(*spec)
-    assert 7.5 < q and 40 * q > 80 and 40 * q < 900
+    assert 7.5 < q
     if pad:
         spec = _union(spec, pad)
     t = ctx.table(6)
@@ -55,15 +55,15 @@ def test_choice_and_counts(ctx, pad, randoms, method):
             h.free()
 
 
-def test_light_batch_enumerates(ctx):
-    spec = I.er_digraph(300, 500, np.random.default_rng(8))
+def test_light_graphs_enumerate(ctx):
+    spec = _union(I.er_digraph(300, 500, np.random.default_rng(8)), 1200)
     assert _q(*spec) < 7.5
     t = ctx.table(6)
-    gs = [ctx.load_graph(*spec) for _ in range(16)]
+    gs = [ctx.load_graph(*spec) for _ in range(8)]
     try:
-        for ng, method in ((15, M.METHOD_CORES), (16, M.METHOD_ESU)):
+        for ng in (1, 8):
             b = ctx.batch(gs[:ng], t)
-            assert b.stats()["method"] == method
+            assert b.stats()["method"] == M.METHOD_ESU
             b.free()
     finally:
         for g in gs:
