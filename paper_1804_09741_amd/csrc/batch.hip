@@ -29,6 +29,7 @@ struct mk_batch {
     mk_batch_opts opts{};
     int32_t debug_flags = 0;  // test hooks (mk_batch_debug)
 
+    unsigned char *d_plan = nullptr;  // d_graphs .. d_unit_begin, one allocation
     DevGraph *d_graphs = nullptr;
     uint32_t *d_ws = nullptr;  // bit matrices (or list-build arrays), urow, uadj
     uint64_t bits_words = 0;   // MK_ADJ_BITS: words of all bit matrices
@@ -183,10 +184,7 @@ static void batch_release(mk_batch *b)
         if (e) (void)hipEventDestroy(e);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    void *bufs[] = {b->d_graphs, b->d_ws, b->d_slot_cnt, b->d_slot_off, b->d_slot_est,
-                    b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                    b->d_units, b->d_counters, b->d_unit_begin, b->d_hist_own, b->d_wave_scratch,
-                    b->d_marks};
+    void *bufs[] = {b->d_plan, b->d_ws, b->d_units, b->d_hist_own, b->d_wave_scratch, b->d_marks};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
 }
@@ -242,10 +240,10 @@ static uint32_t slice_least(const mk_batch *b)
 
 // enqueue the preparation part of one pass on stream: counters and
 // histograms cleared, typed adjacency, work-unit plan (captured as a
-// hipGraph); a planned threshold is the sizing plan's, so d_slot_off keeps
-// that plan's offsets.  (Clearing the histograms from extra workgroups of the
-// latency-bound plan passes instead was measured slower: the streaming
-// stores raise the latency of the passes' dependent loads.)
+// hipGraph); where a sizing plan was made, its threshold is taken and
+// d_slot_off keeps its offsets.  (Clearing the histograms from extra
+// workgroups of the latency-bound plan passes instead was measured slower:
+// the streaming stores raise the latency of the passes' dependent loads.)
 static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t stream)
 {
     ClearRange bins{nullptr, 0};
@@ -336,6 +334,13 @@ static bool cores6(const mk_batch *b)
     }
     const double q = d1 > 0 ? d2 / d1 : 0.0;
     return q >= 7.5 && b->max_n >= (b->ng < 8 ? 1200 : 900);
+}
+
+// units of a graph in a plan for sets of plan_k <= 3 vertices: one per vertex
+// with a neighbour, or one per adjacent pair
+static uint64_t plan_units(int plan_k, const mk_graph *g)
+{
+    return plan_k == 2 ? (uint64_t)g->covered : (uint64_t)g->nnz_u / 2;
 }
 
 // A batch of ng graphs for subgraph size k: counted with table t (k <= 6),
@@ -488,19 +493,35 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
             hg[i] = d;
         }
     }
-    BAIL_HIP(hipMalloc(&b->d_graphs, sizeof(DevGraph) * std::max(ng, 1)));
+    // the descriptors and the planner's arrays in one allocation (nine took a
+    // fifth of a small blocking count)
+    size_t plan_bytes = 0;
+    const auto place = [&](size_t bytes) {
+        const size_t at = plan_bytes;
+        plan_bytes += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t slot_bytes = sizeof(uint32_t) * slots;
+    const size_t o_graphs = place(sizeof(DevGraph) * (size_t)ng), o_cnt = place(slot_bytes),
+                 o_off = place(slot_bytes), o_est = place(slot_bytes), o_vi = place(slot_bytes),
+                 o_l2 = place(slot_bytes),
+                 o_tmp = place(sizeof(uint32_t) * plan_tmp_words(ng, b->max_nnz, (uint32_t)slots)),
+                 o_counters = place(sizeof(uint32_t) * kNumCounters),
+                 o_begin = place(sizeof(uint32_t) * ((size_t)ng + 1));
+    BAIL_HIP(hipMalloc(&b->d_plan, plan_bytes));
+    const auto words = [&](size_t at) { return reinterpret_cast<uint32_t *>(b->d_plan + at); };
+    b->d_graphs = reinterpret_cast<DevGraph *>(b->d_plan + o_graphs);
+    b->d_slot_cnt = words(o_cnt);
+    b->d_slot_off = words(o_off);
+    b->d_slot_est = words(o_est);
+    b->d_slot_vi = words(o_vi);
+    b->d_slot_l2 = words(o_l2);
+    b->d_scan_tmp = words(o_tmp);
+    b->d_counters = words(o_counters);
+    b->d_unit_begin = words(o_begin);
     if (ng > 0)
         BAIL_HIP(hipMemcpyAsync(b->d_graphs, hg.data(), sizeof(DevGraph) * ng,
                                 hipMemcpyHostToDevice, ctx->stream));
-    BAIL_HIP(hipMalloc(&b->d_slot_cnt, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_slot_off, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_slot_est, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_slot_vi, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_slot_l2, sizeof(uint32_t) * std::max<uint64_t>(slots, 1)));
-    BAIL_HIP(hipMalloc(&b->d_scan_tmp,
-                       sizeof(uint32_t) * plan_tmp_words(ng, b->max_nnz, (uint32_t)slots)));
-    BAIL_HIP(hipMalloc(&b->d_counters, sizeof(uint32_t) * kNumCounters));
-    BAIL_HIP(hipMalloc(&b->d_unit_begin, sizeof(uint32_t) * ((size_t)ng + 1)));
     for (hipEvent_t &e : b->ev) BAIL_HIP(hipEventCreate(&e));
 
     int per_cu = 0;
@@ -523,28 +544,38 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         b->max_grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, fit);
     }
 
-    // sizing pass: typed adjacency + unit counts only
-    rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
-                      ctx->stream);
-    if (!rc) rc = batch_enqueue_typed(b, ctx->stream);
-    if (!rc)
-        rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
-                         b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                         nullptr, 0, b->opts.split_threshold, 0, false,
-                         slice_least(b), (uint32_t)b->max_grid,
-                         (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
-                         ctx->stream);
-    if (rc) return bail(rc);
-    uint32_t cnt[kNumCounters];
-    BAIL_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost, ctx->stream));
-    BAIL_HIP(hipStreamSynchronize(ctx->stream));
-    if (cnt[kAdjOverflow] != 0)
-        return bail(fail(MK_EDEVICE, "typed adjacency exceeds its reserved size"));
-    b->units = cnt[kNumUnits];
-    b->split_pairs = cnt[kSplitPairs];
-    // the same graphs plan to the same threshold at every pass
-    std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
-    b->unit_cap = std::max<uint32_t>(cnt[kNumUnits], 1);
+    if (b->plan_k <= 3) {
+        // Plans for 2- and 3-sets cut no node, so the graphs tell their units
+        // and no sizing pass is needed: its ten launches and a wait were a
+        // third of a small blocking count (k = 3, n = 200: with the one allocation
+        // above 199 -> 121 us).
+        for (int i = 0; i < ng; ++i) b->units += plan_units(b->plan_k, gs[i]);
+        b->spec_threshold = b->opts.split_threshold;
+        BAIL_HIP(hipStreamSynchronize(ctx->stream));  // the descriptors are on the device
+    } else {
+        // sizing pass: typed adjacency + unit counts only
+        rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
+                          ctx->stream);
+        if (!rc) rc = batch_enqueue_typed(b, ctx->stream);
+        if (!rc)
+            rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
+                             b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
+                             nullptr, 0, b->opts.split_threshold, 0, false,
+                             slice_least(b), (uint32_t)b->max_grid,
+                             (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
+                             ctx->stream);
+        if (rc) return bail(rc);
+        uint32_t cnt[kNumCounters];
+        BAIL_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost, ctx->stream));
+        BAIL_HIP(hipStreamSynchronize(ctx->stream));
+        if (cnt[kAdjOverflow] != 0)
+            return bail(fail(MK_EDEVICE, "typed adjacency exceeds its reserved size"));
+        b->units = cnt[kNumUnits];
+        b->split_pairs = cnt[kSplitPairs];
+        // the same graphs plan to the same threshold at every pass
+        std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
+    }
+    b->unit_cap = std::max<uint32_t>((uint32_t)b->units, 1);
     b->grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, std::max<uint64_t>(b->units, 1));
     if (t && !lean)
         b->layout = hist_layout(ng, t->num_classes, b->grid, b->method == MK_METHOD_CORES);
@@ -778,6 +809,11 @@ int batch_unit_begins(mk_batch *b, std::vector<uint32_t> *out)
     MK_HIP(hipSetDevice(b->ctx->device));
     out->assign((size_t)b->ng + 1, 0u);
     if (b->ng == 0) return MK_OK;
+    if (b->plan_k <= 3) {
+        for (int i = 0; i < b->ng; ++i)
+            (*out)[i + 1] = (*out)[i] + (uint32_t)plan_units(b->plan_k, b->graphs[i]);
+        return MK_OK;
+    }
     int rc = launch_unit_begins(b->d_graphs, b->ng, b->d_slot_off, b->total_slots, b->d_counters,
                                 b->d_unit_begin, b->ctx->stream);
     if (rc) return rc;

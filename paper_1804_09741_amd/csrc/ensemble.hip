@@ -429,6 +429,7 @@ extern "C" int mk_randomise(mk_ctx *ctx, const mk_graph *g, int32_t count, uint6
         made[r]->nnz_u = (int64_t)hs[4 * r + 1];
         made[r]->max_udeg = (int32_t)hs[4 * r + 2];
         made[r]->sum_d2 = (int64_t)hs[4 * r + 3];
+        made[r]->covered = g->covered;  // switches keep every vertex's degrees
         if (made[r]->max_udeg > MK_MAX_DEGREE) {
             cleanup(true);
             return fail(MK_ERANGE, "random graph %d has undirected degree %d > MK_MAX_DEGREE=%d", r,

@@ -52,6 +52,7 @@ struct Graph {
     int64_t nnz_u = 0;        // sum of undirected degrees |delta(v)|
     int32_t max_udeg = 0;
     int64_t sum_d2 = 0;       // sum of squared undirected degrees
+    int32_t covered = 0;      // vertices with a neighbour
     int32_t *d_row = nullptr; // n+1, out-adjacency CSR as given
     int32_t *d_col = nullptr; // m
 };

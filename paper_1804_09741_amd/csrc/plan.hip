@@ -167,6 +167,7 @@ __device__ __forceinline__ uint64_t effective_threshold(const PlanGraph &g, uint
                                                         uint64_t floor_t, uint32_t waves,
                                                         uint32_t upw)
 {
+    if (K <= 3) return floor_t;  // no node is cut
     uint64_t total = 0;
 #pragma unroll
     for (int x = 0; x < kQueues; ++x)
