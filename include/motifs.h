@@ -268,8 +268,9 @@ typedef struct mk_batch_opts {
      of one class at once, each arc inside adj(X) moves one k-set to its
      true class, and the sums are divided by the cores per class
      (mk_table_core_mult). */
-/* MK_METHOD_AUTO: MK_METHOD_CORES for k <= 5 and, by the batch's degrees and
-   number of graphs, for k = 6 where it is the faster; MK_METHOD_ESU else and
+/* MK_METHOD_AUTO: MK_METHOD_CORES for k <= 5 and, by the batch's degrees,
+   vertex count and number of graphs, for k = 6 where it is the faster;
+   MK_METHOD_ESU else and
    for graphs with more than MK_LDS_MARKS_MAX_VERTICES vertices (which
    MK_METHOD_CORES rejects with MK_ERANGE). */
 #define MK_METHOD_AUTO 0
@@ -293,8 +294,8 @@ typedef struct mk_batch_opts {
 
 /* Per-vertex marks of each wave (every vertex's relation to the current
    members).
-   MK_MARKS_LDS: in LDS, 2 bytes per vertex for k <= 5 and 4 for k = 6;
-     needs n <= MK_LDS_MARKS_MAX_VERTICES.
+   MK_MARKS_LDS: in LDS, 2 bytes per vertex (1 by MK_METHOD_CORES); needs
+     n <= MK_LDS_MARKS_MAX_VERTICES.
    MK_MARKS_GLOBAL: a private n-entry array per wave in device memory, 4
      bytes per vertex (kept zero between work units; fewer waves when they
      would take more than 1/16 of the device memory); needs MK_ADJ_LISTS and
