@@ -130,8 +130,7 @@ extern "C" void mk_destroy(mk_ctx *ctx)
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
     for (int k = 0; k < 7; ++k) free_table(ctx->tables[k]);
-    if (ctx->k7_cache_key) (void)hipFree(ctx->k7_cache_key);
-    if (ctx->k7_cache_val) (void)hipFree(ctx->k7_cache_val);
+    if (ctx->k7_cache) (void)hipFree(ctx->k7_cache);
     if (ctx->k7_cache_used) (void)hipFree(ctx->k7_cache_used);
     (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1056,8 +1055,7 @@ constexpr int kK7CacheLog2 = 22;
 static int k7_cache_clear(mk_ctx *ctx, hipStream_t st)
 {
     const size_t cache_slots = (size_t)1 << kK7CacheLog2;
-    int rc = fill_u32(ctx->k7_cache_key, 0xFFFFFFFFu, 2 * cache_slots, st);
-    if (!rc) rc = fill_u32(ctx->k7_cache_val, 0xFFFFFFFFu, 2 * cache_slots, st);
+    int rc = fill_u32(ctx->k7_cache, 0xFFFFFFFFu, 4 * cache_slots, st);
     if (!rc) rc = fill_u32(ctx->k7_cache_used, 0u, 1, st);
     if (!rc) ctx->k7_cache_fill = 0;
     return rc;
@@ -1067,8 +1065,8 @@ extern "C" int mk_k7_cache_info(mk_ctx *ctx, uint64_t *slots, uint64_t *used)
 {
     if (!ctx) return fail(MK_EINVAL, "mk_k7_cache_info: NULL context");
     std::lock_guard<std::recursive_mutex> lock(ctx->mu);
-    if (slots) *slots = ctx->k7_cache_key ? (uint64_t)1 << kK7CacheLog2 : 0;
-    if (used) *used = ctx->k7_cache_key ? ctx->k7_cache_fill : 0;
+    if (slots) *slots = ctx->k7_cache ? (uint64_t)1 << kK7CacheLog2 : 0;
+    if (used) *used = ctx->k7_cache ? ctx->k7_cache_fill : 0;
     return MK_OK;
 }
 
@@ -1076,7 +1074,7 @@ extern "C" int mk_k7_cache_clear(mk_ctx *ctx)
 {
     if (!ctx) return fail(MK_EINVAL, "mk_k7_cache_clear: NULL context");
     std::lock_guard<std::recursive_mutex> lock(ctx->mu);
-    if (!ctx->k7_cache_key) return MK_OK;
+    if (!ctx->k7_cache) return MK_OK;
     MK_HIP(hipSetDevice(ctx->device));
     int rc = k7_cache_clear(ctx, ctx->stream);
     if (rc) return rc;
@@ -1111,21 +1109,18 @@ static int count7_once(mk_batch *b, int class_log2, int64_t cap, uint64_t *codes
     // the canonical-code cache of the context: made and cleared once, then
     // kept warm across counts (its entries do not depend on the graphs)
     hipError_t e = hipSuccess;
-    if (!ctx->k7_cache_key) {
-        unsigned long long *ck = nullptr, *cv = nullptr;
+    if (!ctx->k7_cache) {
+        unsigned long long *ck = nullptr;
         uint32_t *cu = nullptr;
-        e = hipMalloc(&ck, 8 * cache_slots);
-        if (e == hipSuccess) e = hipMalloc(&cv, 8 * cache_slots);
+        e = hipMalloc(&ck, 16 * cache_slots);
         if (e == hipSuccess) e = hipMalloc(&cu, 4);
         if (e != hipSuccess) {
             if (ck) (void)hipFree(ck);
-            if (cv) (void)hipFree(cv);
             if (cu) (void)hipFree(cu);
             return fail(e == hipErrorOutOfMemory ? MK_ENOMEM : MK_EDEVICE,
                         "mk_count7: cache allocation: %s", hipGetErrorString(e));
         }
-        ctx->k7_cache_key = ck;
-        ctx->k7_cache_val = cv;
+        ctx->k7_cache = ck;
         ctx->k7_cache_used = cu;
         ctx->k7_cache_fill = cache_slots;  // forces the clear below
     }
@@ -1135,8 +1130,7 @@ static int count7_once(mk_batch *b, int class_log2, int64_t cap, uint64_t *codes
         int frc = k7_cache_clear(ctx, st);
         if (frc) return frc;
     }
-    a.cache_key = ctx->k7_cache_key;
-    a.cache_val = ctx->k7_cache_val;
+    a.cache = ctx->k7_cache;
     a.cache_used = ctx->k7_cache_used;
     e = alloc((void **)&a.class_key, 8 * class_slots);
     if (e == hipSuccess) e = alloc((void **)&a.class_cnt, 8 * class_slots);

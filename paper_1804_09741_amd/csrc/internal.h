@@ -151,7 +151,7 @@ struct Ctx {
     int k7_class_log2 = 10;  // class-table size of the last k = 7 count (grows as needed)
     // k = 7 canonical-code cache (labelled code -> canonical code; 2^22
     // slots each, made by the first count and kept: it holds no graph data)
-    unsigned long long *k7_cache_key = nullptr, *k7_cache_val = nullptr;
+    unsigned long long *k7_cache = nullptr;  // pairs (k7.hip)
     uint32_t *k7_cache_used = nullptr;  // device: slots claimed since the last clear
     uint64_t k7_cache_fill = 0;         // host copy, read back after every count
     std::recursive_mutex mu;
@@ -219,7 +219,7 @@ int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32
 // Enumeration + code + lookup + histogram over the queued units.
 // k = 7 (k7.hip): device tables of one count
 struct K7Launch {
-    unsigned long long *cache_key, *cache_val;  // labeled -> canonical code
+    unsigned long long *cache;                  // labeled code, canonical code pairs
     int cache_log2;                              // log2 of the cache slots
     unsigned long long *class_key, *class_cnt;  // per graph: canonical code -> count
     int class_log2;                              // log2 of the class slots per graph

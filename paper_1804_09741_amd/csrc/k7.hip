@@ -32,8 +32,8 @@ constexpr int kCacheProbes = 32;
 constexpr int kClassProbes = 64;
 
 struct K7Tables {
-    Code7 *cache_key;              // labeled code (kNoCode: free)
-    Code7 *cache_val;              // its canonical code (kNoCode: not written yet)
+    Code7 *cache;                  // per slot: labeled code (kNoCode: free) and its
+                                   //   canonical code (kNoCode: not written yet)
     int cache_shift;               // 64 - log2(cache slots)
     uint32_t cache_mask;
     Code7 *class_key;              // per graph class_mask + 1 canonical codes
@@ -52,8 +52,7 @@ struct K7Wave {
     int hused;
     uint32_t hpending;
     int graph;
-    Code7 *cc1, *cc2;  // per cell of E: code bits at positions 5 and 6
-    uint32_t *csz;     //   and its size
+    uint32_t *cell;    // per cell of E: its vertices' mark | its size << 16
 };
 
 __device__ __forceinline__ uint32_t hash7(Code7 c, int shift)
@@ -199,7 +198,10 @@ __device__ __forceinline__ Code7 canon7_wave(Code7 code)
 }
 
 // Move the wave's pending counts to its graph's class table: canonical code
-// from the cache (or computed and entered), count added; hash emptied.
+// from the cache (or computed and entered), count added; hash emptied.  (The
+// cache's code and value in one 16-byte read and no compare-and-swap on a
+// class that is there: 131,073 vertices on lists 293 -> 288 ms, 16 graphs of
+// n = 700 the same.)
 template <int V>
 __device__ __forceinline__ void flush7(EnumState<7, V> &s, K7Wave &w, const K7Tables &t)
 {
@@ -217,12 +219,12 @@ __device__ __forceinline__ void flush7(EnumState<7, V> &s, K7Wave &w, const K7Ta
         if (live) {
             uint32_t h = hash7(key, t.cache_shift);
             for (int p = 0; p < kCacheProbes; ++p) {
-                const Code7 k2 = t.cache_key[h];
-                if (k2 == key) {
-                    canon = t.cache_val[h];
+                const ulonglong2 e = reinterpret_cast<const ulonglong2 *>(t.cache)[h];
+                if (e.x == key) {
+                    canon = e.y;
                     break;
                 }
-                if (k2 == kNoCode) break;
+                if (e.x == kNoCode) break;
                 h = (h + 1) & t.cache_mask;
             }
         }
@@ -240,9 +242,9 @@ __device__ __forceinline__ void flush7(EnumState<7, V> &s, K7Wave &w, const K7Ta
             // reader that meets the key before the value computes it again
             uint32_t h = hash7(key, t.cache_shift);
             for (int p = 0; p < kCacheProbes; ++p) {
-                const Code7 old = atomicCAS(&t.cache_key[h], kNoCode, key);
+                const Code7 old = atomicCAS(&t.cache[2 * (size_t)h], kNoCode, key);
                 if (old == kNoCode) {
-                    atomicExch(&t.cache_val[h], canon);
+                    atomicExch(&t.cache[2 * (size_t)h + 1], canon);
                     claimed = true;
                     break;
                 }
@@ -258,7 +260,10 @@ __device__ __forceinline__ void flush7(EnumState<7, V> &s, K7Wave &w, const K7Ta
             uint32_t h = hash7(canon, t.class_shift);
             bool done = false;
             for (int p = 0; p < kClassProbes && !done; ++p) {
-                const Code7 old = atomicCAS(&ckey[h], kNoCode, canon);
+                // a slot's key is written once, so a plain read that finds it
+                // is current; one that finds none may not be
+                Code7 old = ckey[h];
+                if (old == kNoCode) old = atomicCAS(&ckey[h], kNoCode, canon);
                 if (old == kNoCode || old == canon) {
                     atomicAdd(&ccnt[h], add);
                     done = true;
@@ -517,9 +522,7 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
     const int ncell = __popcll(leaders);
     if (leader) {
         const int rk = (int)lanes_below(leaders);
-        w7.cc1[rk] = cb1;
-        w7.cc2[rk] = cb2;
-        w7.csz[rk] = size;
+        w7.cell[rk] = m | (size << 16);
     }
     __syncthreads();
     const int mm = e - jlo;
@@ -538,9 +541,10 @@ __device__ __forceinline__ void last_two7_cells(EnumState<7, V> &s, K7Wave &w7, 
             if ((z + 1) * (z + 2) / 2 <= p) ++z;
             if (z * (z + 1) / 2 > p) --z;
             const int y = p - z * (z + 1) / 2;
-            const uint32_t ny = w7.csz[y], nz = w7.csz[z];
+            const uint32_t cy = w7.cell[y], cz = w7.cell[z];
+            const uint32_t ny = cy >> 16, nz = cz >> 16;
             w = y == z ? ny * (ny - 1u) / 2u : ny * nz;
-            c = code | w7.cc1[y] | w7.cc2[z];
+            c = code | code_bits7(cy, 5) | code_bits7(cz, 6);
             valid = w > 0u;
         }
         hash7_insert(s, w7, t, valid, c, w);
@@ -730,7 +734,7 @@ __device__ __forceinline__ void run_unit7(EnumState<7, V> &s, K7Wave &w7, const 
 }
 
 // this kernel's part of a wave's LDS, after the shared layout: the hash
-// (u64 keys, u32 counts), the cell table (2 x u64 + u32 per cell)
+// (u64 keys, u32 counts), the cell table (u32 per cell)
 static __host__ __device__ int k7_hash_offset(int max_n, int seg_cap, bool global)
 {
     return (lds_layout(7, max_n, seg_cap, 0, global ? kVarGlobal : 0).total + 7) & ~7;
@@ -743,9 +747,12 @@ static __host__ __device__ int k7_cells_offset(int max_n, int seg_cap, bool glob
 }
 
 // V = 0: LDS marks, bit-matrix arc tests; V = kVarSearch | kVarGlobal: marks
-// in device memory, arc tests on the lists
+// in device memory, arc tests on the lists.  V = 0 is held to 80 VGPRs, six
+// waves per SIMD, which its LDS then allows too at n = 700 (6.8 KB a wave; 16
+// graphs 31.6 -> 29.5 ms, with ten spilled registers); the other keeps its
+// 100 (24 would be spilled: 30,001 vertices 70.5 -> 74.5 ms).
 template <int V>
-__global__ __launch_bounds__(kWave) void k7_kernel(const DevGraph *graphs, const int4 *units,
+__global__ __launch_bounds__(kWave, V == 0 ? 6 : 4) void k7_kernel(const DevGraph *graphs, const int4 *units,
                                                    uint32_t unit_cap, uint32_t unit_end,
                                                    uint32_t *counters, K7Tables t, EnumConfig cfg)
 {
@@ -758,9 +765,7 @@ __global__ __launch_bounds__(kWave) void k7_kernel(const DevGraph *graphs, const
     K7Wave w7;
     w7.hkey = reinterpret_cast<Code7 *>(base + k7_hash_offset(cfg.max_n, cfg.seg_cap, kGlobal));
     w7.hcnt = reinterpret_cast<uint32_t *>(w7.hkey + kHash7Slots);
-    w7.cc1 = reinterpret_cast<Code7 *>(base + k7_cells_offset(cfg.max_n, cfg.seg_cap, kGlobal));
-    w7.cc2 = w7.cc1 + kWave;
-    w7.csz = reinterpret_cast<uint32_t *>(w7.cc2 + kWave);
+    w7.cell = reinterpret_cast<uint32_t *>(base + k7_cells_offset(cfg.max_n, cfg.seg_cap, kGlobal));
     w7.hused = 0;
     w7.hpending = 0;
     w7.graph = 0;
@@ -805,7 +810,7 @@ __global__ void k7_collect_kernel(const Code7 *class_key, const unsigned long lo
 int k7_lds_bytes(int max_n, int seg_cap, int variant)
 {
     return k7_cells_offset(max_n, seg_cap, (variant & kVarGlobal) != 0) +
-           kWave * (int)(2 * sizeof(Code7) + sizeof(uint32_t));
+           kWave * (int)sizeof(uint32_t);
 }
 
 static const void *k7_fn(int variant)
@@ -831,8 +836,7 @@ int launch_k7(const DevGraph *d_graphs, const int4 *units, uint32_t unit_cap, ui
 {
     if (grid <= 0) return MK_OK;
     K7Tables t;
-    t.cache_key = a.cache_key;
-    t.cache_val = a.cache_val;
+    t.cache = a.cache;
     t.cache_shift = 64 - a.cache_log2;
     t.cache_mask = (1u << a.cache_log2) - 1u;
     t.class_key = a.class_key;
