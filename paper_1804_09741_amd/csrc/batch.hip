@@ -252,9 +252,10 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
     if (rc) return rc;
     rc = batch_enqueue_typed(b, stream);
     if (rc) return rc;
+    const uint64_t spec = b->spec_threshold + ((uint32_t)b->debug_flags & kDebugPlanMiss ? 1u : 0u);
     return launch_plan(b->plan_k, b->d_graphs, b->ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                        b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                       b->d_units, b->unit_cap, b->opts.split_threshold, b->spec_threshold, true,
+                       b->d_units, b->unit_cap, b->opts.split_threshold, spec, true,
                        slice_least(b), (uint32_t)b->max_grid, (uint32_t)std::max(b->opts.units_per_wave, 0),
                        b->d_counters, stream);
 }
@@ -888,7 +889,7 @@ extern "C" int mk_batch_timing(mk_batch *b, double *pass_ms, double *enum_ms)
 extern "C" int mk_batch_debug(mk_batch *b, int32_t flags)
 {
     if (!b) return fail(MK_EINVAL, "mk_batch_debug: NULL batch");
-    if (flags & ~(int32_t)(kDebugNoHash | kDebugFlushAlways | kDebugNoShare))
+    if (flags & ~(int32_t)(kDebugNoHash | kDebugFlushAlways | kDebugNoShare | kDebugPlanMiss))
         return fail(MK_EINVAL, "mk_batch_debug: unknown flags %d", flags);
     std::lock_guard<std::recursive_mutex> lock(b->ctx->mu);
     if (b->debug_flags != flags) b->exec_hist = nullptr;  // captured with the old flags

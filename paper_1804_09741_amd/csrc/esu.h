@@ -551,7 +551,10 @@ __device__ __forceinline__ void unit_loop(EnumState<K, V> &s, const DevGraph *gr
                                           uint32_t *counters, const EnumConfig &cfg, Run run,
                                           Switch on_switch, After after_unit)
 {
-    const uint32_t navail = counters[kNumUnits];
+    // after an error of the planner the unit list has entries that were never
+    // written: such a launch takes none
+    const uint32_t failed = counters[kErrors] | counters[kAdjOverflow];
+    const uint32_t navail = failed ? 0u : counters[kNumUnits];
     const uint32_t cap = unit_cap < unit_end ? unit_cap : unit_end;
     const uint32_t end = navail < cap ? navail : cap;
     const uint32_t begin = counters[kSliceBegin];

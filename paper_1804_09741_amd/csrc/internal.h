@@ -207,7 +207,8 @@ int launch_typed_csr(const DevGraph *d_graphs, int ng, int max_n, int64_t max_m,
 // as spec_threshold (a batch passes the one its sizing plan of the same
 // graphs found, read from counters[kPlanThreshold]): there is no count pass,
 // and the emit pass finds its offsets itself where the estimate's workgroups
-// are few enough (a threshold that differs is a device error).  slice_least:
+// are few enough (a threshold that differs is a device error, and no unit is
+// written).  slice_least:
 // a child may be cut into units of its own children that cost this much at
 // least (plans for k >= 5; 0: children stay whole).
 int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
@@ -292,6 +293,7 @@ int core_hash_bits(int k);
 constexpr uint32_t kDebugNoHash = 1u;      // every code straight to the histogram
 constexpr uint32_t kDebugFlushAlways = 2u; // flush the hash after every insert
 constexpr uint32_t kDebugNoShare = 4u;     // core kernel: no per-parent arc lists
+constexpr uint32_t kDebugPlanMiss = 8u;    // sized plans: a threshold that will not come out
 // Arc pairs inside adj(P) kept per parent node P by the core kernel (global
 // memory, one list per workgroup); a parent with more uses the per-core scan.
 constexpr uint32_t kParentArcCap = 2048;

@@ -423,13 +423,17 @@ __global__ __launch_bounds__(kPlanThreadsFew) void plan_kernel(const DevGraph *g
         }
     }
     uint32_t first_unit = 0;  // emit: the slot's
+    uint32_t planned = 0;     //   and the units counted for it
     if (PASS == kEmit) {
+        planned = live ? slot_cnt[slot] : 0u;
         if (block_sums) {
-            first_unit = sized_offset(live ? slot_cnt[slot] : 0u, block_sums, counters);
+            // the counts are for another threshold: no unit is written, and
+            // counters[kNumUnits] stays zero
             if (threshold != spec_t) {
                 if (lead) atomicOr(&counters[kErrors], 1u);
                 return;
             }
+            first_unit = sized_offset(planned, block_sums, counters);
             if (lead) {
                 *reinterpret_cast<unsigned long long *>(counters + kPlanThreshold) = threshold;
                 counters[kSplitPairs] = spec_split_pairs(counters);
@@ -545,12 +549,16 @@ __global__ __launch_bounds__(kPlanThreadsFew) void plan_kernel(const DevGraph *g
         if (PASS == kCount) {
             if (cnt > 1) atomicAdd(&counters[kSplitPairs], 1u);
             slot_cnt[slot] = cnt;
-        } else if (cnt == 1 && !walk) {
-            if (first_unit < unit_cap)
-                units[first_unit] = make_int4(unit_x(gi, sest, threshold), (int)(vi & kViMask),
-                                              (int)(vi >> kViShift), (int)kFullChild);
-            else
-                atomicOr(&counters[kErrors], 1u);
+        } else {
+            // fewer or more than were counted leave holes in the unit list
+            if (cnt != planned) atomicOr(&counters[kErrors], 1u);
+            if (cnt == 1 && !walk) {
+                if (first_unit < unit_cap)
+                    units[first_unit] = make_int4(unit_x(gi, sest, threshold), (int)(vi & kViMask),
+                                                  (int)(vi >> kViShift), (int)kFullChild);
+                else
+                    atomicOr(&counters[kErrors], 1u);
+            }
         }
     }
 }

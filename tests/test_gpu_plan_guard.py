@@ -1,0 +1,47 @@
+"""A pass whose plan does not come out as the batch was sized ends as a device
+error: no work unit is taken (the unit list was not written), the histograms
+are empty, and the same batch counts again afterwards."""
+
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_hist_equals_oracle
+from paper_1804_09741_amd import inputs as I
+from paper_1804_09741_amd import motifs as M
+
+pytestmark = pytest.mark.gpu
+
+PLAN_MISS = 8
+
+
+@pytest.mark.parametrize("k,method", [(3, M.METHOD_CORES), (4, M.METHOD_ESU), (5, M.METHOD_CORES),
+                                      (5, M.METHOD_ESU), (6, M.METHOD_ESU), (6, M.METHOD_CORES)])
+@pytest.mark.parametrize("use_graph", [-1, 1, 2])
+def test_threshold_that_differs(ctx, k, method, use_graph):
+    import torch
+    t = ctx.table(k)
+    specs = [I.chung_lu_digraph(60, 150, 2.2, 25, 0.2, np.random.default_rng([85, i]))
+             for i in range(3)]
+    gs = [ctx.load_graph(*s) for s in specs]
+    b = ctx.batch(gs, t, method=method, use_graph=use_graph)
+    stream = torch.cuda.current_stream()
+    try:
+        d = torch.full((3, t.num_classes), 9, dtype=torch.int64, device="cuda:0")
+        # the first pass of the batch: its unit list holds nothing yet
+        M.mk_batch_debug(b.handle, PLAN_MISS)
+        for _ in range(2):
+            b.run(d, stream)
+            with pytest.raises(M.MotifsError) as e:
+                b.read()
+            assert e.value.status == M.MK_EDEVICE
+            assert not d.any().item()
+        M.mk_batch_debug(b.handle, 0)
+        for _ in range(2):
+            b.run(d, stream)
+            hist, _ = b.read()
+            for h, s in zip(hist, specs):
+                assert_hist_equals_oracle(h, t.class_codes(), *s, k)
+    finally:
+        b.free()
+        for g in gs:
+            g.free()
