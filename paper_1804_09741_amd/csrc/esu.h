@@ -61,9 +61,6 @@ constexpr int kScratchWords = 3 * kWave;
 #ifndef MK_HASH_BITS
 #define MK_HASH_BITS 8   // log2 of the per-wave hash slots
 #endif
-#ifndef MK_HEAVY_GRAB
-#define MK_HEAVY_GRAB 4  // units per grab of the first sweep, in grabs of the second
-#endif
 #ifndef MK_MERGE_ROUNDS
 #define MK_MERGE_ROUNDS 1  // ballot rounds merging equal codes before the hash
 #endif
@@ -558,16 +555,8 @@ __device__ __forceinline__ void unit_loop(EnumState<K, V> &s, const DevGraph *gr
     const uint32_t cap = unit_cap < unit_end ? unit_cap : unit_end;
     const uint32_t end = navail < cap ? navail : cap;
     const uint32_t begin = counters[kSliceBegin];
-    const uint32_t span = end > begin ? end - begin : 0u;
-    // units per grab: about 1/32 of a wave's share, 1..16
-    uint32_t chunk = cfg.chunk ? cfg.chunk : span / (gridDim.x * 32u);
-    chunk = chunk < 1u ? 1u : (chunk > 256u ? 256u : chunk);
-    if (!cfg.chunk && chunk > 16u) chunk = 16u;
-    // two sweeps only with at least 32 units per wave (a launch of one
-    // graph's units would leave most waves idle behind a few heavy grabs);
-    // the first sweep's grabs: MK_HEAVY_GRAB times as many units, at most 64
-    const bool two = HeavyFirst && span >= gridDim.x * 32u;
-    const uint32_t chunk0 = chunk * MK_HEAVY_GRAB < (uint32_t)kWave ? chunk * MK_HEAVY_GRAB : (uint32_t)kWave;
+    const UnitQueue q =
+        unit_queue(begin, end, gridDim.x, blockIdx.x, cfg.chunk, HeavyFirst, cfg.mix != 0);
     int cur = -1;
     auto take = [&](const int4 &u) {
         const int gi = uniform((int)((uint32_t)u.x & ~kHeavyBit));
@@ -583,39 +572,14 @@ __device__ __forceinline__ void unit_loop(EnumState<K, V> &s, const DevGraph *gr
         run(uniform(u.y), uniform(u.z), (uint32_t)uniform(u.w));
         after_unit();
     };
-    // Range x: the units [lo_x, lo_{x+1}) of the launch, or (mix) every eighth
-    // grab of all units.  A grab: its first unit and one past its last.
-    const int home = (int)(blockIdx.x % kQueues);
-    const bool mix = cfg.mix != 0;
-    // Ranges a wave looks into after its own.  A visit is an atomic on a head
-    // that all eight XCDs share, about 10 ns one after another, and most
-    // visits find the range empty.  So launches with many units a wave visit
-    // every range (the walk's time hides it, and ranges of unlike graphs
-    // need it); in the others a wave tries one, in turn.  8,327 units on 6,144
-    // waves (k = 4, n = 2000, m = 10000): 7 visits 0.181 ms of kernel, 2
-    // 0.109, 1 0.096, none 0.090; k = 5 by enumeration, n = 1000, m = 3000,
-    // 26,895 units on 7,168 waves: 0.62 ms with 1 or 2, 0.64 with none.
-    // (Launches of 8 waves and more have a home wave on every range, which
-    // empties it whoever else comes.)
-    const int tries =
-        span / gridDim.x >= 16u || gridDim.x < 8u * kQueues ? kQueues - 1 : 1;
-    const uint32_t turn = tries < kQueues - 1 ? blockIdx.x / kQueues : 0u;
-    for (int sweep = two ? 0 : 1; sweep < 2; ++sweep) {
-        const uint32_t ch = sweep == 0 ? chunk0 : chunk;
-        for (int t = 0; t <= tries; ++t) {
-            const int x = t == 0 ? home
-                                 : (int)((home + 1 + (turn + (uint32_t)t - 1u) % (kQueues - 1)) % kQueues);
+    for (int sweep = q.two ? 0 : 1; sweep < 2; ++sweep) {
+        for (int t = 0; t <= q.tries; ++t) {
+            const int x = queue_range(q, t);
             uint32_t *head = &counters[(sweep == 0 ? kHeavyHeads : kQueueHeads) + x * kHeadStride];
-            const uint32_t lo = mix ? begin + (uint32_t)x * ch : begin + (uint32_t)((uint64_t)span * x / kQueues);
-            const uint32_t hi = mix ? end : begin + (uint32_t)((uint64_t)span * (x + 1) / kQueues);
             for (;;) {
-                uint32_t idx = 0;
-                if (lane_id() == 0) idx = atomicAdd(head, ch);
-                idx = (uint32_t)uniform((int)idx) * (mix ? (uint32_t)kQueues : 1u);
-                if (idx >= span) break;  // also keeps lo + idx in 32 bits
-                idx += lo;
-                if (idx >= hi) break;
-                const uint32_t stop = idx + ch < hi ? idx + ch : hi;
+                uint32_t taken = 0, idx, stop;
+                if (lane_id() == 0) taken = atomicAdd(head, queue_chunk(q, sweep));
+                if (!queue_grab(q, x, sweep, (uint32_t)uniform((int)taken), idx, stop)) break;
                 if (sweep == 0) {
                     const uint32_t my = idx + (uint32_t)lane_id();
                     const bool heavy =
@@ -629,7 +593,7 @@ __device__ __forceinline__ void unit_loop(EnumState<K, V> &s, const DevGraph *gr
                 } else {
                     for (; idx < stop; ++idx) {
                         const int4 u = units[idx];
-                        if (two && ((uint32_t)u.x & kHeavyBit)) continue;
+                        if (q.two && ((uint32_t)u.x & kHeavyBit)) continue;
                         take(u);
                     }
                 }

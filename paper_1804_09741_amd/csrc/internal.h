@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "motifs.h"
+#include "queue.h"
 
 namespace mk {
 
@@ -136,7 +137,6 @@ enum Counter : int {
     kPlanSums = 16 + 2 * 8 * 16,  // the estimate pass's sums: a line per XCD (plan.hip)
     kNumCounters = kPlanSums + 8 * 32,
 };
-constexpr int kQueues = 8;       // one queue per XCD of the MI355X
 constexpr int kHeadStride = 16;  // 64 bytes: one cache line per head
 
 // --------------------------------------------------------------- context
