@@ -22,25 +22,12 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "plan_shape.h"
 #include "server_hooks.h"
 
 namespace mk {
 
-// A workgroup takes kPlanSlots slots, a thread each of its first wave; its
-// other waves join in the walks, where there are any (K > 3): 1,024 threads,
-// so that every node has a team of lanes of its own, where two such
-// workgroups fit each CU (94 workgroups, one graph of n = 1000 at k = 5: the
-// preparation 104 us, 176 with 256 threads), else 256 (9,500 workgroups, that
-// graph and 100 random versions: 338 us, 549 with 1,024).
-constexpr int kPlanSlots = kWave;
-constexpr int kPlanThreads = 256, kPlanThreadsFew = 1024;
-constexpr uint64_t kPlanFewBlocks = 512;
-
-static int plan_threads(int k, dim3 grid)
-{
-    if (k <= 3) return kPlanSlots;
-    return (uint64_t)grid.x * grid.y <= kPlanFewBlocks ? kPlanThreadsFew : kPlanThreads;
-}
+static_assert(kPlanSlots == kWave, "a workgroup's slots are its first wave's");
 
 // The estimate pass's sums at counters[kPlanSums], one line per XCD
 // (workgroup b runs on XCD b % kQueues; an add to a line that all XCDs share
@@ -569,8 +556,7 @@ constexpr uint32_t kSizedBlocks = kSumWindow * kSumWindows;
 
 static dim3 plan_grid(int ng, int64_t max_nnz)
 {
-    return dim3((unsigned)std::max<int64_t>((max_nnz + kPlanSlots - 1) / kPlanSlots, 1),
-                (unsigned)ng);
+    return dim3((unsigned)plan_blocks(max_nnz), (unsigned)ng);
 }
 
 size_t plan_tmp_words(int ng, int64_t max_nnz, uint32_t total_slots)
@@ -587,11 +573,11 @@ static int plan_k(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t to
                   uint64_t threshold, uint64_t spec, bool sized, uint32_t least, uint32_t waves,
                   uint32_t upw, uint32_t *counters, hipStream_t stream)
 {
-    const dim3 grid = plan_grid(ng, max_nnz), threads((unsigned)plan_threads(K, grid));
+    const dim3 grid = plan_grid(ng, max_nnz), threads(plan_threads(K, grid.x, grid.y));
     const uint64_t spec_t = spec ? spec : threshold;
     sized = sized && units && (uint64_t)grid.x * grid.y <= kSizedBlocks;
     uint32_t *sums = sized ? scan_tmp : nullptr;
-    // the estimate total (counters[kEstTotal]) starts at zero: the callers
+    // the estimate's sums (counters[kPlanSums]) start at zero: the callers
     // clear all counters before every plan
     hipLaunchKernelGGL((plan_kernel<K, kEstimate>), grid, threads, 0, stream, d_graphs,
                        slot_cnt, slot_off, slot_est, slot_vi, slot_l2, units, unit_cap, threshold,
