@@ -20,10 +20,10 @@ extern "C" {
    2 = flush the per-wave count hash after every insert,
    4 = MK_METHOD_CORES rescans every list instead of sharing a parent's arc
        pairs,
-   8 = the planner is told a split threshold that will not come out, as if
-       the graphs had changed since the batch was made: a pass that plans
-       without counting again (batches of up to 14,336 planner workgroups)
-       ends with empty histograms, and mk_batch_read returns MK_EDEVICE.
+   16 = the planner is told a split threshold that will not come out, as if
+        the graphs had changed since the batch was made: a pass that plans
+        without counting again (batches of up to 14,336 planner workgroups)
+        ends with empty histograms, and mk_batch_read returns MK_EDEVICE.
    Flags 1 and 2 switch the batch to builds of its counting kernel that
    carry these checks (the production builds leave them out).  With flags 1,
    2 and 4 the histograms are the same on every path. */

@@ -293,7 +293,7 @@ int core_hash_bits(int k);
 constexpr uint32_t kDebugNoHash = 1u;      // every code straight to the histogram
 constexpr uint32_t kDebugFlushAlways = 2u; // flush the hash after every insert
 constexpr uint32_t kDebugNoShare = 4u;     // core kernel: no per-parent arc lists
-constexpr uint32_t kDebugPlanMiss = 8u;    // sized plans: a threshold that will not come out
+constexpr uint32_t kDebugPlanMiss = 16u;   // sized plans: a threshold that will not come out
 // Arc pairs inside adj(P) kept per parent node P by the core kernel (global
 // memory, one list per workgroup); a parent with more uses the per-core scan.
 constexpr uint32_t kParentArcCap = 2048;

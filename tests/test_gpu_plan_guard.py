@@ -11,7 +11,7 @@ from paper_1804_09741_amd import motifs as M
 
 pytestmark = pytest.mark.gpu
 
-PLAN_MISS = 8
+PLAN_MISS = 16
 
 
 @pytest.mark.parametrize("k,method", [(3, M.METHOD_CORES), (4, M.METHOD_ESU), (5, M.METHOD_CORES),
