@@ -269,10 +269,10 @@ typedef struct mk_batch_opts {
      true class, and the sums are divided by the cores per class
      (mk_table_core_mult). */
 /* MK_METHOD_AUTO: MK_METHOD_CORES for k <= 5 and, by the batch's degrees,
-   vertex count and number of graphs, for k = 6 where it is the faster;
-   MK_METHOD_ESU else and
-   for graphs with more than MK_LDS_MARKS_MAX_VERTICES vertices (which
-   MK_METHOD_CORES rejects with MK_ERANGE). */
+   linked neighbours, two-way arcs, vertex count and number of graphs, for k =
+   6 where it is the faster; MK_METHOD_ESU else and for graphs with more than
+   MK_LDS_MARKS_MAX_VERTICES vertices (which MK_METHOD_CORES rejects with
+   MK_ERANGE). */
 #define MK_METHOD_AUTO 0
 #define MK_METHOD_ESU 1
 #define MK_METHOD_CORES 2

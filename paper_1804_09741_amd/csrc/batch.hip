@@ -12,6 +12,7 @@
 // graph of the batch shares one queue and one launch; histograms are
 // [ng][num_classes] uint64.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include "internal.h"
@@ -312,20 +313,20 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
 
 // The library's choice of method at k = 6.  (For k <= 5 counting from the
 // (k-2)-sets is the faster throughout: k = 5, n = 1000, m = 3000 0.5 against
-// 0.7 ms, 101 such graphs 16 against 54 ms.)  A core costs about the same
-// whatever it closes, so the counting pays where cores close many k-sets:
-// where a vertex reached along an edge has many neighbours, q = sum d^2 / sum
-// d of them, and four members' neighbours hardly overlap; and the
-// enumeration's marks leave it fewer waves the larger n is.  Pass times by
-// enumeration over those from the (k-2)-sets, 140 graphs and batches of n =
-// 100..5000, m = 1.2 n..6 n: one graph of 100..1000 vertices 0.4 to 1.1 (n =
-// 700, m = 3850: 7.7 and 16.8 ms), of 1250 and 1500 mostly 1.05 to 1.25 (0.8
-// at the least), of 2200 to 5000 1.15 to 3.5 (n = 5000, m = 30000: 304 and 78
-// ms).  From 8 graphs on, where the division's pass over the bins is the
-// smaller part: n = 700 0.85 to 1.02, 850 0.93 to 1.1, 1000 0.99 to 1.28 (20
-// of m = 3500: 56 and 45 ms), 1250 1.13 to 1.25.  With q of 5 to 6.5 (n =
-// 700, m = 1.6 n..2.2 n) 0.73 to 0.95 in every batch.
-static bool cores6(const mk_batch *b)
+// 0.7 ms, 101 such graphs 16 against 54 ms.)  Both methods visit the 4-sets.
+// The counting looks at all of a 4-set's neighbourhood, and pays where that
+// closes many k-sets at a time: where a vertex reached along an edge has many
+// neighbours, q = sum d^2 / sum d of them, the more the wider the degrees
+// spread, and where the enumeration's marks leave it few waves (large n).  An
+// arc inside the neighbourhood costs it two table lookups, once there are more
+// than 14 cells, so it loses where neighbours are linked to each other and
+// where arcs of all three types (out, in, both) make many cells.
+//
+// Candidates are batches of q >= 7.5 with a graph of 1,200 vertices, of 900
+// from 8 graphs on, where the division's pass over the bins is the smaller
+// part (with q of 5 to 6.5, n = 700 0.73 to 0.95 of the enumeration's speed in
+// every batch; one graph of 100..1000 vertices 0.4 to 1.1).
+static bool cores6_candidate(const mk_batch *b)
 {
     double d1 = 0, d2 = 0;
     for (const mk_graph *g : b->graphs) {
@@ -334,6 +335,39 @@ static bool cores6(const mk_batch *b)
     }
     const double q = d1 > 0 ? d2 / d1 : 0.0;
     return q >= 7.5 && b->max_n >= (b->ng < 8 ? 1200 : 900);
+}
+
+// Candidates whose graphs have fewer adjacency entries than this each are
+// counted from the (k-2)-sets without a look at their links, which costs as
+// much as their pass.
+constexpr int64_t kLinksLeast = 1024;
+
+// Whether a candidate is counted from the (k-2)-sets.  The line is a least
+// squares fit of the logarithm of the enumeration's pass time over the
+// counting's, 621 graphs and batches of n = 900..7000 (random, power-law, small
+// worlds, communities, geometric, cliques; shares of two-way arcs 0 to 0.8),
+// on ln n, ln (sum d^3 / sum d^2), the root of the share of linked
+// neighbours and the number of arc types, e^entropy.  Of 253 on the counting's
+// side the worst takes 1.2 times as long by it, five more than 1.05, and the
+// median 0.68 (power-law, n = 4322, m = 22000 32 against 103 ms); on the other
+// side are small worlds, n = 1200, d = 16 1.4 against 8.7 ms by the counting,
+// communities of 20, n = 5000 2.2 against 5.1, random geometric graphs of n =
+// 1200, d = 30 33 against 278.
+static bool cores6_pays(const mk_batch *b, double linked)
+{
+    double d1 = 0, d2 = 0, d3 = 0;
+    for (const mk_graph *g : b->graphs) {
+        d1 += (double)g->nnz_u;
+        d2 += (double)g->sum_d2;
+        d3 += (double)g->sum_d3;
+    }
+    const double both = std::min(std::max(2.0 * (double)b->total_m / d1 - 1.0, 0.0), 1.0);
+    const double one = (1.0 - both) / 2.0;
+    const auto h = [](double p) { return p > 0.0 ? -p * std::log(p) : 0.0; };
+    const double types = std::exp(2.0 * h(one) + h(both));
+    return 0.115 * std::log((double)b->max_n) + 0.4 * std::log(d3 / d2) -
+               5.3 * std::sqrt(linked) - 0.55 * types >
+           0.15;
 }
 
 // units of a graph in a plan for sets of plan_k <= 3 vertices: one per vertex
@@ -412,9 +446,10 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                        : (b->marks == MK_MARKS_GLOBAL ? MK_ADJ_LISTS : MK_ADJ_BITS);
     b->method = b->opts.method != MK_METHOD_AUTO
                     ? b->opts.method
-                    : (b->marks == MK_MARKS_LDS && (b->k <= 5 || (b->k == 6 && !lean && cores6(b)))
-                           ? MK_METHOD_CORES
-                           : MK_METHOD_ESU);
+                    : (b->marks == MK_MARKS_LDS && b->k <= 5 ? MK_METHOD_CORES : MK_METHOD_ESU);
+    // at k = 6 the choice waits for the typed adjacency
+    const bool candidate = b->opts.method == MK_METHOD_AUTO && b->marks == MK_MARKS_LDS &&
+                           b->k == 6 && !lean && cores6_candidate(b);
     if (b->marks == MK_MARKS_LDS && big) {
         const int max_n = b->max_n;
         delete b;
@@ -432,26 +467,12 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     }
     b->variant = (b->adjacency == MK_ADJ_LISTS ? kVarSearch : 0) |
                  (b->marks == MK_MARKS_GLOBAL ? kVarGlobal : 0);
-    b->plan_k = b->method == MK_METHOD_CORES ? (b->k == 3 ? 2 : b->k - 1) : b->k;
-    if (b->opts.split_threshold == 0)
-        b->opts.split_threshold = b->method == MK_METHOD_CORES && b->k == 6 ? kCore6Split
-                                                                           : kDefaultSplit[b->plan_k];
     if (b->opts.use_graph == 0) b->opts.use_graph = 1;
 
     b->bits_words = b->adjacency == MK_ADJ_BITS ? bits : 0;
     const uint64_t region = b->adjacency == MK_ADJ_BITS ? bits : list_ws_words(b->total_n, b->total_m);
     b->total_slots = (uint32_t)slots;
     b->seg_cap = std::max(b->seg_cap, 1);
-    b->lds_bytes = b->k == 7 ? k7_lds_bytes(std::max(b->max_n, 1), b->seg_cap, b->variant)
-                   : b->method == MK_METHOD_CORES
-                       ? core_lds_bytes(b->k, std::max(b->max_n, 1), b->seg_cap)
-                       : enum_lds_bytes(b->k, std::max(b->max_n, 1), b->seg_cap, b->variant);
-    if ((size_t)b->lds_bytes > ctx->max_lds) {
-        const int lds = b->lds_bytes;
-        delete b;
-        return fail(MK_ERANGE, "graphs need %d bytes of LDS per wave (limit %zu)", lds,
-                    ctx->max_lds);
-    }
     int rc = MK_OK;
     auto bail = [&](int status) {
         batch_release(b);
@@ -524,6 +545,33 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                                 hipMemcpyHostToDevice, ctx->stream));
     for (hipEvent_t &e : b->ev) BAIL_HIP(hipEventCreate(&e));
 
+    bool typed = false;  // the typed adjacency is built
+    if (candidate && b->max_nnz < kLinksLeast) {
+        b->method = MK_METHOD_CORES;
+    } else if (candidate) {
+        double linked = 0.0;
+        rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
+                          ctx->stream);
+        if (!rc) rc = batch_enqueue_typed(b, ctx->stream);
+        if (!rc)
+            rc = measure_links(b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_counters, &linked,
+                               ctx->stream);
+        if (rc) return bail(rc);
+        typed = true;
+        if (cores6_pays(b, linked)) b->method = MK_METHOD_CORES;
+    }
+    b->plan_k = b->method == MK_METHOD_CORES ? (b->k == 3 ? 2 : b->k - 1) : b->k;
+    if (b->opts.split_threshold == 0)
+        b->opts.split_threshold = b->method == MK_METHOD_CORES && b->k == 6 ? kCore6Split
+                                                                           : kDefaultSplit[b->plan_k];
+    b->lds_bytes = b->k == 7 ? k7_lds_bytes(std::max(b->max_n, 1), b->seg_cap, b->variant)
+                   : b->method == MK_METHOD_CORES
+                       ? core_lds_bytes(b->k, std::max(b->max_n, 1), b->seg_cap)
+                       : enum_lds_bytes(b->k, std::max(b->max_n, 1), b->seg_cap, b->variant);
+    if ((size_t)b->lds_bytes > ctx->max_lds)
+        return bail(fail(MK_ERANGE, "graphs need %d bytes of LDS per wave (limit %zu)",
+                         b->lds_bytes, ctx->max_lds));
+
     int per_cu = 0;
     rc = b->k == 7 ? k7_max_blocks_per_cu(b->variant, b->lds_bytes, &per_cu)
          : b->method == MK_METHOD_CORES
@@ -554,9 +602,13 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         BAIL_HIP(hipStreamSynchronize(ctx->stream));  // the descriptors are on the device
     } else {
         // sizing pass: typed adjacency + unit counts only
-        rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
-                          ctx->stream);
-        if (!rc) rc = batch_enqueue_typed(b, ctx->stream);
+        if (!typed)
+            rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
+                              ctx->stream);
+        else
+            rc = clear_ranges({b->d_counters + kPlanSums, kNumCounters - kPlanSums}, {nullptr, 0},
+                              {nullptr, 0}, ctx->stream);
+        if (!rc && !typed) rc = batch_enqueue_typed(b, ctx->stream);
         if (!rc)
             rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                              b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,

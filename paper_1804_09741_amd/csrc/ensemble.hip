@@ -57,6 +57,7 @@ __global__ void tails_kernel(const int32_t *row, const int32_t *col, int n, int3
     }
 }
 
+constexpr int kStats = 5;  // of ChainArgs
 struct ChainArgs {
     const int32_t *row, *col0, *src, *indeg;
     int n, words;
@@ -66,7 +67,7 @@ struct ChainArgs {
     uint32_t *bits;               // per graph of this launch: n x words
     int32_t *recip;               // per graph of this launch: n
     unsigned long long *stats;    // per graph of the ensemble: accepted, nnz_u, max |delta|,
-                                  // sum of |delta|^2
+                                  // sums of |delta|^2 and |delta|^3
 };
 
 // round-stamped LDS tables of the chain's dependence test (slots, arcs)
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(kWave) void switch_kernel(ChainArgs a)
             t0 += (uint64_t)cut;
             __syncthreads();
         }
-        if (lane == 0) a.stats[4 * r] = accepted;
+        if (lane == 0) a.stats[kStats * r] = accepted;
     }
     // reciprocal arcs: u -> v with v -> u
     for (uint32_t t = lane; t < a.m; t += kWave) {
@@ -270,25 +271,28 @@ __global__ __launch_bounds__(kWave) void switch_kernel(ChainArgs a)
     }
     __syncthreads();
     // |delta(v)| = out + in - reciprocal
-    unsigned long long sum = 0, sum2 = 0;
+    unsigned long long sum = 0, sum2 = 0, sum3 = 0;
     int mx = 0;
     for (int v = lane; v < a.n; v += kWave) {
         const int d = (a.row[v + 1] - a.row[v]) + a.indeg[v] - recip[v];
         sum += (unsigned long long)d;
         sum2 += (unsigned long long)d * (unsigned long long)d;
+        sum3 += (unsigned long long)d * (unsigned long long)d * (unsigned long long)d;
         mx = d > mx ? d : mx;
     }
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
         sum += __shfl_down(sum, o, kWave);
         sum2 += __shfl_down(sum2, o, kWave);
+        sum3 += __shfl_down(sum3, o, kWave);
         const int other = __shfl_down(mx, o, kWave);
         mx = other > mx ? other : mx;
     }
     if (lane == 0) {
-        a.stats[4 * r + 1] = sum;
-        a.stats[4 * r + 2] = (unsigned long long)mx;
-        a.stats[4 * r + 3] = sum2;
+        a.stats[kStats * r + 1] = sum;
+        a.stats[kStats * r + 2] = (unsigned long long)mx;
+        a.stats[kStats * r + 3] = sum2;
+        a.stats[kStats * r + 4] = sum3;
     }
 }
 
@@ -388,7 +392,7 @@ extern "C" int mk_randomise(mk_ctx *ctx, const mk_graph *g, int32_t count, uint6
     ENS_HIP(hipMalloc(&bits, sizeof(uint32_t) * std::max<size_t>((size_t)chunk * n * words, 1)));
     ENS_HIP(hipMalloc(&recip, sizeof(int32_t) * std::max<size_t>((size_t)chunk * n, 1)));
     ENS_HIP(hipMalloc(&d_cols, sizeof(int32_t *) * count));
-    ENS_HIP(hipMalloc(&stats, sizeof(unsigned long long) * 4 * count));
+    ENS_HIP(hipMalloc(&stats, sizeof(unsigned long long) * kStats * count));
     ENS_HIP(hipMemcpyAsync(d_cols, cols.data(), sizeof(int32_t *) * count, hipMemcpyHostToDevice, st));
     rc = fill_u32(indeg, 0, (size_t)std::max(n, 1), st);
     if (rc) {
@@ -421,21 +425,22 @@ extern "C" int mk_randomise(mk_ctx *ctx, const mk_graph *g, int32_t count, uint6
         hipLaunchKernelGGL(switch_kernel, dim3(cnt), dim3(kWave), 0, st, a);
         ENS_HIP(hipGetLastError());
     }
-    std::vector<unsigned long long> hs(4 * (size_t)count);
-    ENS_HIP(hipMemcpyAsync(hs.data(), stats, sizeof(unsigned long long) * 4 * count,
+    std::vector<unsigned long long> hs(kStats * (size_t)count);
+    ENS_HIP(hipMemcpyAsync(hs.data(), stats, sizeof(unsigned long long) * kStats * count,
                            hipMemcpyDeviceToHost, st));
     ENS_HIP(hipStreamSynchronize(st));
     for (int r = 0; r < count; ++r) {
-        made[r]->nnz_u = (int64_t)hs[4 * r + 1];
-        made[r]->max_udeg = (int32_t)hs[4 * r + 2];
-        made[r]->sum_d2 = (int64_t)hs[4 * r + 3];
+        made[r]->nnz_u = (int64_t)hs[kStats * r + 1];
+        made[r]->max_udeg = (int32_t)hs[kStats * r + 2];
+        made[r]->sum_d2 = (int64_t)hs[kStats * r + 3];
+        made[r]->sum_d3 = (int64_t)hs[kStats * r + 4];
         made[r]->covered = g->covered;  // switches keep every vertex's degrees
         if (made[r]->max_udeg > MK_MAX_DEGREE) {
             cleanup(true);
             return fail(MK_ERANGE, "random graph %d has undirected degree %d > MK_MAX_DEGREE=%d", r,
-                        (int)hs[4 * r + 2], MK_MAX_DEGREE);
+                        (int)hs[kStats * r + 2], MK_MAX_DEGREE);
         }
-        if (accepted) accepted[r] = hs[4 * r];
+        if (accepted) accepted[r] = hs[kStats * r];
     }
 #undef ENS_HIP
     cleanup(false);

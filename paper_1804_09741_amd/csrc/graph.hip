@@ -374,7 +374,7 @@ extern "C" int mk_graph_load_csr(mk_ctx *ctx, int32_t n, const int32_t *row_ptr,
     for (int u = 0; u < n; ++u)
         for (int32_t e = row_ptr[u]; e < row_ptr[u + 1]; ++e) in_col[fill[col[e]]++] = u;
     std::fill(mark.begin(), mark.end(), -1);
-    int64_t nnz_u = 0, sum_d2 = 0;
+    int64_t nnz_u = 0, sum_d2 = 0, sum_d3 = 0;
     int32_t max_udeg = 0, covered = 0;
     for (int v = 0; v < n; ++v) {
         int32_t d = row_ptr[v + 1] - row_ptr[v];
@@ -383,6 +383,7 @@ extern "C" int mk_graph_load_csr(mk_ctx *ctx, int32_t n, const int32_t *row_ptr,
             if (mark[in_col[e]] != v) ++d;
         nnz_u += d;
         sum_d2 += (int64_t)d * d;
+        sum_d3 += (int64_t)d * d * d;
         covered += d > 0;
         max_udeg = std::max(max_udeg, d);
     }
@@ -399,6 +400,7 @@ extern "C" int mk_graph_load_csr(mk_ctx *ctx, int32_t n, const int32_t *row_ptr,
     g->nnz_u = nnz_u;
     g->max_udeg = max_udeg;
     g->sum_d2 = sum_d2;
+    g->sum_d3 = sum_d3;
     g->covered = covered;
     hipError_t e1 = hipMalloc(&g->d_row, sizeof(int32_t) * ((size_t)n + 1));
     hipError_t e2 = hipMalloc(&g->d_col, sizeof(int32_t) * (size_t)std::max<int64_t>(m, 1));

@@ -53,6 +53,7 @@ struct Graph {
     int64_t nnz_u = 0;        // sum of undirected degrees |delta(v)|
     int32_t max_udeg = 0;
     int64_t sum_d2 = 0;       // sum of squared undirected degrees
+    int64_t sum_d3 = 0;       // of cubed ones
     int32_t covered = 0;      // vertices with a neighbour
     int32_t *d_row = nullptr; // n+1, out-adjacency CSR as given
     int32_t *d_col = nullptr; // m
@@ -216,6 +217,13 @@ int launch_plan(int k, const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32
                 uint32_t *slot_l2, uint32_t *scan_tmp, int4 *units, uint32_t unit_cap,
                 uint64_t split_threshold, uint64_t spec_threshold, bool sized,
                 uint32_t slice_least, uint32_t waves, uint32_t units_per_wave, uint32_t *counters, hipStream_t stream);
+
+// How much the neighbourhoods of a batch's graphs overlap, from a sample of
+// the typed adjacency's entries (v, u), which is in place: *linked receives
+// the common neighbours of v and u over the neighbours of v but u (0 to 1).
+// Uses counters[kPlanSums], which the caller has cleared.  Blocks.
+int measure_links(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
+                  uint32_t *counters, double *linked, hipStream_t stream);
 
 // Enumeration + code + lookup + histogram over the queued units.
 // k = 7 (k7.hip): device tables of one count

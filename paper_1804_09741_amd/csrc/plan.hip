@@ -20,6 +20,7 @@
 // gives offsets; the last pass writes the units.  The order is graph by
 // graph, root by root.
 #include <algorithm>
+#include <cstring>
 
 #include "internal.h"
 #include "plan_shape.h"
@@ -125,6 +126,88 @@ __device__ __forceinline__ bool exclusive_above(const PlanGraph &g, int v, int x
     if (!g.bits_out) return x > v && list_relation(g.urow, g.uadj, (uint32_t)v, (uint32_t)x) == 0u;
     const size_t w = (size_t)v * g.words + (x >> 5);
     return (x > v) & !(((g.bits_out[w] | g.bits_in[w]) >> (x & 31)) & 1u);
+}
+
+// Common neighbours of the ends of every step-th adjacency entry (v, u), and
+// the neighbours of v but u: a team of 16 lanes an entry, the shorter list
+// tested against the other end.  Sums to sum_line's first two u64.
+constexpr int kLinkThreads = 256, kLinkTeam = 16;
+__global__ __launch_bounds__(kLinkThreads) void links_kernel(const DevGraph *graphs, uint32_t step,
+                                                             uint32_t *counters)
+{
+    __shared__ unsigned long long part[2][kLinkThreads / kWave];
+    const PlanGraph g = plan_graph(graphs[blockIdx.y]);
+    const int tid = threadIdx.x, sub = tid % kLinkTeam;
+    const uint64_t nnz = g.n > 0 ? (uint64_t)min(g.urow[g.n], (int)g.nnz_cap) : 0u;
+    const uint64_t team = ((uint64_t)blockIdx.x * kLinkThreads + tid) / kLinkTeam;
+    const uint64_t teams = (uint64_t)gridDim.x * (kLinkThreads / kLinkTeam);
+    unsigned long long common = 0, others = 0;
+    for (uint64_t e = team * step; e < nnz; e += teams * step) {
+        const int v = owner_of(g.urow, g.n, (int)e), u = (int)(g.uadj[e] >> 2);
+        const int v0 = g.urow[v], v1 = g.urow[v + 1], u0 = g.urow[u], u1 = g.urow[u + 1];
+        const bool by_u = u1 - u0 < v1 - v0;
+        const int end = by_u ? u1 : v1, other = by_u ? v : u;
+        for (int i = (by_u ? u0 : v0) + sub; i < end; i += kLinkTeam) {
+            const int x = (int)(g.uadj[i] >> 2);
+            bool arc;
+            if (g.bits_out) {
+                const size_t w = (size_t)other * g.words + (x >> 5);
+                arc = ((g.bits_out[w] | g.bits_in[w]) >> (x & 31)) & 1u;
+            } else {
+                arc = list_relation(g.urow, g.uadj, (uint32_t)other, (uint32_t)x) != 0u;
+            }
+            common += arc;
+        }
+        if (sub == 0) others += (unsigned long long)(v1 - v0 - 1);
+    }
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) {
+        common += __shfl_down(common, d, kWave);
+        others += __shfl_down(others, d, kWave);
+    }
+    if (tid % kWave == 0) {
+        part[0][tid / kWave] = common;
+        part[1][tid / kWave] = others;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        unsigned long long sum = 0;
+        for (int i = 0; i < kLinkThreads / kWave; ++i) sum += part[tid][i];
+        if (sum)
+            atomicAdd(reinterpret_cast<unsigned long long *>(
+                          sum_line(counters, plan_block() % kQueues)) + tid, sum);
+    }
+}
+
+// Entries sampled over the batch (all of a graph of n = 5000, m = 30000) and
+// workgroups that share them.
+constexpr uint32_t kLinkSample = 1u << 16;
+constexpr uint32_t kLinkBlocks = 1024;
+
+int measure_links(const DevGraph *d_graphs, int ng, int64_t max_nnz, uint32_t total_slots,
+                  uint32_t *counters, double *linked, hipStream_t stream)
+{
+    *linked = 0.0;
+    if (ng <= 0 || total_slots == 0) return MK_OK;
+    const uint32_t step = (total_slots - 1u) / kLinkSample + 1u;
+    const uint64_t most = ((uint64_t)max_nnz / step + 1) * kLinkTeam / kLinkThreads + 1;
+    const uint32_t blocks =
+        (uint32_t)std::min<uint64_t>(most, std::max(kLinkBlocks / (uint32_t)ng, 1u));
+    hipLaunchKernelGGL(links_kernel, dim3(blocks, (unsigned)ng), dim3(kLinkThreads), 0, stream,
+                       d_graphs, step, counters);
+    MK_HIP(hipGetLastError());
+    uint32_t line[kQueues * kSumLine];
+    MK_HIP(hipMemcpyAsync(line, counters + kPlanSums, sizeof(line), hipMemcpyDeviceToHost, stream));
+    MK_HIP(hipStreamSynchronize(stream));
+    uint64_t sum[2] = {0, 0};
+    for (int x = 0; x < kQueues; ++x)
+        for (int i = 0; i < 2; ++i) {
+            uint64_t part;
+            std::memcpy(&part, line + x * kSumLine + 2 * i, sizeof(part));
+            sum[i] += part;
+        }
+    if (sum[1]) *linked = (double)sum[0] / (double)sum[1];
+    return MK_OK;
 }
 
 // Pass kinds of the planner kernel.
