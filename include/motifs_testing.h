@@ -29,6 +29,9 @@ extern "C" {
    2 and 4 the histograms are the same on every path. */
 int mk_batch_debug(mk_batch *b, int32_t flags);
 
+/* Device bytes the batch holds, its own histograms included. */
+int mk_batch_bytes(const mk_batch *b, uint64_t *bytes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -122,6 +122,7 @@ SIGNATURES = {
                                    ctypes.POINTER(ctypes.c_double),
                                    ctypes.POINTER(ctypes.c_double)]),
     "mk_batch_debug": (ctypes.c_int, [_P, _I32]),
+    "mk_batch_bytes": (ctypes.c_int, [_P, ctypes.POINTER(_U64)]),
     "mk_server_start": (ctypes.c_int, [_P, ctypes.POINTER(ServerOpts), ctypes.POINTER(_P)]),
     "mk_submit": (ctypes.c_int, [_P, _P, ctypes.c_int, ctypes.POINTER(_U64)]),
     "mk_wait": (ctypes.c_int, [_P, _U64, _P, _U32, _I32, ctypes.POINTER(RequestTimes)]),
@@ -382,6 +383,13 @@ def mk_batch_create(ctx: int, gs: Sequence[int], t: int, split_threshold: int = 
 def mk_batch_debug(b: int, flags: int) -> None:
     """Test hook (include/motifs_testing.h): alternative internal paths."""
     _check(library().mk_batch_debug(b, flags))
+
+
+def mk_batch_bytes(b: int) -> int:
+    """Test hook (include/motifs_testing.h): device bytes the batch holds."""
+    n = _U64()
+    _check(library().mk_batch_bytes(b, ctypes.byref(n)))
+    return n.value
 
 
 def mk_batch_run(b: int, d_hist: int = 0, stream: int = 0) -> None:
