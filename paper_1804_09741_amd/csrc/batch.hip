@@ -379,8 +379,9 @@ static uint64_t plan_units(int plan_k, const mk_graph *g)
 
 // The most arc pairs inside adj(P) that a parent P of cores (k - 3 members) of
 // these graphs can have, rounded up to a cache line of them.  A blocking count
-// allocates and frees a list of this length for every wave: 40 graphs of n =
-// 100, m = 200 at k = 5 1.23 ms with lists of 8,192, of n = 3000, m = 4500 0.88.
+// allocates and frees a list of this length for every wave: with lists of up to
+// 8,192 40 graphs of n = 100, m = 200 took 1.23 ms at k = 5 (now 0.72), one of
+// n = 3000, m = 4500 0.88 (0.34).
 static uint64_t most_parent_arcs(const mk_batch *b)
 {
     uint64_t most = 1;
