@@ -646,7 +646,8 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     b->unit_cap = std::max<uint32_t>((uint32_t)b->units, 1);
     b->grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, std::max<uint64_t>(b->units, 1));
     if (t && !lean)
-        b->layout = hist_layout(ng, t->num_classes, b->grid, b->method == MK_METHOD_CORES);
+        b->layout = hist_layout(ng, t->num_classes, b->grid, b->units,
+                                b->method == MK_METHOD_CORES);
     const size_t unit_bytes = (sizeof(int4) * (size_t)b->unit_cap + 255) & ~(size_t)255;
     if (b->layout.graph_words &&
         hipMalloc(&b->d_units, unit_bytes + 8 * b->layout.words()) != hipSuccess) {

@@ -106,14 +106,25 @@ int launch_core_divide(unsigned long long *hist, int ng, uint32_t num_classes,
 // graphs.)  The work array is cleared instead of the histograms and read once
 // more: 128 MiB of it for the enumeration, whose many light graphs at k = 6
 // (380 MB of bins) gain nothing, 512 MiB for the cores method, which reads
-// and divides the bins anyway.
+// and divides the bins anyway.  That costs light launches more than the
+// spread bins give, so there must be a unit of work for every kUnitWords of
+// it (kUnitWordsRows at k = 6).  Passes in place over passes with the work
+// array, by units a graph:
+//   k = 6 by enumeration    174 0.93  220 0.80  1,660 1.00  3,190 1.02
+//                           7,370 1.41  8,650 1.17
+//         from the cores    160 0.81  165 0.95  5,740 1.28  6,000 1.44
+//   k = 5 from the cores    60 0.91  153 0.94  549 1.02  1,180 1.05
+//         by enumeration    60 0.97  154 0.95  598 1.00
+//   k = 3, 4                0.97 to 1.08
 constexpr uint32_t kRowWords = 4;
 constexpr uint32_t kMaxRowBits = 15;
 constexpr uint32_t kMaxCopies = 16;
 constexpr size_t kCopiesWords = (size_t)1 << 18;
 constexpr size_t kWorkWords = (size_t)1 << 24;
+constexpr size_t kUnitWords = 128;
+constexpr size_t kUnitWordsRows = 900;
 
-HistLayout hist_layout(int ng, uint32_t num_classes, int grid, bool cores)
+HistLayout hist_layout(int ng, uint32_t num_classes, int grid, uint64_t units, bool cores)
 {
     HistLayout l;
     if (ng <= 0 || num_classes == 0) return l;
@@ -126,6 +137,7 @@ HistLayout hist_layout(int ng, uint32_t num_classes, int grid, bool cores)
     w.graph_words = (size_t)w.stride << w.row_bits;
     const size_t words = w.graph_words * (size_t)ng;
     if (words > (cores ? 4 : 1) * kWorkWords || cols > (uint32_t)kTileCols) return l;
+    if (words / (cols == 1 ? kUnitWords : kUnitWordsRows) > units) return l;
     w.copy_words = words;
     if (cols == 1)
         while (w.copies < kMaxCopies && 2 * (size_t)w.copies * words <= kCopiesWords &&

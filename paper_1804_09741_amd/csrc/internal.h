@@ -278,8 +278,9 @@ struct HistLayout {
     size_t copy_words = 0;
     size_t words() const { return (size_t)copies * copy_words; }
 };
-// The layout of a launch of `grid` waves over ng graphs (see hist.hip).
-HistLayout hist_layout(int ng, uint32_t num_classes, int grid, bool cores);
+// The layout of a launch of `grid` waves over the `units` work units of ng
+// graphs (see hist.hip).
+HistLayout hist_layout(int ng, uint32_t num_classes, int grid, uint64_t units, bool cores);
 
 struct EnumConfig {
     int max_n;       // largest n of the batch (LDS marks)

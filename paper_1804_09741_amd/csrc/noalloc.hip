@@ -161,7 +161,7 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     // more per node; slices of children, which cost twice the threshold at
     // least, add up to two more per unit of the target.  A scratch without
     // the room for those plans whole children.
-    HistLayout layout = hist_layout(1, nc, grid, false);
+    HistLayout layout = hist_layout(1, nc, grid, ~0ull, false);
     const uint64_t target = 32ull * (uint64_t)grid + 1;
     const uint64_t most_whole = 2 * target + nnz + kMinStaticUnits;
     bool slices = most_whole + 2 * target <= unit_cap;
