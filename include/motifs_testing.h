@@ -2,7 +2,8 @@
  * motifs_testing.h -- test hooks of libmotifs.so (not for production use).
  *
  * They switch a prepared batch onto alternative internal paths whose
- * results must equal the default's, so that tests can compare them.
+ * results must equal the default's, so that tests can compare them, or show
+ * what it takes.
  */
 #ifndef MOTIFS_TESTING_H
 #define MOTIFS_TESTING_H
@@ -28,6 +29,11 @@ extern "C" {
    carry these checks (the production builds leave them out).  With flags 1,
    2 and 4 the histograms are the same on every path. */
 int mk_batch_debug(mk_batch *b, int32_t flags);
+
+/* mk_batch_create as if the device had only most_bytes for the batch. */
+int mk_batch_create_capped(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
+                           const mk_table *t, const mk_batch_opts *opts, uint64_t most_bytes,
+                           mk_batch **out);
 
 /* Device bytes the batch holds, its own histograms included. */
 int mk_batch_bytes(const mk_batch *b, uint64_t *bytes);

@@ -41,6 +41,9 @@ struct mk_batch {
     uint32_t *d_slot_l2 = nullptr;
     uint32_t *d_scan_tmp = nullptr;
     uint32_t total_slots = 0;
+    // units, arc lists, marks and the work array, one allocation
+    char *d_run = nullptr;
+    uint64_t run_bytes = 0;
     int4 *d_units = nullptr;
     uint32_t unit_cap = 0;
     uint64_t spec_threshold = 0;  // split threshold of the sizing plan (0: the floor)
@@ -48,13 +51,14 @@ struct mk_batch {
     uint32_t *d_unit_begin = nullptr;    // first unit of every graph, plus the total
     unsigned long long *d_hist_own = nullptr;
     HistLayout layout;                            // of what the waves count into:
-    unsigned long long *d_hist_work = nullptr;    // a work array behind the units (one
-                                                  // allocation), null: the histograms
+    unsigned long long *d_hist_work = nullptr;    // a work array, null: the histograms
     uint32_t *d_wave_scratch = nullptr;  // core method: per-workgroup arc lists
     uint32_t arc_cap = 0;                //   of this many arc pairs
     void *d_marks = nullptr;             // MK_MARKS_GLOBAL: per-workgroup marks
     size_t mark_stride = 0;              //   marks per workgroup
     size_t mark_bytes = 0;               //   bytes of d_marks
+    uint64_t held = 0;                   // device bytes allocated
+    uint64_t most_bytes = UINT64_MAX;    // and at most (tests)
     unsigned long long *hist_last = nullptr;
 
     int max_n = 0, max_words = 0, seg_cap = 0;
@@ -184,9 +188,94 @@ static void batch_release(mk_batch *b)
         if (e) (void)hipEventDestroy(e);
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    void *bufs[] = {b->d_plan, b->d_ws, b->d_units, b->d_hist_own, b->d_wave_scratch, b->d_marks};
+    void *bufs[] = {b->d_plan, b->d_ws, b->d_run, b->d_hist_own};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
+}
+
+// device memory of a batch
+static hipError_t batch_malloc(mk_batch *b, void **p, uint64_t bytes)
+{
+    if (bytes > b->most_bytes || b->held > b->most_bytes - bytes) return hipErrorOutOfMemory;
+    const hipError_t e = hipMalloc(p, (size_t)bytes);
+    if (e == hipSuccess) b->held += bytes;
+    else (void)hipGetLastError();
+    return e;
+}
+
+// The memory of a launch: work units, arc lists of the core method and marks
+// (zero), and the histograms' work array, which the launch can do without and
+// does where there is no room.  Blocks where there are marks to clear.
+static int batch_alloc_run(mk_batch *b)
+{
+    uint64_t bytes = 0;
+    const auto place = [&](uint64_t part) {
+        const uint64_t at = bytes;
+        bytes += (part + 255) & ~255ull;
+        return at;
+    };
+    const uint64_t o_units = place(sizeof(int4) * (uint64_t)b->unit_cap);
+    const uint64_t list_bytes = sizeof(uint32_t) * (uint64_t)b->arc_cap * (uint64_t)b->grid;
+    const uint64_t o_lists = place(list_bytes), o_marks = place(b->mark_bytes);
+    const uint64_t needed = bytes;
+    void *p = nullptr;
+    if (b->layout.graph_words) {
+        const uint64_t o_work = place(8 * (uint64_t)b->layout.words());
+        if (batch_malloc(b, &p, bytes) == hipSuccess)
+            b->d_hist_work =
+                reinterpret_cast<unsigned long long *>(static_cast<char *>(p) + o_work);
+        else b->layout = HistLayout();
+    }
+    if (!p) {
+        const hipError_t e = batch_malloc(b, &p, needed);
+        if (e != hipSuccess)
+            return fail(e == hipErrorOutOfMemory ? MK_ENOMEM : MK_EDEVICE,
+                        "batch memory (%llu bytes): %s", (unsigned long long)needed,
+                        hipGetErrorString(e));
+    }
+    b->run_bytes = b->d_hist_work ? bytes : needed;
+    b->d_run = static_cast<char *>(p);
+    b->d_units = reinterpret_cast<int4 *>(b->d_run + o_units);
+    if (list_bytes) b->d_wave_scratch = reinterpret_cast<uint32_t *>(b->d_run + o_lists);
+    if (b->mark_bytes) {
+        // zero once: every pop restores the marks it changed, so they are
+        // zero again whenever a workgroup finishes a unit
+        b->d_marks = b->d_run + o_marks;
+        const int rc = fill_u32(b->d_marks, 0, b->mark_bytes / 4, b->ctx->stream);
+        if (rc) return rc;
+        MK_HIP(hipStreamSynchronize(b->ctx->stream));
+    }
+    return MK_OK;
+}
+
+// The batch's own histograms, made on first use; where they do not fit beside
+// the work array, that goes.
+static int batch_own_hist(mk_batch *b)
+{
+    if (b->d_hist_own) return MK_OK;
+    const uint64_t bytes =
+        8 * std::max<uint64_t>((uint64_t)b->ng * b->table->num_classes, 1);
+    void *p = nullptr;
+    hipError_t e = batch_malloc(b, &p, bytes);
+    if (e != hipSuccess && b->d_hist_work) {
+        if (b->last_stream) MK_HIP(hipStreamSynchronize(b->last_stream));
+        MK_HIP(hipFree(b->d_run));
+        b->held -= b->run_bytes;
+        b->d_run = nullptr;
+        b->d_units = nullptr;
+        b->d_wave_scratch = nullptr;
+        b->d_marks = nullptr;
+        b->d_hist_work = nullptr;
+        b->layout = HistLayout();
+        b->exec_hist = nullptr;  // captured with the old addresses
+        const int rc = batch_alloc_run(b);
+        if (rc) return rc;
+        e = batch_malloc(b, &p, bytes);
+    }
+    if (e != hipSuccess)
+        return fail(MK_ENOMEM, "histogram allocation (%llu bytes) failed", (unsigned long long)bytes);
+    b->d_hist_own = static_cast<unsigned long long *>(p);
+    return MK_OK;
 }
 
 static EnumConfig enum_config(const mk_batch *b)
@@ -398,7 +487,8 @@ static uint64_t most_parent_arcs(const mk_batch *b)
 // that mk_graph_footprint does not count (the histograms' work array, the
 // arc lists of k = 6 from the (k-2)-sets).
 static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int k,
-                        const mk_table *t, const mk_batch_opts *opts, bool lean, mk_batch **out)
+                        const mk_table *t, const mk_batch_opts *opts, bool lean, mk_batch **out,
+                        uint64_t most_bytes = UINT64_MAX)
 {
     *out = nullptr;
     for (int i = 0; i < ng; ++i)
@@ -413,6 +503,7 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     b->k = k;
     b->ng = ng;
     b->graphs.assign(gs, gs + ng);
+    b->most_bytes = most_bytes;
     if (opts) b->opts = *opts;
     const mk_batch_opts o = b->opts;
     if (o.units_per_wave < 0 || o.units_per_wave > 4096) {
@@ -503,7 +594,8 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                              hipGetErrorString(e_)));                                          \
     } while (0)
 
-    BAIL_HIP(hipMalloc(&b->d_ws, sizeof(uint32_t) * std::max<uint64_t>(region + rows + adj, 1)));
+    BAIL_HIP(batch_malloc(b, reinterpret_cast<void **>(&b->d_ws),
+                          sizeof(uint32_t) * std::max<uint64_t>(region + rows + adj, 1)));
     {
         const bool with_bits = b->adjacency == MK_ADJ_BITS;
         uint64_t ob = 0, orow = region, oadj = region + rows, oslot = 0, vbase = 0;
@@ -545,7 +637,7 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                  o_tmp = place(sizeof(uint32_t) * plan_tmp_words(ng, b->max_nnz, (uint32_t)slots)),
                  o_counters = place(sizeof(uint32_t) * kNumCounters),
                  o_begin = place(sizeof(uint32_t) * ((size_t)ng + 1));
-    BAIL_HIP(hipMalloc(&b->d_plan, plan_bytes));
+    BAIL_HIP(batch_malloc(b, reinterpret_cast<void **>(&b->d_plan), plan_bytes));
     const auto words = [&](size_t at) { return reinterpret_cast<uint32_t *>(b->d_plan + at); };
     b->d_graphs = reinterpret_cast<DevGraph *>(b->d_plan + o_graphs);
     b->d_slot_cnt = words(o_cnt);
@@ -648,18 +740,6 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
     if (t && !lean)
         b->layout = hist_layout(ng, t->num_classes, b->grid, b->units,
                                 b->method == MK_METHOD_CORES);
-    const size_t unit_bytes = (sizeof(int4) * (size_t)b->unit_cap + 255) & ~(size_t)255;
-    if (b->layout.graph_words &&
-        hipMalloc(&b->d_units, unit_bytes + 8 * b->layout.words()) != hipSuccess) {
-        (void)hipGetLastError();  // no room for the work array: count in place
-        b->d_units = nullptr;
-        b->layout = HistLayout();
-    }
-    if (!b->d_units) BAIL_HIP(hipMalloc(&b->d_units, unit_bytes));
-    if (b->layout.graph_words)
-        b->d_hist_work = reinterpret_cast<unsigned long long *>(
-            reinterpret_cast<char *>(b->d_units) + unit_bytes);
-
     if (b->method == MK_METHOD_CORES && k >= 5) {
         // Lists of kParentArcCap arc pairs, longer (to 4 times) where the
         // launch has fewer waves than the footprint counts with: a parent
@@ -672,17 +752,10 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
             std::max<uint64_t>(waves * kParentArcCap / (uint64_t)b->grid, kParentArcCap),
             4 * kParentArcCap);
         b->arc_cap = (uint32_t)std::min<uint64_t>(cap, most_parent_arcs(b));
-        BAIL_HIP(hipMalloc(&b->d_wave_scratch, sizeof(uint32_t) * b->arc_cap * (size_t)b->grid));
     }
-    if (b->marks == MK_MARKS_GLOBAL) {
-        // zero once: every pop restores the marks it changed, so they are
-        // zero again whenever a workgroup finishes a unit
-        b->mark_bytes = b->mark_stride * 4 * (size_t)b->grid;
-        BAIL_HIP(hipMalloc(&b->d_marks, b->mark_bytes));
-        rc = fill_u32(b->d_marks, 0, b->mark_bytes / 4, ctx->stream);
-        if (rc) return bail(rc);
-        BAIL_HIP(hipStreamSynchronize(ctx->stream));
-    }
+    if (b->marks == MK_MARKS_GLOBAL) b->mark_bytes = b->mark_stride * 4 * (size_t)b->grid;
+    rc = batch_alloc_run(b);
+    if (rc) return bail(rc);
 #undef BAIL_HIP
     *out = b;
     return MK_OK;
@@ -713,13 +786,11 @@ extern "C" int mk_batch_run(mk_batch *b, uint64_t *d_hist, void *stream)
     MK_HIP(hipSetDevice(ctx->device));
     unsigned long long *hist = reinterpret_cast<unsigned long long *>(d_hist);
     if (!hist) {
-        if (!b->d_hist_own) {
-            hipError_t e = hipMalloc(&b->d_hist_own, sizeof(unsigned long long) *
-                                                         std::max<size_t>((size_t)b->ng * b->table->num_classes, 1));
-            if (e != hipSuccess) return fail(MK_ENOMEM, "mk_batch_run: histogram allocation failed");
-        }
+        const int rc = batch_own_hist(b);
+        if (rc) return rc;
         hist = b->d_hist_own;
     }
+    if (!b->d_units) return fail(MK_ENOMEM, "mk_batch_run: the batch lost its memory");
     hipStream_t s = stream ? reinterpret_cast<hipStream_t>(stream) : ctx->stream;
     if (b->ng == 0) {
         b->hist_last = hist;
@@ -834,25 +905,16 @@ uint64_t batch_units(const mk_batch *b) { return b->units; }
 
 uint64_t batch_device_bytes(const mk_batch *b)
 {
-    uint64_t words = b->adjacency == MK_ADJ_BITS ? b->bits_words
-                                                 : list_ws_words(b->total_n, b->total_m);
-    for (const mk_graph *g : b->graphs) words += (uint64_t)g->n + 1 + (uint64_t)g->nnz_u;
-    return 4 * words + 20ull * b->total_slots + 4 * plan_tmp_words(b->ng, b->max_nnz, b->total_slots) +
-           16ull * b->unit_cap + 8ull * b->ng * b->table->num_classes + 4ull * (b->ng + 1) +
-           8ull * b->layout.words() +
-           sizeof(DevGraph) * b->graphs.size() + 4 * kNumCounters +
-           (b->d_wave_scratch ? 4ull * b->arc_cap * (uint64_t)b->grid : 0) + b->mark_bytes;
+    const uint64_t own = 8ull * b->ng * b->table->num_classes;
+    return b->held + (b->d_hist_own ? 0 : own);
 }
 
 // typed adjacency + plan into the batch's own histogram buffer
 int batch_prepare(mk_batch *b, hipStream_t stream)
 {
     MK_HIP(hipSetDevice(b->ctx->device));
-    if (!b->d_hist_own) {
-        hipError_t e = hipMalloc(&b->d_hist_own, sizeof(unsigned long long) *
-                                                     std::max<size_t>((size_t)b->ng * b->table->num_classes, 1));
-        if (e != hipSuccess) return fail(MK_ENOMEM, "histogram allocation failed");
-    }
+    const int rc = batch_own_hist(b);
+    if (rc) return rc;
     b->hist_last = b->d_hist_own;
     b->last_stream = stream;
     if (b->ng == 0) return MK_OK;
@@ -966,6 +1028,15 @@ extern "C" int mk_batch_debug(mk_batch *b, int32_t flags)
     if (b->debug_flags != flags) b->exec_hist = nullptr;  // captured with the old flags
     b->debug_flags = flags;
     return MK_OK;
+}
+
+extern "C" int mk_batch_create_capped(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
+                                      const mk_table *t, const mk_batch_opts *opts,
+                                      uint64_t most_bytes, mk_batch **out)
+{
+    if (!ctx || !t || !out || ng < 0 || (ng > 0 && !gs) || t->ctx != ctx || !t->d_table)
+        return fail(MK_EINVAL, "mk_batch_create_capped: bad argument");
+    return batch_create(ctx, gs, ng, t->k, t, opts, false, out, most_bytes);
 }
 
 extern "C" int mk_batch_bytes(const mk_batch *b, uint64_t *bytes)

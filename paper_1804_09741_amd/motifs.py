@@ -122,6 +122,8 @@ SIGNATURES = {
                                    ctypes.POINTER(ctypes.c_double),
                                    ctypes.POINTER(ctypes.c_double)]),
     "mk_batch_debug": (ctypes.c_int, [_P, _I32]),
+    "mk_batch_create_capped": (ctypes.c_int, [_P, _P, _I32, _P, ctypes.POINTER(BatchOpts), _U64,
+                                              ctypes.POINTER(_P)]),
     "mk_batch_bytes": (ctypes.c_int, [_P, ctypes.POINTER(_U64)]),
     "mk_server_start": (ctypes.c_int, [_P, ctypes.POINTER(ServerOpts), ctypes.POINTER(_P)]),
     "mk_submit": (ctypes.c_int, [_P, _P, ctypes.c_int, ctypes.POINTER(_U64)]),
@@ -380,6 +382,16 @@ def mk_batch_create(ctx: int, gs: Sequence[int], t: int, split_threshold: int = 
     return h.value
 
 
+def mk_batch_create_capped(ctx: int, gs: Sequence[int], t: int, most_bytes: int,
+                           **opts) -> int:
+    """Test hook (include/motifs_testing.h): no more device memory than that."""
+    h = _P()
+    _check(library().mk_batch_create_capped(ctx, _handles(gs), len(gs), t,
+                                            ctypes.byref(BatchOpts(**opts)), most_bytes,
+                                            ctypes.byref(h)))
+    return h.value
+
+
 def mk_batch_debug(b: int, flags: int) -> None:
     """Test hook (include/motifs_testing.h): alternative internal paths."""
     _check(library().mk_batch_debug(b, flags))
@@ -514,8 +526,12 @@ class Batch:
         self.graphs = list(graphs)
         self.table = table
         debug = opts.pop("debug_flags", 0)
-        self.handle = mk_batch_create(ctx.handle, [g.handle for g in graphs], table.handle,
-                                      **opts)
+        most_bytes = opts.pop("most_bytes", None)
+        gs = [g.handle for g in graphs]
+        if most_bytes is None:
+            self.handle = mk_batch_create(ctx.handle, gs, table.handle, **opts)
+        else:
+            self.handle = mk_batch_create_capped(ctx.handle, gs, table.handle, most_bytes, **opts)
         if debug:
             try:
                 mk_batch_debug(self.handle, debug)
