@@ -123,8 +123,11 @@ int mk_graph_load_csr(mk_ctx *ctx, int32_t n, const int32_t *row_ptr,
    any output pointer may be NULL. */
 int mk_graph_info(const mk_graph *g, int32_t *n, int64_t *m, int32_t *max_degree);
 
-/* Device bytes one count of this graph needs beyond the graph itself
-   (workspace, work units, histogram) for subgraph size k. */
+/* Device bytes one count of this graph takes beyond the graph itself for
+   subgraph size k: workspace, work units (an estimate: a plan tells their
+   number), histogram and its work array, arc lists and marks.  With less
+   memory it is still counted, without the work array (mk_count) or as the
+   server's budget allows. */
 int mk_graph_footprint(const mk_graph *g, int k, uint64_t *bytes);
 
 void mk_graph_free(mk_graph *g);

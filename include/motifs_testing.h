@@ -35,6 +35,14 @@ int mk_batch_create_capped(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
                            const mk_table *t, const mk_batch_opts *opts, uint64_t most_bytes,
                            mk_batch **out);
 
+/* mk_batch_create for a batch that keeps to `limit` device bytes, as the
+   server's batches do, and the least limit that holds for one graph (what a
+   batch of several takes at the least is not more than their sum and 64 KiB). */
+int mk_batch_create_within(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
+                           const mk_table *t, const mk_batch_opts *opts, uint64_t limit,
+                           mk_batch **out);
+int mk_graph_least_footprint(const mk_graph *g, int k, uint64_t *bytes);
+
 /* Device bytes the batch holds, its own histograms included. */
 int mk_batch_bytes(const mk_batch *b, uint64_t *bytes);
 

@@ -71,6 +71,7 @@ struct mk_batch {
     int marks = MK_MARKS_LDS;    // resolved MK_MARKS_*
     int variant = 0;             // kVar* bits of the enumeration kernel
     int plan_k = 0;              // set size the planner cuts units for
+    uint32_t slice_least = 0;    // the planner's least cost of a slice (0: none)
     uint64_t units = 0, split_pairs = 0;
 
     // pass start, counting kernel start, counting kernel end, pass end
@@ -153,31 +154,6 @@ static uint32_t classes_for_k(int k)
 {
     static const uint32_t n[7] = {0, 0, 0, 13, 199, 9364, 1530843};
     return (k >= 3 && k <= 6) ? n[k] : 0;
-}
-
-extern "C" int mk_graph_footprint(const mk_graph *g, int k, uint64_t *bytes)
-{
-    if (!g || !bytes) return fail(MK_EINVAL, "mk_graph_footprint: NULL argument");
-    if (k < 3 || k > 6) return fail(MK_ERANGE, "k=%d outside 3..6", k);
-    const uint64_t n = (uint64_t)g->n, w = (n + 31) / 32;
-    const bool big = g->n > MK_LDS_MARKS_MAX_VERTICES;  // list-built adjacency, global marks
-    const uint64_t region = big ? list_ws_words(n, (uint64_t)g->m) : 2 * n * w;
-    const uint64_t ws = 4 * (region + (n + 1) + (uint64_t)g->nnz_u);
-    const uint64_t slots = 20 * (uint64_t)g->nnz_u + 4 * ((uint64_t)g->nnz_u / 4096 + 2);
-    const uint64_t units = 16 * (uint64_t)g->nnz_u * 4;  // planning estimate
-    const uint64_t hist = 8ull * classes_for_k(k);
-    // per-workgroup arc lists of the core method (the default for k <= 5 on
-    // graphs with LDS marks), one workgroup per unit at most
-    const uint64_t scratch =
-        k <= 5 && !big ? 4ull * kParentArcCap * std::min<uint64_t>(g->nnz_u + 1, 8192) : 0;
-    // per-workgroup marks, at most 32 workgroups per CU and 1/16 of the memory
-    const uint64_t per_wave = ((n + 63) & ~63ull) * 4;
-    const uint64_t marks =
-        big ? std::min<uint64_t>((uint64_t)g->ctx->hbm_bytes / 16,
-                                 (uint64_t)g->ctx->num_cus * 32 * per_wave)
-            : 0;
-    *bytes = ws + slots + units + hist + scratch + marks + sizeof(DevGraph) + 4 * kNumCounters;
-    return MK_OK;
 }
 
 // ------------------------------------------------------------------ batch
@@ -322,10 +298,6 @@ static int batch_enqueue_typed(mk_batch *b, hipStream_t stream)
 // (k = 6, n = 500, m = 1200 0.93 -> 0.75 ms of kernel, n = 1500, m = 9000 19.7
 // -> 15.6, 0.78 and 14.8 with 2,048; 128 as 512).
 constexpr uint32_t kCoreSliceLeast = 512;
-static uint32_t slice_least(const mk_batch *b)
-{
-    return b->method == MK_METHOD_ESU ? kSliceLeast : kCoreSliceLeast;
-}
 
 // enqueue the preparation part of one pass on stream: counters and
 // histograms cleared, typed adjacency, work-unit plan (captured as a
@@ -346,8 +318,8 @@ static int batch_enqueue_prep(mk_batch *b, unsigned long long *hist, hipStream_t
     return launch_plan(b->plan_k, b->d_graphs, b->ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
                        b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
                        b->d_units, b->unit_cap, b->opts.split_threshold, spec, true,
-                       slice_least(b), (uint32_t)b->max_grid, (uint32_t)std::max(b->opts.units_per_wave, 0),
-                       b->d_counters, stream);
+                       b->slice_least, (uint32_t)b->max_grid,
+                       (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters, stream);
 }
 
 // the counting kernel over units [counters[kSliceBegin], unit_end)
@@ -415,15 +387,17 @@ static int batch_enqueue_enum(mk_batch *b, unsigned long long *hist, hipStream_t
 // from 8 graphs on, where the division's pass over the bins is the smaller
 // part (with q of 5 to 6.5, n = 700 0.73 to 0.95 of the enumeration's speed in
 // every batch; one graph of 100..1000 vertices 0.4 to 1.1).
-static bool cores6_candidate(const mk_batch *b)
+static bool cores6_candidate(const mk_graph *const *gs, int ng)
 {
     double d1 = 0, d2 = 0;
-    for (const mk_graph *g : b->graphs) {
-        d1 += (double)g->nnz_u;
-        d2 += (double)g->sum_d2;
+    int max_n = 0;
+    for (int i = 0; i < ng; ++i) {
+        d1 += (double)gs[i]->nnz_u;
+        d2 += (double)gs[i]->sum_d2;
+        max_n = std::max(max_n, gs[i]->n);
     }
     const double q = d1 > 0 ? d2 / d1 : 0.0;
-    return q >= 7.5 && b->max_n >= (b->ng < 8 ? 1200 : 900);
+    return q >= 7.5 && max_n >= (ng < 8 ? 1200 : 900);
 }
 
 // Candidates whose graphs have fewer adjacency entries than this each are
@@ -471,24 +445,95 @@ static uint64_t plan_units(int plan_k, const mk_graph *g)
 // allocates and frees a list of this length for every wave: with lists of up to
 // 8,192 40 graphs of n = 100, m = 200 took 1.23 ms at k = 5 (now 0.72), one of
 // n = 3000, m = 4500 0.88 (0.34).
-static uint64_t most_parent_arcs(const mk_batch *b)
+static uint64_t most_parent_arcs(const mk_graph *g, int k)
 {
-    uint64_t most = 1;
-    for (const mk_graph *g : b->graphs) {
-        const uint64_t d = (uint64_t)g->max_udeg;
-        const uint64_t adj = std::min<uint64_t>((uint64_t)(b->k - 3) * d, (uint64_t)g->n);
-        most = std::max(most, std::min<uint64_t>((uint64_t)g->nnz_u, adj * std::min(adj, d)) / 2);
-    }
+    const uint64_t d = (uint64_t)g->max_udeg;
+    const uint64_t adj = std::min<uint64_t>((uint64_t)(k - 3) * d, (uint64_t)g->n);
+    const uint64_t most =
+        std::max<uint64_t>(std::min<uint64_t>((uint64_t)g->nnz_u, adj * std::min(adj, d)) / 2, 1);
     return (most + 15) & ~15ull;
 }
 
+// Bytes of all the arc lists of a launch whose longest useful list is `most`:
+// at most max_waves lists, and kMostListWaves of kParentArcCap arc pairs.
+constexpr uint64_t kMostListWaves = 8192;
+constexpr uint64_t kMostListBytes = 4ull * kParentArcCap * kMostListWaves;
+static uint64_t arc_list_bytes(uint64_t most, uint64_t max_waves)
+{
+    return std::min<uint64_t>(4 * std::min(max_waves, kMostListWaves) * most, kMostListBytes);
+}
+
+// --------------------------------------------------------------- footprint
+
+// waves of a launch at most
+static uint64_t most_waves(const mk_ctx *ctx) { return 32ull * (uint64_t)ctx->num_cus; }
+
+namespace mk {
+
+// Device bytes that one graph brings to a batch kept to its least memory (see
+// batch_create): workspace, units, histogram and marks; *lists the arc lists of
+// a batch of this graph alone, which a batch has once.
+uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists)
+{
+    const uint64_t n = (uint64_t)g->n, w = (n + 31) / 32, nnz = (uint64_t)g->nnz_u;
+    const bool big = g->n > MK_LDS_MARKS_MAX_VERTICES;  // list-built adjacency, global marks
+    const uint64_t region = big ? list_ws_words(n, (uint64_t)g->m) : 2 * n * w;
+    const uint64_t ws = 4 * (region + (n + 1) + nnz);
+    const uint64_t slots = 20 * nnz + 4 * plan_tmp_words(1, g->nnz_u, (uint32_t)nnz);
+    const uint64_t units = sizeof(int4) * nnz * 4;
+    const uint64_t hist = 8ull * classes_for_k(k);
+    // per-workgroup marks, at most 32 workgroups per CU and 1/16 of the memory
+    const uint64_t per_wave = ((n + 63) & ~63ull) * 4;
+    const uint64_t marks =
+        big ? std::min<uint64_t>((uint64_t)g->ctx->hbm_bytes / 16, most_waves(g->ctx) * per_wave)
+            : 0;
+    *lists = k == 5 && !big
+                 ? std::min<uint64_t>(
+                       arc_list_bytes(most_parent_arcs(g, k), most_waves(g->ctx)),
+                       4ull * kParentArcCap * std::min<uint64_t>(nnz + 1, kMostListWaves))
+                 : 0;
+    // the parts of the two shared allocations start on 256 bytes
+    const uint64_t rounding = 16 * 256;
+    return ws + slots + units + hist + marks + sizeof(DevGraph) + 4 * kNumCounters + rounding;
+}
+
+}  // namespace mk
+
+extern "C" int mk_graph_footprint(const mk_graph *g, int k, uint64_t *bytes)
+{
+    if (!g || !bytes) return fail(MK_EINVAL, "mk_graph_footprint: NULL argument");
+    if (k < 3 || k > 6) return fail(MK_ERANGE, "k=%d outside 3..6", k);
+    const bool big = g->n > MK_LDS_MARKS_MAX_VERTICES;
+    uint64_t lists = 0;
+    const uint64_t least = graph_least_bytes(g, k, &lists);
+    const bool cores = !big && (k <= 5 || cores6_candidate(&g, 1));
+    if (k == 6 && cores)
+        lists = arc_list_bytes(most_parent_arcs(g, k), most_waves(g->ctx));
+    const HistLayout l =
+        hist_layout(1, classes_for_k(k), (int)most_waves(g->ctx), UINT64_MAX, cores);
+    *bytes = least + lists + 8 * (uint64_t)l.words();
+    return MK_OK;
+}
+
+extern "C" int mk_graph_least_footprint(const mk_graph *g, int k, uint64_t *bytes)
+{
+    if (!g || !bytes) return fail(MK_EINVAL, "mk_graph_least_footprint: NULL argument");
+    if (k < 3 || k > 6) return fail(MK_ERANGE, "k=%d outside 3..6", k);
+    uint64_t lists = 0;
+    *bytes = graph_least_bytes(g, k, &lists);
+    *bytes += lists;
+    return MK_OK;
+}
+
 // A batch of ng graphs for subgraph size k: counted with table t (k <= 6),
-// or with the k = 7 kernel and no table (t null).  lean: without the memory
-// that mk_graph_footprint does not count (the histograms' work array, the
-// arc lists of k = 6 from the (k-2)-sets).
+// or with the k = 7 kernel and no table (t null).  limit: the device bytes it
+// is to keep to, its own histograms included.  A batch that would take more
+// does without the work array, plans fewer units, has shorter arc lists and
+// at k = 6 counts from the (k-2)-sets only where the arc lists fit; what the
+// graphs' graph_least_bytes count it takes at any limit.
 static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int k,
-                        const mk_table *t, const mk_batch_opts *opts, bool lean, mk_batch **out,
-                        uint64_t most_bytes = UINT64_MAX)
+                        const mk_table *t, const mk_batch_opts *opts, uint64_t limit,
+                        mk_batch **out, uint64_t most_bytes = UINT64_MAX)
 {
     *out = nullptr;
     for (int i = 0; i < ng; ++i)
@@ -556,7 +601,7 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                     : (b->marks == MK_MARKS_LDS && b->k <= 5 ? MK_METHOD_CORES : MK_METHOD_ESU);
     // at k = 6 the choice waits for the typed adjacency
     const bool candidate = b->opts.method == MK_METHOD_AUTO && b->marks == MK_MARKS_LDS &&
-                           b->k == 6 && !lean && cores6_candidate(b);
+                           b->k == 6 && cores6_candidate(gs, ng);
     if (b->marks == MK_MARKS_LDS && big) {
         const int max_n = b->max_n;
         delete b;
@@ -653,8 +698,20 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
                                 hipMemcpyHostToDevice, ctx->stream));
     for (hipEvent_t &e : b->ev) BAIL_HIP(hipEventCreate(&e));
 
+    // what is left of the limit beside the histograms and the marks
+    const uint64_t own = t ? 8ull * (uint64_t)ng * t->num_classes : 0;
+    uint64_t most_arcs = 0;
+    for (int i = 0; i < ng && k >= 5 && k <= 6; ++i)
+        most_arcs = std::max(most_arcs, most_parent_arcs(gs[i], k));
+    const auto room = [&](uint64_t more) {
+        const uint64_t taken = b->held + own + more;
+        return limit > taken ? limit - taken : 0;
+    };
     bool typed = false;  // the typed adjacency is built
-    if (candidate && b->max_nnz < kLinksLeast) {
+    if (candidate && room(sizeof(int4) * 4 * slots) <
+                         arc_list_bytes(most_arcs, most_waves(ctx))) {
+        // no room for the arc lists
+    } else if (candidate && b->max_nnz < kLinksLeast) {
         b->method = MK_METHOD_CORES;
     } else if (candidate) {
         double linked = 0.0;
@@ -668,6 +725,15 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         typed = true;
         if (cores6_pays(b, linked)) b->method = MK_METHOD_CORES;
     }
+    // the arc lists that graph_least_bytes counts at k = 5, all of them at k = 6
+    const uint64_t lists_wanted =
+        b->method != MK_METHOD_CORES || k < 5
+            ? 0
+            : std::min<uint64_t>(arc_list_bytes(most_arcs, most_waves(ctx)),
+                                 k == 6 ? kMostListBytes
+                                        : 4ull * kParentArcCap *
+                                              std::min<uint64_t>(slots + 1, kMostListWaves));
+    b->slice_least = b->method == MK_METHOD_ESU ? kSliceLeast : kCoreSliceLeast;
     b->plan_k = b->method == MK_METHOD_CORES ? (b->k == 3 ? 2 : b->k - 1) : b->k;
     if (b->opts.split_threshold == 0)
         b->opts.split_threshold = b->method == MK_METHOD_CORES && b->k == 6 ? kCore6Split
@@ -709,37 +775,45 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         b->spec_threshold = b->opts.split_threshold;
         BAIL_HIP(hipStreamSynchronize(ctx->stream));  // the descriptors are on the device
     } else {
-        // sizing pass: typed adjacency + unit counts only
-        if (!typed)
-            rc = clear_ranges({b->d_counters, kNumCounters}, {b->d_ws, b->bits_words}, {nullptr, 0},
+        const uint64_t marks = b->mark_stride * 4 * (uint64_t)b->max_grid;
+        for (bool again = false;; again = true) {
+            // sizing pass: typed adjacency + unit counts only
+            const ClearRange all{b->d_counters, kNumCounters};
+            const ClearRange sums{b->d_counters + kPlanSums, kNumCounters - kPlanSums};
+            const ClearRange bits_of{b->d_ws, b->bits_words}, none{nullptr, 0};
+            rc = clear_ranges(typed && !again ? sums : all, typed ? none : bits_of, none,
                               ctx->stream);
-        else
-            rc = clear_ranges({b->d_counters + kPlanSums, kNumCounters - kPlanSums}, {nullptr, 0},
-                              {nullptr, 0}, ctx->stream);
-        if (!rc && !typed) rc = batch_enqueue_typed(b, ctx->stream);
-        if (!rc)
-            rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots, b->d_slot_cnt,
-                             b->d_slot_off, b->d_slot_est, b->d_slot_vi, b->d_slot_l2, b->d_scan_tmp,
-                             nullptr, 0, b->opts.split_threshold, 0, false,
-                             slice_least(b), (uint32_t)b->max_grid,
-                             (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
-                             ctx->stream);
-        if (rc) return bail(rc);
-        uint32_t cnt[kNumCounters];
-        BAIL_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost, ctx->stream));
-        BAIL_HIP(hipStreamSynchronize(ctx->stream));
-        if (cnt[kAdjOverflow] != 0)
-            return bail(fail(MK_EDEVICE, "typed adjacency exceeds its reserved size"));
-        b->units = cnt[kNumUnits];
-        b->split_pairs = cnt[kSplitPairs];
-        // the same graphs plan to the same threshold at every pass
-        std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
+            if (!rc && !typed) rc = batch_enqueue_typed(b, ctx->stream);
+            typed = true;
+            if (!rc)
+                rc = launch_plan(b->plan_k, b->d_graphs, ng, b->max_nnz, b->total_slots,
+                                 b->d_slot_cnt, b->d_slot_off, b->d_slot_est, b->d_slot_vi,
+                                 b->d_slot_l2, b->d_scan_tmp, nullptr, 0, b->opts.split_threshold,
+                                 0, false, b->slice_least, (uint32_t)b->max_grid,
+                                 (uint32_t)std::max(b->opts.units_per_wave, 0), b->d_counters,
+                                 ctx->stream);
+            if (rc) return bail(rc);
+            uint32_t cnt[kNumCounters];
+            BAIL_HIP(hipMemcpyAsync(cnt, b->d_counters, sizeof(cnt), hipMemcpyDeviceToHost,
+                                    ctx->stream));
+            BAIL_HIP(hipStreamSynchronize(ctx->stream));
+            if (cnt[kAdjOverflow] != 0)
+                return bail(fail(MK_EDEVICE, "typed adjacency exceeds its reserved size"));
+            b->units = cnt[kNumUnits];
+            b->split_pairs = cnt[kSplitPairs];
+            // the same graphs plan to the same threshold at every pass
+            std::memcpy(&b->spec_threshold, &cnt[kPlanThreshold], sizeof(b->spec_threshold));
+            // within the limit: children whole, then fewer ranges, down to a
+            // unit a node, of which there are at most half as many as slots
+            if (b->units <= slots || sizeof(int4) * b->units <= room(marks + lists_wanted)) break;
+            if (b->slice_least) b->slice_least = 0;
+            else b->opts.split_threshold = 8 * std::max(b->opts.split_threshold, b->spec_threshold);
+        }
     }
     b->unit_cap = std::max<uint32_t>((uint32_t)b->units, 1);
     b->grid = (int)std::min<uint64_t>((uint64_t)b->max_grid, std::max<uint64_t>(b->units, 1));
-    if (t && !lean)
-        b->layout = hist_layout(ng, t->num_classes, b->grid, b->units,
-                                b->method == MK_METHOD_CORES);
+    if (b->marks == MK_MARKS_GLOBAL) b->mark_bytes = b->mark_stride * 4 * (size_t)b->grid;
+    const uint64_t unit_bytes = sizeof(int4) * (uint64_t)b->unit_cap;
     if (b->method == MK_METHOD_CORES && k >= 5) {
         // Lists of kParentArcCap arc pairs, longer (to 4 times) where the
         // launch has fewer waves than the footprint counts with: a parent
@@ -751,9 +825,16 @@ static int batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int 
         const uint64_t cap = std::min<uint64_t>(
             std::max<uint64_t>(waves * kParentArcCap / (uint64_t)b->grid, kParentArcCap),
             4 * kParentArcCap);
-        b->arc_cap = (uint32_t)std::min<uint64_t>(cap, most_parent_arcs(b));
+        const uint64_t fit = room(unit_bytes) / (4 * (uint64_t)b->grid) & ~15ull;
+        b->arc_cap = (uint32_t)std::min(std::min(cap, most_arcs), std::max<uint64_t>(fit, 16));
     }
-    if (b->marks == MK_MARKS_GLOBAL) b->mark_bytes = b->mark_stride * 4 * (size_t)b->grid;
+    if (t) {
+        b->layout = hist_layout(ng, t->num_classes, b->grid, b->units,
+                                b->method == MK_METHOD_CORES);
+        if (8 * (uint64_t)b->layout.words() >
+            room(unit_bytes + b->mark_bytes + 4ull * b->arc_cap * (uint64_t)b->grid))
+            b->layout = HistLayout();
+    }
     rc = batch_alloc_run(b);
     if (rc) return bail(rc);
 #undef BAIL_HIP
@@ -767,14 +848,14 @@ extern "C" int mk_batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t n
     if (!ctx || !t || !out || (ng > 0 && !gs)) return fail(MK_EINVAL, "mk_batch_create: NULL argument");
     if (ng < 0) return fail(MK_EINVAL, "mk_batch_create: ng=%d < 0", ng);
     if (t->ctx != ctx || !t->d_table) return fail(MK_EINVAL, "mk_batch_create: table of another context");
-    return batch_create(ctx, gs, ng, t->k, t, opts, false, out);
+    return batch_create(ctx, gs, ng, t->k, t, opts, UINT64_MAX, out);
 }
 
 namespace mk {
-int batch_create_lean(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
-                      const mk_batch_opts *opts, mk_batch **out)
+int batch_create_within(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
+                        const mk_batch_opts *opts, uint64_t limit, mk_batch **out)
 {
-    return batch_create(ctx, gs, ng, t->k, t, opts, true, out);
+    return batch_create(ctx, gs, ng, t->k, t, opts, limit, out);
 }
 }  // namespace mk
 
@@ -1030,13 +1111,22 @@ extern "C" int mk_batch_debug(mk_batch *b, int32_t flags)
     return MK_OK;
 }
 
+extern "C" int mk_batch_create_within(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
+                                      const mk_table *t, const mk_batch_opts *opts,
+                                      uint64_t limit, mk_batch **out)
+{
+    if (!ctx || !t || !out || ng < 0 || (ng > 0 && !gs) || t->ctx != ctx || !t->d_table)
+        return fail(MK_EINVAL, "mk_batch_create_within: bad argument");
+    return batch_create(ctx, gs, ng, t->k, t, opts, limit, out);
+}
+
 extern "C" int mk_batch_create_capped(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
                                       const mk_table *t, const mk_batch_opts *opts,
                                       uint64_t most_bytes, mk_batch **out)
 {
     if (!ctx || !t || !out || ng < 0 || (ng > 0 && !gs) || t->ctx != ctx || !t->d_table)
         return fail(MK_EINVAL, "mk_batch_create_capped: bad argument");
-    return batch_create(ctx, gs, ng, t->k, t, opts, false, out, most_bytes);
+    return batch_create(ctx, gs, ng, t->k, t, opts, UINT64_MAX, out, most_bytes);
 }
 
 extern "C" int mk_batch_bytes(const mk_batch *b, uint64_t *bytes)
@@ -1394,7 +1484,7 @@ extern "C" int mk_count7(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, int
     o.adjacency = big ? MK_ADJ_LISTS : MK_ADJ_BITS;
     o.marks = big ? MK_MARKS_GLOBAL : MK_MARKS_LDS;
     mk_batch *b = nullptr;
-    int rc = batch_create(ctx, gs, ng, 7, nullptr, &o, false, &b);
+    int rc = batch_create(ctx, gs, ng, 7, nullptr, &o, UINT64_MAX, &b);
     if (rc) return rc;
     // class tables of the size the last count needed (2^10 slots per graph
     // at first), 4x larger after an overflow

@@ -209,8 +209,8 @@ static Group *start_group(mk_server *s, int k, std::vector<Request *> reqs, uint
             std::lock_guard<std::mutex> lock(s->mu);
             lean = s->used_bytes + kSpareBytes > s->opts.hbm_budget_bytes;
         }
-        rc = lean ? batch_create_lean(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, &gp->batch)
-                  : mk_batch_create(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, &gp->batch);
+        rc = batch_create_within(s->ctx, gs.data(), (int32_t)gs.size(), t, &o,
+                                 lean ? est_bytes : UINT64_MAX, &gp->batch);
     }
     if (rc == MK_OK) rc = batch_unit_begins(gp->batch, &gp->unit_begin);
     if (rc == MK_OK) rc = batch_prepare(gp->batch, s->streams[gp->stream]);
@@ -410,9 +410,8 @@ extern "C" int mk_submit(mk_server *s, const mk_graph *g, int k, uint64_t *ticke
     if (!s || !g || !ticket) return fail(MK_EINVAL, "mk_submit: NULL argument");
     if (k < 3 || k > 6) return fail(MK_ERANGE, "mk_submit: k=%d outside 3..6", k);
     if (g->ctx != s->ctx) return fail(MK_EINVAL, "mk_submit: graph of another context");
-    uint64_t est = 0;
-    int rc = mk_graph_footprint(g, k, &est);
-    if (rc) return rc;
+    uint64_t lists = 0;
+    const uint64_t own = graph_least_bytes(g, k, &lists), est = own + lists;
     std::lock_guard<std::mutex> lock(s->mu);
     if (s->stopping) return fail(MK_EBUSY, "mk_submit: server is stopping");
     if (est > s->opts.hbm_budget_bytes)

@@ -9,11 +9,17 @@
 
 namespace mk {
 
+// Device bytes of one graph in a batch kept to its least memory, and of the arc
+// lists of a batch of this graph alone (a batch has them once).
+uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists);
+
+// mk_batch_create for a batch that keeps to `limit` device bytes, its own
+// histograms included, where that is at least its graphs' graph_least_bytes.
+int batch_create_within(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
+                        const mk_batch_opts *opts, uint64_t limit, mk_batch **out);
+
 // First work unit of every graph of a batch after mk_batch_create (its
 // sizing plan), plus the total: ng + 1 values.  Blocks.
-// mk_batch_create without the memory that mk_graph_footprint does not count
-int batch_create_lean(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
-                      const mk_batch_opts *opts, mk_batch **out);
 int batch_unit_begins(mk_batch *b, std::vector<uint32_t> *out);
 
 // Finish graph gi's histogram (the core method's division) and copy it to

@@ -124,6 +124,9 @@ SIGNATURES = {
     "mk_batch_debug": (ctypes.c_int, [_P, _I32]),
     "mk_batch_create_capped": (ctypes.c_int, [_P, _P, _I32, _P, ctypes.POINTER(BatchOpts), _U64,
                                               ctypes.POINTER(_P)]),
+    "mk_batch_create_within": (ctypes.c_int, [_P, _P, _I32, _P, ctypes.POINTER(BatchOpts), _U64,
+                                              ctypes.POINTER(_P)]),
+    "mk_graph_least_footprint": (ctypes.c_int, [_P, ctypes.c_int, ctypes.POINTER(_U64)]),
     "mk_batch_bytes": (ctypes.c_int, [_P, ctypes.POINTER(_U64)]),
     "mk_server_start": (ctypes.c_int, [_P, ctypes.POINTER(ServerOpts), ctypes.POINTER(_P)]),
     "mk_submit": (ctypes.c_int, [_P, _P, ctypes.c_int, ctypes.POINTER(_U64)]),
@@ -392,6 +395,22 @@ def mk_batch_create_capped(ctx: int, gs: Sequence[int], t: int, most_bytes: int,
     return h.value
 
 
+def mk_batch_create_within(ctx: int, gs: Sequence[int], t: int, limit: int, **opts) -> int:
+    """Test hook (include/motifs_testing.h): keeps to that much device memory."""
+    h = _P()
+    _check(library().mk_batch_create_within(ctx, _handles(gs), len(gs), t,
+                                            ctypes.byref(BatchOpts(**opts)), limit,
+                                            ctypes.byref(h)))
+    return h.value
+
+
+def mk_graph_least_footprint(g: int, k: int) -> int:
+    """Test hook (include/motifs_testing.h)."""
+    b = _U64()
+    _check(library().mk_graph_least_footprint(g, k, ctypes.byref(b)))
+    return b.value
+
+
 def mk_batch_debug(b: int, flags: int) -> None:
     """Test hook (include/motifs_testing.h): alternative internal paths."""
     _check(library().mk_batch_debug(b, flags))
@@ -527,11 +546,14 @@ class Batch:
         self.table = table
         debug = opts.pop("debug_flags", 0)
         most_bytes = opts.pop("most_bytes", None)
+        limit = opts.pop("limit", None)
         gs = [g.handle for g in graphs]
-        if most_bytes is None:
-            self.handle = mk_batch_create(ctx.handle, gs, table.handle, **opts)
-        else:
+        if most_bytes is not None:
             self.handle = mk_batch_create_capped(ctx.handle, gs, table.handle, most_bytes, **opts)
+        elif limit is not None:
+            self.handle = mk_batch_create_within(ctx.handle, gs, table.handle, limit, **opts)
+        else:
+            self.handle = mk_batch_create(ctx.handle, gs, table.handle, **opts)
         if debug:
             try:
                 mk_batch_debug(self.handle, debug)
