@@ -46,6 +46,12 @@ int mk_graph_least_footprint(const mk_graph *g, int k, uint64_t *bytes);
 /* Device bytes the batch holds, its own histograms included. */
 int mk_batch_bytes(const mk_batch *b, uint64_t *bytes);
 
+/* What the server has done so far: groups made, groups that could use more
+   memory than its budget left them, and the most device bytes charged to the
+   budget. */
+int mk_server_counts(mk_server *s, uint64_t *groups, uint64_t *short_groups,
+                     uint64_t *peak_bytes);
+
 #ifdef __cplusplus
 }
 #endif

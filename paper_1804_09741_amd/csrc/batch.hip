@@ -497,6 +497,14 @@ uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists)
     return ws + slots + units + hist + marks + sizeof(DevGraph) + 4 * kNumCounters + rounding;
 }
 
+uint64_t most_list_bytes() { return kMostListBytes; }
+
+uint64_t batch_extra_bytes(const mk_ctx *ctx, int k, int ng)
+{
+    const HistLayout l = hist_layout(ng, classes_for_k(k), (int)most_waves(ctx), UINT64_MAX, true);
+    return 8 * (uint64_t)l.words() + (k == 6 ? kMostListBytes : 0);
+}
+
 }  // namespace mk
 
 extern "C" int mk_graph_footprint(const mk_graph *g, int k, uint64_t *bytes)

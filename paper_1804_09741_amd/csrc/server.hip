@@ -6,7 +6,8 @@
 // resident and runs the requests through the same kernels as mk_count:
 //
 //   submit   -> FIFO queue
-//   admit    -> while the head fits the HBM budget and a slot is free; the
+//   admit    -> while the head fits the HBM budget (its graph's part, and the
+//               arc lists that its group has once) and a slot is free; the
 //               requests admitted together are grouped by k and by size
 //               class of n (ceil log2), and each group becomes one batch (one typed-adjacency and plan pass, one
 //               persistent launch per slice for all its graphs), its graphs
@@ -46,8 +47,6 @@ constexpr int kServerStreams = 4;  // the hardware queues a process gets
 constexpr uint64_t kDefaultBudget = 8ull << 30;
 constexpr int kDefaultSlots = 64;
 constexpr int kDefaultTickUnits = 8192;
-// the most a batch takes beyond its footprint (work array and arc lists)
-constexpr uint64_t kSpareBytes = 640ull << 20;
 // slices of a group queued on its stream at once: the next one is already
 // there when one ends, so the host's polling leaves no gap
 constexpr int kInFlight = 2;
@@ -60,7 +59,8 @@ struct Request {
     uint64_t ticket = 0;
     const mk_graph *g = nullptr;
     int k = 0;
-    uint64_t est_bytes = 0;
+    uint64_t est_bytes = 0;   // its graph's part of a batch, at the least
+    uint64_t list_bytes = 0;  // the arc lists of a batch of it alone
     State state = State::Queued;
     int status = MK_OK;
     std::string error;
@@ -114,6 +114,9 @@ struct mk_server {
     // wait for every kernel in flight); their bytes stay in used_bytes
     std::vector<std::pair<mk_batch *, uint64_t>> graveyard;
     std::chrono::steady_clock::time_point t0;
+    struct {
+        uint64_t groups = 0, short_groups = 0, peak_bytes = 0;
+    } counts;  // see mk_server_counts
 
     double now_us() const
     {
@@ -129,6 +132,9 @@ static int size_class(int n)
     while (c < 31 && (1 << c) < n) ++c;
     return c;
 }
+
+// requests of one key admitted together form a group
+static int group_key(const Request *r) { return r->k * 64 + size_class(r->g->n); }
 
 // a request leaves the server (its waiter is woken)
 static void finish_request(mk_server *s, Request *r, State st, int status, const char *why)
@@ -171,6 +177,20 @@ static void bury(mk_server *s)
     s->used_bytes -= std::min(s->used_bytes, freed);
 }
 
+// what the budget leaves beside everything charged to it
+static uint64_t spare_bytes(mk_server *s)
+{
+    std::lock_guard<std::mutex> lock(s->mu);
+    const uint64_t budget = s->opts.hbm_budget_bytes;
+    return budget > s->used_bytes ? budget - s->used_bytes : 0;
+}
+
+static bool has_graves(mk_server *s)
+{
+    std::lock_guard<std::mutex> lock(s->mu);
+    return !s->graveyard.empty();
+}
+
 // fail every request of a group that is not collected yet
 static void fail_group(mk_server *s, Group *gp, int status, const char *why)
 {
@@ -203,14 +223,21 @@ static Group *start_group(mk_server *s, int k, std::vector<Request *> reqs, uint
     if (rc == MK_OK) {
         mk_batch_opts o{};
         o.use_graph = -1;
-        // near the budget's end the batch keeps to its estimated footprint
-        bool lean;
+        // the batch may take what is left of the budget; where that is less
+        // than it can use, the finished batches' memory comes first
+        const uint64_t want = batch_extra_bytes(s->ctx, k, (int)gs.size());
+        uint64_t spare = spare_bytes(s);
+        if (spare < want && has_graves(s)) {
+            bury(s);
+            spare = spare_bytes(s);
+        }
         {
             std::lock_guard<std::mutex> lock(s->mu);
-            lean = s->used_bytes + kSpareBytes > s->opts.hbm_budget_bytes;
+            ++s->counts.groups;
+            s->counts.short_groups += spare < want;
         }
-        rc = batch_create_within(s->ctx, gs.data(), (int32_t)gs.size(), t, &o,
-                                 lean ? est_bytes : UINT64_MAX, &gp->batch);
+        rc = batch_create_within(s->ctx, gs.data(), (int32_t)gs.size(), t, &o, est_bytes + spare,
+                                 &gp->batch);
     }
     if (rc == MK_OK) rc = batch_unit_begins(gp->batch, &gp->unit_begin);
     if (rc == MK_OK) rc = batch_prepare(gp->batch, s->streams[gp->stream]);
@@ -232,6 +259,7 @@ static Group *start_group(mk_server *s, int k, std::vector<Request *> reqs, uint
         std::lock_guard<std::mutex> lock(s->mu);
         const uint64_t actual = batch_device_bytes(gp->batch);
         s->used_bytes = s->used_bytes - std::min(s->used_bytes, gp->bytes) + actual;
+        s->counts.peak_bytes = std::max(s->counts.peak_bytes, s->used_bytes);
         gp->bytes = actual;
     } else {
         gp->status = rc;
@@ -263,18 +291,27 @@ static void server_loop(mk_server *s)
         bool need_bury = false;
         {
             std::lock_guard<std::mutex> lock(s->mu);
-            const bool blocked = !s->queue.empty() &&
-                                 s->used_bytes + s->queue.front()->est_bytes > budget;
+            const bool blocked =
+                !s->queue.empty() && s->used_bytes + s->queue.front()->est_bytes +
+                                             s->queue.front()->list_bytes > budget;
             need_bury = !s->graveyard.empty() && (s->groups.empty() || blocked);
         }
         if (need_bury) bury(s);
         // admit: FIFO while a slot is free and the head fits the budget
         std::vector<Request *> admitted;
+        std::unordered_map<int, uint64_t> lists;  // arc lists charged, by group
         {
             std::unique_lock<std::mutex> lock(s->mu);
+            // a group has its arc lists once: what another request adds to them
+            const auto more_lists = [&](const Request *r) {
+                const auto it = lists.find(group_key(r));
+                const uint64_t have = it == lists.end() ? 0 : it->second;
+                return std::min(r->list_bytes, most_list_bytes() - std::min(have, most_list_bytes()));
+            };
             auto can_admit = [&] {
                 return !s->queue.empty() && s->active_requests < slots &&
-                       s->used_bytes + s->queue.front()->est_bytes <= budget;
+                       s->used_bytes + s->queue.front()->est_bytes +
+                               more_lists(s->queue.front()) <= budget;
             };
             if (s->groups.empty() && s->graveyard.empty())
                 s->cv_work.wait(lock, [&] { return s->stopping || can_admit(); });
@@ -285,7 +322,9 @@ static void server_loop(mk_server *s)
                 s->queue.pop_front();
                 r->state = State::Active;
                 r->times.admit_us = s->now_us();
-                s->used_bytes += r->est_bytes;
+                const uint64_t more = more_lists(r);
+                lists[group_key(r)] += more;
+                s->used_bytes += r->est_bytes + more;
                 ++s->active_requests;
                 admitted.push_back(r);
             }
@@ -297,7 +336,7 @@ static void server_loop(mk_server *s)
         // one's occupancy)
         std::vector<std::pair<int, std::vector<Request *>>> parts;
         for (Request *r : admitted) {
-            const int key = r->k * 64 + size_class(r->g->n);
+            const int key = group_key(r);
             auto it = std::find_if(parts.begin(), parts.end(),
                                    [key](const auto &p) { return p.first == key; });
             if (it == parts.end()) {
@@ -307,7 +346,7 @@ static void server_loop(mk_server *s)
             it->second.push_back(r);
         }
         for (auto &part : parts) {
-            uint64_t bytes = 0;
+            uint64_t bytes = lists[part.first];
             for (Request *r : part.second) bytes += r->est_bytes;
             Group *gp = start_group(s, part.first / 64, part.second, bytes);
             if (gp->status != MK_OK) {
@@ -421,7 +460,8 @@ extern "C" int mk_submit(mk_server *s, const mk_graph *g, int k, uint64_t *ticke
     r->ticket = s->next_ticket++;
     r->g = g;
     r->k = k;
-    r->est_bytes = est;
+    r->est_bytes = own;
+    r->list_bytes = lists;
     r->times.submit_us = s->now_us();
     r->times.admit_us = -1;
     r->times.done_us = -1;
@@ -460,6 +500,18 @@ extern "C" int mk_wait(mk_server *s, uint64_t ticket, uint64_t *hist, uint32_t c
     s->all.erase(it);
     delete r;
     return rc;
+}
+
+extern "C" int mk_server_counts(mk_server *s, uint64_t *groups, uint64_t *short_groups,
+                                uint64_t *peak_bytes)
+{
+    if (!s || !groups || !short_groups || !peak_bytes)
+        return fail(MK_EINVAL, "mk_server_counts: NULL argument");
+    std::lock_guard<std::mutex> lock(s->mu);
+    *groups = s->counts.groups;
+    *short_groups = s->counts.short_groups;
+    *peak_bytes = s->counts.peak_bytes;
+    return MK_OK;
 }
 
 extern "C" int mk_server_stop(mk_server *s)

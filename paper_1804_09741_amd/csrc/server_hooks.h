@@ -13,6 +13,13 @@ namespace mk {
 // lists of a batch of this graph alone (a batch has them once).
 uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists);
 
+// the arc lists of any batch at most
+uint64_t most_list_bytes();
+
+// Device bytes that a batch of ng graphs can use beyond its least, at most: the
+// histograms' work array, and the arc lists of k = 6.
+uint64_t batch_extra_bytes(const mk_ctx *ctx, int k, int ng);
+
 // mk_batch_create for a batch that keeps to `limit` device bytes, its own
 // histograms included, where that is at least its graphs' graph_least_bytes.
 int batch_create_within(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,

@@ -131,6 +131,8 @@ SIGNATURES = {
     "mk_server_start": (ctypes.c_int, [_P, ctypes.POINTER(ServerOpts), ctypes.POINTER(_P)]),
     "mk_submit": (ctypes.c_int, [_P, _P, ctypes.c_int, ctypes.POINTER(_U64)]),
     "mk_wait": (ctypes.c_int, [_P, _U64, _P, _U32, _I32, ctypes.POINTER(RequestTimes)]),
+    "mk_server_counts": (ctypes.c_int, [_P, ctypes.POINTER(_U64), ctypes.POINTER(_U64),
+                                        ctypes.POINTER(_U64)]),
     "mk_server_stop": (ctypes.c_int, [_P]),
     "mk_status_str": (ctypes.c_char_p, [ctypes.c_int]),
     "mk_last_error": (ctypes.c_char_p, []),
@@ -488,6 +490,13 @@ def mk_wait(s: int, ticket: int, num_classes: int, timeout_ms: int = -1):
                              ctypes.byref(times)))
     return hist, {"submit_us": times.submit_us, "admit_us": times.admit_us,
                   "done_us": times.done_us}
+
+
+def mk_server_counts(s: int) -> Tuple[int, int, int]:
+    """Test hook (include/motifs_testing.h): groups, short groups, peak bytes."""
+    a, b, c = _U64(), _U64(), _U64()
+    _check(library().mk_server_counts(s, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)))
+    return a.value, b.value, c.value
 
 
 def mk_server_stop(s: int) -> None:
