@@ -357,8 +357,9 @@ void mk_batch_free(mk_batch *b);
    graph by enumeration, equal to mk_count's histogram, with every buffer of
    the path other than the caller's -- counters, typed adjacency, bit
    matrices, planner slots and work units -- taken from one static device
-   array of mk_static_scratch_bytes() bytes (64 MiB) that the library holds
-   on each device it runs on until the process ends.  No hipMalloc, hipFree
+   array of mk_static_scratch_bytes() bytes (64 MiB; the planner's sums have 1
+   KiB beside it) that the library holds on each device it runs on until the
+   process ends.  No hipMalloc, hipFree
    or allocating library call is made.  g: a loaded graph with n <=
    MK_LDS_MARKS_MAX_VERTICES whose workspace fits the array (about 8 n^2/32 +
    24 |delta| bytes plus the work units), else MK_ERANGE with a message
@@ -373,7 +374,8 @@ void mk_batch_free(mk_batch *b);
 int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t, uint64_t *d_hist,
                     void *stream);
 
-/* Size in bytes of the static device array of mk_count_static. */
+/* Size in bytes of the static device array of mk_count_static, the planner's
+   sums aside. */
 uint64_t mk_static_scratch_bytes(void);
 
 /* H_7 of ng graphs.  Section 1 counts 880,471,142 classes of 7-vertex

@@ -6,15 +6,17 @@
 // besides the caller's graph, table and histogram -- counters, the graph's
 // descriptor, bit matrices, typed lists, planner slots, scan workspace and
 // work units -- is carved from one file-scope device array, `scratch`, of
-// kStaticScratchBytes.  Its device address is looked up once per device at
+// kScratchBytes.  Its device address is looked up once per device at
 // mk_init (static_scratch_init) and kept per device; host code never passes
 // the array's own name to a kernel or a copy.
 //
 // Every call on a device shares that device's array and leaves its contents
-// behind; each call clears what must start at zero (counters, bit matrices,
-// the caller's histogram) with fill kernels.  Calls through one context are
-// serialised (the context lock, and the call blocks until its work is done);
-// calls from two contexts on one device at the same time race on the array.
+// behind; each call clears what must start at zero (counters, bit matrices, the
+// histogram's work array or, where there is no room for one, the caller's
+// histogram, which the finishing kernel overwrites otherwise) with a kernel.
+// Calls through one context are serialised (the context lock, and the call
+// blocks until its work is done); calls from two contexts on one device at the
+// same time race on the array.
 #include <algorithm>
 #include <mutex>
 
@@ -22,10 +24,12 @@
 
 namespace mk {
 
+// 64 MiB, and the planner's sums beside the other counters
 constexpr size_t kStaticScratchBytes = 64ull << 20;
+constexpr size_t kScratchBytes = kStaticScratchBytes + 4 * (kNumCounters - kPlanSums);
 
 // the static device array (one copy per device, for the life of the process)
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 
@@ -119,13 +123,12 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     const size_t o_scan = take(4ull * scan_tmp_words(nnz));
     const size_t o_units = off;
     uint64_t unit_cap =
-        o_units < kStaticScratchBytes ? (kStaticScratchBytes - o_units) / sizeof(int4) : 0;
+        o_units < kScratchBytes ? (kScratchBytes - o_units) / sizeof(int4) : 0;
     if (unit_cap < kMinStaticUnits)
         return fail(MK_ERANGE,
                     "mk_count_static: graph (n=%d, %lld adjacency entries) needs %zu bytes of "
                     "workspace; the static scratch holds %zu",
-                    g->n, (long long)nnz, o_units + kMinStaticUnits * sizeof(int4),
-                    kStaticScratchBytes);
+                    g->n, (long long)nnz, o_units + kMinStaticUnits * sizeof(int4), kScratchBytes);
     uint32_t *counters = reinterpret_cast<uint32_t *>(base + o_cnt);
     DevGraph *dg = reinterpret_cast<DevGraph *>(base + o_dg);
     uint32_t *slots = reinterpret_cast<uint32_t *>(base + o_slot);
@@ -168,7 +171,7 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     size_t o_work = 0;
     const auto work_fits = [&](uint64_t most_units) {
         o_work = round_up(o_units + most_units * sizeof(int4), 256);
-        return o_work + 8 * layout.words() <= kStaticScratchBytes;
+        return o_work + 8 * layout.words() <= kScratchBytes;
     };
     if (layout.graph_words && slices && work_fits(most_whole + 2 * target))
         unit_cap = (o_work - o_units) / sizeof(int4);
