@@ -1163,12 +1163,14 @@ extern "C" void mk_batch_free(mk_batch *b)
 // what compares); the histograms go to host memory in *hist
 static int time_candidate(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, const mk_table *t,
                           const mk_batch_opts &o, int trials, double *ms,
-                          std::vector<uint64_t> *hist, int *waves_per_cu = nullptr)
+                          std::vector<uint64_t> *hist, int *waves_per_cu = nullptr,
+                          int *method = nullptr)
 {
     mk_batch *b = nullptr;
     int rc = mk_batch_create(ctx, gs, ng, t, &o, &b);
     if (rc) return rc;
     if (waves_per_cu) *waves_per_cu = b->max_grid / std::max(ctx->num_cus, 1);
+    if (method) *method = b->method;
     double best = 1e30;
     for (int i = 0; i < trials && rc == MK_OK; ++i) {
         rc = mk_batch_run(b, nullptr, nullptr);
@@ -1196,8 +1198,8 @@ extern "C" int mk_autotune(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, c
     cur.use_graph = 1;
     std::vector<uint64_t> ref, h;
     double cur_ms = 0;
-    int per_cu = 0;
-    int rc = time_candidate(ctx, gs, ng, t, cur, trials, &cur_ms, &ref, &per_cu);
+    int per_cu = 0, method = MK_METHOD_ESU;
+    int rc = time_candidate(ctx, gs, ng, t, cur, trials, &cur_ms, &ref, &per_cu, &method);
     if (rc) return rc;
     if (default_ms) *default_ms = cur_ms;
     auto trial = [&](mk_batch_opts o) -> int {
@@ -1215,8 +1217,8 @@ extern "C" int mk_autotune(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng, c
     // coordinate search: method, arc tests, split floor, units per grab,
     // waves per CU
     {
-        mk_batch_opts o = cur;
-        o.method = MK_METHOD_CORES;
+        mk_batch_opts o = cur;  // the method that the defaults are not
+        o.method = method == MK_METHOD_CORES ? MK_METHOD_ESU : MK_METHOD_CORES;
         if ((rc = trial(o))) return rc;
     }
     {
