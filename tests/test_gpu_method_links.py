@@ -49,9 +49,11 @@ CASES = {  # name: (graphs, method)
     "powerlaw8": (lambda r: [I.chung_lu_digraph(1000, 2500, 2.2, 60, 0.0, r) for _ in range(8)],
                   M.METHOD_CORES),
     "rings8": (lambda r: [_ring(900, 8, r) for _ in range(8)], M.METHOD_ESU),
-    # 125 of 1,200 vertices on a ring: 1,000 adjacency entries, no look at links
-    "few_entries": (lambda r: [_padded(_ring(125, 8, r), 1200)], M.METHOD_CORES),
-    "more_entries": (lambda r: [_padded(_ring(129, 8, r), 1200)], M.METHOD_ESU),
+    # 47 of 1,200 vertices on a ring: 376 adjacency entries, no look at links
+    "few_entries": (lambda r: [_padded(_ring(47, 8, r), 1200)], M.METHOD_CORES),
+    "more_entries": (lambda r: [_padded(_ring(48, 8, r), 1200)], M.METHOD_ESU),
+    "few_entries8": (lambda r: [_padded(_ring(47, 8, r), 900) for _ in range(8)], M.METHOD_CORES),
+    "more_entries9": (lambda r: [_padded(_ring(47, 8, r), 900) for _ in range(9)], M.METHOD_ESU),
 }
 
 
