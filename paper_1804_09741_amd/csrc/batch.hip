@@ -272,12 +272,12 @@ static EnumConfig enum_config(const mk_batch *b)
     // Queues of a range each keep a batch's graphs in one L2.  A launch of
     // fewer graphs than queues gains no locality that way, and dealing its
     // units out in turn spreads the costly roots over the queues: k = 5 by
-    // enumeration, n = 1000, m = 3000 (4 units a wave) 0.735 -> 0.607 ms, one
-    // graph of 131,073 vertices on sorted lists at k = 6 (66 units a wave)
-    // 27.7 -> 26.4 ms.  With many units a wave on bit matrices the ranges are
-    // better: k = 5, n = 5000, m = 30000 (38 units a wave) 30.3 against 32.5 ms.
-    c.mix = b->ng < kQueues &&
-            (b->units < 16 * (uint64_t)b->grid || b->adjacency == MK_ADJ_LISTS);
+    // enumeration, n = 1000, m = 3000 (4 units a wave) 0.735 -> 0.607 ms.  With
+    // many units a wave the ranges are better: k = 5, n = 5000, m = 30000 (38
+    // units a wave) 30.3 against 32.5 ms, k = 6 on sorted lists, 131,072
+    // vertices (66 units a wave) 23.3 against 23.5, 2^20 (463) 187.7 against
+    // 190.4.
+    c.mix = b->ng < kQueues && b->units < 16 * (uint64_t)b->grid;
     c.hist = b->layout;
     return c;
 }
