@@ -398,7 +398,7 @@ def _k7(ctx, M, I, torch):
          "kernel %.1f ms; first call %.1f ms; cache %d of %d slots" % (
              sub, kern, res["value"], res["call_ms"], kern_warm, res["first_call_ms"], used,
              slots))
-    # one graph past the LDS limit (marks and tags in device memory)
+    # one graph past the LDS limit (marks in device memory)
     wl = I.workload_k6_large(1 << 17)
     g = ctx.load_graph(*wl.graphs[0])
     try:

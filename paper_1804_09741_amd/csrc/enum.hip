@@ -1,37 +1,8 @@
 // Enumeration of connected induced k-subgraphs, their adjacency codes, the
 // O(1) class lookup (Section 3.2) and the histogram H_k (Problem Motifs-k).
 //
-// One 64-lane wavefront is one workgroup.  Waves are persistent: each takes
-// work units from global queues until they are empty.  The unit list is cut
-// into eight ranges with a head each (one per XCD, on separate cache lines);
-// a wave starts on the range of its own XCD (workgroups are dealt to the
-// XCDs round-robin, so consecutive units of one graph stay in one L2) and
-// then helps the others.  Units are grabbed a few at a time, so the head
-// atomics stay far below their throughput limit.
-// A unit is a first-level ESU node (root v, first extension vertex w_i),
-// possibly restricted to a range of that node's children (hub splitting).
-//
-// Per wave, LDS holds
-//   mark[n]        for every vertex x, its relation to the current members
-//                  s_0..s_d of the growing subgraph: "in" bit d set iff arc
-//                  s_d -> x, "out" bit OUTB+d set iff arc x -> s_d.  With the
-//                  in bits spread at stride k-1, the code bits that a vertex
-//                  adds when it joins at position p are
-//                      (out << p(k-1)) | (in << (p-1))
-//                  -- exactly bits b(i,p) = i(k-1)+p-1 and b(p,i) = p(k-1)+i
-//                  of the adjacency code.  mark[x] == 0 also says "x is
-//                  neither a member nor a neighbour of one" (the exclusive
-//                  neighbourhood test of ESU).
-//   seg[l][.]      the vertices that joined the extension list when member
-//                  s_l was added (s_0's are the root's larger neighbours).
-// A node's extension list is the concatenation of the unconsumed tails of
-// seg[0..d]; it is never copied.
-//
-// Adding a member scans its typed adjacency list (Section 2's A/B/C types)
-// with all 64 lanes: each lane reads the mark of one neighbour, a ballot and
-// a lane-prefix count compact the new extension vertices into seg[d], and the
-// lane ORs the member's two bits into the neighbour's mark.  Removing it
-// clears those bits again, so marks are all zero between units.
+// The walk itself -- work units, per-wave marks and extension segments, member
+// push and pop, the hash of pending counts -- is in esu.h.
 //
 // At the last level every extension vertex u closes one k-subgraph: lanes
 // take one u each, read mark[u] and form the code with two shifts and an OR

@@ -10,10 +10,11 @@
 // into eight ranges with a head each (one per XCD, on separate cache lines);
 // a wave starts on the range of its own XCD (workgroups are dealt to the
 // XCDs round-robin, so consecutive units of one graph stay in one L2) and
-// then helps the others.  Units are grabbed a few at a time, so the head
-// atomics stay far below their throughput limit.
+// then looks into others (queue.h).  Units are grabbed a few at a time, so the
+// head atomics stay far below their throughput limit.
 // A unit is a first-level ESU node (root v, first extension vertex w_i),
-// possibly restricted to a range of that node's children (hub splitting).
+// possibly restricted to a range of that node's children, or to a slice of
+// one child's own children (hub splitting).
 //
 // Per wave, LDS holds
 //   mark[n]        for every vertex x, its relation to the current members
@@ -49,8 +50,6 @@
 #include "internal.h"
 
 namespace mk {
-
-
 
 // members whose extension segment is kept: positions 0..k-3 (k >= 4; the
 // last two levels are flat), positions 0..1 for k = 3

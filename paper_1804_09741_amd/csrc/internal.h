@@ -199,7 +199,7 @@ int launch_typed_csr(const DevGraph *d_graphs, int ng, int max_n, int64_t max_m,
 // nullptr: sizing only).  k = 2 plans one unit per vertex with a neighbour.
 // Writes counters[kNumUnits].  The split threshold is max(split_threshold,
 // estimated total / (waves * units_per_wave)); units_per_wave 0 takes the
-// planner's rule (16, or 64 on sorted-list adjacency below k = 7).
+// planner's rule (32; 128 on sorted-list adjacency; 16 at k = 7).
 // slot_l2: per slot, the extension length of its first-level node (written
 // by the estimate pass, read by the count and emit passes).
 // spec_threshold (0: the floor): the threshold at which the estimate pass

@@ -35,7 +35,8 @@ from collections import defaultdict
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ("paper_1804_09741_amd/csrc/enum.hip", "paper_1804_09741_amd/csrc/core.hip",
-                  "paper_1804_09741_amd/csrc/esu.h", "paper_1804_09741_amd/csrc/internal.h")
+                  "paper_1804_09741_amd/csrc/esu.h", "paper_1804_09741_amd/csrc/queue.h",
+                  "paper_1804_09741_amd/csrc/internal.h")
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 
 
@@ -45,6 +46,10 @@ def source_hash() -> str:
         with open(os.path.join(ROOT, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def _source_names() -> str:
+    return ", ".join(os.path.basename(n) for n in KERNEL_SOURCES)
 
 
 def short_name(name: str) -> str:
@@ -257,7 +262,7 @@ def main(argv=None):
         lines = ["# " + a.title, "",
                  "Command (from /tmp with TMPDIR=/tmp; $R is the repository root):", "",
                  "```", a.command, "```", "",
-                 "Kernel sources (enum.hip, core.hip, esu.h, internal.h) sha256[:16] = `%s`." % source_hash(),
+                 "Kernel sources (%s) sha256[:16] = `%s`." % (_source_names(), source_hash()),
                  "Durations in microseconds.", ""]
         lines += stats_table(a.dir)
         if a.note:
@@ -320,7 +325,8 @@ def main(argv=None):
              "for the durations), from /tmp with TMPDIR=/tmp; $R is the repository root:", "",
              "```"] + a.command + [
              "```", "",
-             "Kernel sources (enum.hip, core.hip, esu.h, internal.h) sha256[:16] = `%s`." % rec["source_sha256_16"],
+             "Kernel sources (%s) sha256[:16] = `%s`." % (_source_names(),
+                                                         rec["source_sha256_16"]),
              "Mean per dispatch over %s." % ", ".join(
                  "%s: %d dispatches" % (k, counts[k]) for k in kerns[:-1]), "",
              "| counter | " + " | ".join(kerns) + " |",
