@@ -402,22 +402,23 @@ static bool cores6_candidate(const mk_graph *const *gs, int ng)
 
 // Candidates whose graphs have fewer adjacency entries than kLinksLeast each,
 // and kLinksLeastAll together, are counted from the (k-2)-sets without a look at
-// their links, which costs a third of such a pass (8 cliques of 18, two-way
-// arcs among them, lose by it: 0.28 against 0.18 ms).
+// their links, which costs 30 to 40 us of a create of 75 to 290, where a pass
+// takes 0.13 ms (8 cliques of 18, two-way arcs among them, lose by it: 0.28
+// against 0.18 ms).
 constexpr int64_t kLinksLeast = 384;
 constexpr uint64_t kLinksLeastAll = 3072;
 
 // Whether a candidate is counted from the (k-2)-sets.  The line is a least
 // squares fit of the logarithm of the enumeration's pass time over the
-// counting's, 621 graphs and batches of n = 900..7000 (random, power-law, small
-// worlds, communities, geometric, cliques; shares of two-way arcs 0 to 0.8),
-// on ln n, ln (sum d^3 / sum d^2), the root of the share of linked
-// neighbours and the number of arc types, e^entropy.  Of 253 on the counting's
-// side the worst takes 1.2 times as long by it, five more than 1.05, and the
-// median 0.68 (power-law, n = 4322, m = 22000 32 against 103 ms); on the other
-// side are small worlds, n = 1200, d = 16 1.4 against 8.7 ms by the counting,
-// communities of 20, n = 5000 2.2 against 5.1, random geometric graphs of n =
-// 1200, d = 30 33 against 278.
+// counting's on ln n, ln (sum d^3 / sum d^2), the root of the share of linked
+// neighbours and the number of arc types, e^entropy: 616 graphs and batches of
+// n = 900..7000 (random, power-law, small worlds, communities, geometric,
+// cliques; shares of two-way arcs 0 to 0.8).  Of 256 on the counting's side the
+// worst takes 1.22 times as long by it, seven more than 1.05, the median 0.65
+// (power-law, n = 4322, m = 18092 32 against 103 ms); of 360 on the other side
+// 29 would gain more than 5%, and most lose: small worlds, n = 1200, d = 16 8.7
+// ms by the counting against 1.4, communities of 20, n = 5000 5.1 against 2.2,
+// random geometric graphs of n = 1200, d = 30 278 against 33.
 static bool cores6_pays(const mk_batch *b, double linked)
 {
     double d1 = 0, d2 = 0, d3 = 0;
