@@ -161,25 +161,29 @@ extern "C" int mk_count_static(mk_ctx *ctx, const mk_graph *g, const mk_table *t
     // make: consecutive ranges of a node exceed the split threshold together
     // and the threshold is at least the estimated total over 32 units a
     // wave (rounded down: a 512th at the most), so there are at most two
-    // ranges per unit of that target and one more per node; slices of
+    // ranges per unit of that target and one more per node, of which there
+    // are half as many as adjacency entries (all of them counted where there
+    // is room: where the array then lies the kernel of a graph of n = 1000 at
+    // k = 5 takes 538 us, 549 right behind the nodes there can be); slices of
     // children, which cost twice the threshold at least, add up to two more
     // per unit of the target.  A scratch without the room for those plans
     // whole children, and one without the room for all copies of the array
     // has fewer.  (Counting in place: k = 5, cliques of 147 on 8,192 vertices
     // 8.6 s, 2.1 with the array.)
     HistLayout layout = hist_layout(1, nc, grid, ~0ull, false);
-    const uint64_t target = (32ull * (uint64_t)grid + 1) * 513 / 512 + 1;
-    const uint64_t most_whole = 2 * target + nnz / 2 + kMinStaticUnits;
-    bool slices = most_whole + 2 * target <= unit_cap;
+    const uint64_t target = 32ull * (uint64_t)grid + 1;
+    uint64_t most_whole = 2 * target + nnz + kMinStaticUnits;
     size_t o_work = 0;
     const auto work_fits = [&](uint64_t most_units) {
         o_work = round_up(o_units + most_units * sizeof(int4), 256);
         return o_work + 8 * layout.words() <= kScratchBytes;
     };
-    if (layout.graph_words && !work_fits(most_whole)) {
+    if (layout.graph_words && !work_fits(most_whole + 2 * target)) {
+        most_whole = 2 * target + target / 128 + nnz / 2 + kMinStaticUnits;
         while (layout.copies > 1 && !work_fits(most_whole)) layout.copies /= 2;
         if (!work_fits(most_whole)) layout = HistLayout();
     }
+    bool slices = most_whole + 2 * target <= unit_cap;
     if (layout.graph_words) {
         slices = slices && work_fits(most_whole + 2 * target);
         (void)work_fits(slices ? most_whole + 2 * target : most_whole);  // o_work
