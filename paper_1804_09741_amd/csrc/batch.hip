@@ -475,14 +475,15 @@ namespace mk {
 
 // Device bytes that one graph brings to a batch kept to its least memory (see
 // batch_create): workspace, units, histogram and marks; *lists the arc lists of
-// a batch of this graph alone, which a batch has once.
-uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists)
+// a batch of this graph alone, which a batch has once; *small (may be null) the
+// rounding and the plan's workspace in it.
+uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists, uint64_t *small)
 {
     const uint64_t n = (uint64_t)g->n, w = (n + 31) / 32, nnz = (uint64_t)g->nnz_u;
     const bool big = g->n > MK_LDS_MARKS_MAX_VERTICES;  // list-built adjacency, global marks
     const uint64_t region = big ? list_ws_words(n, (uint64_t)g->m) : 2 * n * w;
     const uint64_t ws = 4 * (region + (n + 1) + nnz);
-    const uint64_t slots = 20 * nnz + 4 * plan_tmp_words(1, g->nnz_u, (uint32_t)nnz);
+    const uint64_t slots = 20 * nnz, plan_ws = 4 * plan_tmp_words(1, g->nnz_u, (uint32_t)nnz);
     const uint64_t units = sizeof(int4) * nnz * 4;
     const uint64_t hist = 8ull * classes_for_k(k);
     // per-workgroup marks, at most 32 workgroups per CU and 1/16 of the memory
@@ -497,7 +498,9 @@ uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists)
                  : 0;
     // the parts of the two shared allocations start on 256 bytes
     const uint64_t rounding = 16 * 256;
-    return ws + slots + units + hist + marks + sizeof(DevGraph) + 4 * kNumCounters + rounding;
+    if (small) *small = plan_ws + rounding;
+    return ws + slots + plan_ws + units + hist + marks + sizeof(DevGraph) + 4 * kNumCounters +
+           rounding;
 }
 
 uint64_t most_list_bytes() { return kMostListBytes; }

@@ -449,8 +449,10 @@ extern "C" int mk_submit(mk_server *s, const mk_graph *g, int k, uint64_t *ticke
     if (!s || !g || !ticket) return fail(MK_EINVAL, "mk_submit: NULL argument");
     if (k < 3 || k > 6) return fail(MK_ERANGE, "mk_submit: k=%d outside 3..6", k);
     if (g->ctx != s->ctx) return fail(MK_EINVAL, "mk_submit: graph of another context");
-    uint64_t lists = 0;
-    const uint64_t own = graph_least_bytes(g, k, &lists), est = own + lists;
+    // a request that fills the budget but for the rounding and the plan's
+    // workspace is taken, and charged the budget
+    uint64_t lists = 0, small = 0;
+    const uint64_t own = graph_least_bytes(g, k, &lists, &small), est = own - small + lists;
     std::lock_guard<std::mutex> lock(s->mu);
     if (s->stopping) return fail(MK_EBUSY, "mk_submit: server is stopping");
     if (est > s->opts.hbm_budget_bytes)
@@ -460,7 +462,7 @@ extern "C" int mk_submit(mk_server *s, const mk_graph *g, int k, uint64_t *ticke
     r->ticket = s->next_ticket++;
     r->g = g;
     r->k = k;
-    r->est_bytes = own;
+    r->est_bytes = std::min(own, s->opts.hbm_budget_bytes - lists);
     r->list_bytes = lists;
     r->times.submit_us = s->now_us();
     r->times.admit_us = -1;

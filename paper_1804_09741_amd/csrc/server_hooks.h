@@ -10,8 +10,9 @@
 namespace mk {
 
 // Device bytes of one graph in a batch kept to its least memory, and of the arc
-// lists of a batch of this graph alone (a batch has them once).
-uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists);
+// lists of a batch of this graph alone (a batch has them once); *small: of the
+// former the rounding and the plan's workspace (at most 62 KB).
+uint64_t graph_least_bytes(const mk_graph *g, int k, uint64_t *lists, uint64_t *small = nullptr);
 
 // the arc lists of any batch at most
 uint64_t most_list_bytes();

@@ -59,3 +59,18 @@ def test_short_groups_count_the_same(ctx, budget_mib):
     specs = [I.chung_lu_digraph(int(rng.integers(100, 900)), 900, 2.2, 15, 0.1, rng) for _ in ks]
     _, _, peak = _serve(ctx, specs, ks, budget_mib * MIB)
     assert peak <= budget_mib * MIB
+
+
+@pytest.mark.parametrize("k", [4, 5, 6])
+def test_budget_of_one_request(ctx, k):
+    """A budget of what the request's arrays take, without rounding, is enough;
+    one of half of it is refused."""
+    rng = np.random.default_rng([67, k])
+    spec = I.chung_lu_digraph(500, 1200, 2.2, 15, 0.1, rng)
+    g = ctx.load_graph(*spec)
+    least = M.mk_graph_least_footprint(g.handle, k)
+    g.free()
+    _serve(ctx, [spec, spec], [k, k], least - 4096)
+    with pytest.raises(M.MotifsError) as e:
+        _serve(ctx, [spec], [k], least // 2)
+    assert e.value.status == M.MK_EBUSY
