@@ -315,7 +315,8 @@ int mk_batch_create(mk_ctx *ctx, const mk_graph *const *gs, int32_t ng,
                     const mk_table *t, const mk_batch_opts *opts, mk_batch **out);
 
 /* Enqueue one full pass of the path on `stream` (a hipStream_t; NULL = the
-   context's stream): typed adjacency, work-unit plan, enumeration, codes,
+   context's stream, which does not wait for work on the default stream, nor
+   that for it): typed adjacency, work-unit plan, enumeration, codes,
    lookups and histograms.  Asynchronous.  d_hist: device array of
    ng * num_classes uint64 that receives the histograms (overwritten), or
    NULL to use the batch's own buffer.  The first run on a given d_hist

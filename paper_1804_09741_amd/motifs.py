@@ -427,7 +427,9 @@ def mk_batch_bytes(b: int) -> int:
 
 def mk_batch_run(b: int, d_hist: int = 0, stream: int = 0) -> None:
     """Enqueue one pass.  d_hist: device address (e.g. tensor.data_ptr()) or 0;
-    stream: hipStream_t address (e.g. torch stream's cuda_stream) or 0."""
+    stream: hipStream_t address (e.g. torch stream's cuda_stream) or 0, the
+    context's stream.  torch's default stream has address 0 too, and the two
+    are not ordered: synchronise after torch has written d_hist there."""
     _check(library().mk_batch_run(b, d_hist or None, stream or None))
 
 

@@ -35,6 +35,7 @@ def test_work_array_goes_first(ctx, k, method, use_graph):
         for cap in (full - 1, full - own - 1):
             b = ctx.batch(gs, t, most_bytes=cap, **opts)
             d = torch.full((len(gs), t.num_classes), 3, dtype=torch.int64, device="cuda:0")
+            torch.cuda.synchronize()  # the library's stream does not wait for torch's default one
             b.run(d, stream)
             assert np.array_equal(b.read()[0], ref)
             for _ in range(2):
@@ -43,6 +44,7 @@ def test_work_array_goes_first(ctx, k, method, use_graph):
             least = M.mk_batch_bytes(b.handle)
             assert least <= full - work
             d.fill_(5)
+            torch.cuda.synchronize()
             b.run(d, stream)
             assert np.array_equal(b.read()[0], ref)
             assert np.array_equal(d.cpu().numpy().astype(np.uint64), ref)
@@ -50,6 +52,7 @@ def test_work_array_goes_first(ctx, k, method, use_graph):
         # neither the work array nor the batch's own histograms fit
         b = ctx.batch(gs, t, most_bytes=least - own // 2, **opts)
         d = torch.full((len(gs), t.num_classes), 3, dtype=torch.int64, device="cuda:0")
+        torch.cuda.synchronize()
         with pytest.raises(M.MotifsError) as e:
             b.run()
         assert e.value.status == M.MK_ENOMEM

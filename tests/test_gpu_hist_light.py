@@ -38,6 +38,7 @@ def test_both_sides(ctx, k, n, m, cap, ng, work, method):
             assert M.mk_batch_bytes(b.handle) < most
         for _ in range(2):
             d = torch.full((ng, t.num_classes), 5, dtype=torch.int64, device="cuda:0")
+            torch.cuda.synchronize()  # the library's stream does not wait for torch's default one
             b.run(d, torch.cuda.current_stream())
             hist, totals = b.read()
             assert np.array_equal(hist, d.cpu().numpy().astype(np.uint64))

@@ -27,6 +27,7 @@ def test_threshold_that_differs(ctx, k, method, use_graph):
     stream = torch.cuda.current_stream()
     try:
         d = torch.full((3, t.num_classes), 9, dtype=torch.int64, device="cuda:0")
+        torch.cuda.synchronize()  # the library's stream does not wait for torch's default one
         # the first pass of the batch: its unit list holds nothing yet
         M.mk_batch_debug(b.handle, PLAN_MISS)
         for _ in range(2):

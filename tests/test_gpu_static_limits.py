@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
 def _static(ctx, g, t):
     import torch
     d = torch.full((t.num_classes,), 7, dtype=torch.int64, device="cuda:0")
+    torch.cuda.synchronize()  # the library's stream does not wait for torch's default one
     ctx.count_static(g, t, d, torch.cuda.current_stream())
     return d.cpu().numpy().astype(np.uint64)
 
